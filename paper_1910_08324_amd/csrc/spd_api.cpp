@@ -201,20 +201,22 @@ struct Layout {
     std::vector<StepPlan> steps;
     int exh_nseg = 0;
     int exh_per = 1;          // 256-slot items per wave
-    int64_t n_slabs = 0, slabs_per_wave = 0;
-    int n_waves = 0, slab_cap = 0, n_scale = 0;
+    int64_t n_slabs = 0;
+    int slabs_per_group = 0, n_groups = 0, n_scale = 0;
     int64_t slab_base[kMaxLevels + 1] = {0};
     int tiles_per_row[kMaxLevels] = {0};
     int tile_slots[kMaxLevels] = {0};
-    int64_t off_scale = 0, off_mask = 0, off_cnt = 0, off_ent = 0, off_surv = 0, off_msk = 0;
-    int64_t off_wtot = 0, off_woff = 0, off_Y = -1, off_W = -1;
+    int cpt[kMaxLevels] = {0};        // chunks per tile
+    int bit_shift[kMaxLevels] = {0};  // chunks per bit of a tile's word, as a power of two
+    int64_t off_scale = 0, off_mask = 0, off_above = 0, off_tot = 0, off_base = 0;
+    int64_t off_Y = -1, off_W = -1;
     int64_t cnt_off[kMaxLevels] = {0};
     int cnt_stride[kMaxLevels] = {0};
     int64_t off_rec = -1;     // records of the cascade steps (lossy, candidates only)
-    int64_t off_amask = -1;   // above-threshold bits of every slot (lossy, candidates only)
-    int64_t amask_words = 0;
-    int64_t mask_off[kMaxLevels] = {0};
-    int mask_wps[kMaxLevels] = {0};
+    // lossy, candidates only: directory and pool of the chunk records
+    int64_t off_dir = -1, off_pool = -1, off_used = -1;
+    int64_t pool_units = 0;
+    int64_t dir_off[kMaxLevels] = {0};
     int64_t scale_ld = 0;
 };
 
@@ -352,7 +354,6 @@ int make_layout(const spd_params *p, const Search &s, int32_t n_dm, int32_t n_in
         L->tiles_per_row[0] = L->exh_nseg;
         L->tile_slots[0] = spd::kExhSlots;
         L->n_scale = s.l_end;
-        L->slab_cap = spd::kExhSlabCap;
     } else {
         // chain of cascade steps, each covering up to kStepMaxLevels levels
         const bool fixed_T = p->segment != 0;
@@ -431,7 +432,6 @@ int make_layout(const spd_params *p, const Search &s, int32_t n_dm, int32_t n_in
         }
         I.segment = L->steps[0].T;
         I.n_segments = L->steps[0].tiles;
-        L->slab_cap = spd::kSlabCap;
         for (StepPlan &st : L->steps) {
             if (st.has_out) {
                 st.off_out = take((int64_t)n_dm * st.ld_out * 4);
@@ -466,10 +466,17 @@ int make_layout(const spd_params *p, const Search &s, int32_t n_dm, int32_t n_in
     for (int k = 0; k < nlev; ++k)
         L->slab_base[k + 1] = L->slab_base[k] + (int64_t)n_dm * L->tiles_per_row[k];
     L->n_slabs = L->slab_base[nlev];
+    for (int k = 0; k < nlev; ++k) {
+        L->cpt[k] = (int)ceil_div(L->tile_slots[k], spd::kChunk);
+        while (ceil_div(L->cpt[k], 1 << L->bit_shift[k]) > 32) ++L->bit_shift[k];
+    }
     for (StepPlan &st : L->steps)
-        for (int j = 0; j < st.J; ++j) st.lv[j].slab_base = L->slab_base[st.k0 + j];
-    // pre-candidate counts: a cascade launch keeps the counts of its levels for one tile side by
-    // side; the exhaustive search has one level
+        for (int j = 0; j < st.J; ++j) {
+            st.lv[j].cpt = L->cpt[st.k0 + j];
+            st.lv[j].bit_shift = L->bit_shift[st.k0 + j];
+        }
+    // chunk bits: a cascade launch keeps the words of its levels for one tile side by side; the
+    // exhaustive search has one level
     {
         int64_t cb = 0;
         for (StepPlan &st : L->steps) {
@@ -485,40 +492,42 @@ int make_layout(const spd_params *p, const Search &s, int32_t n_dm, int32_t n_in
             L->cnt_stride[0] = 1;
         }
     }
-    L->n_waves = (int)std::min<int64_t>(spd::kPeakWaves, L->n_slabs);
-    L->slabs_per_wave = ceil_div(L->n_slabs, L->n_waves);
-    L->n_waves = (int)ceil_div(L->n_slabs, L->slabs_per_wave);
+    // groups of the peak finder: enough that a bright pulse's run of chunks is spread over many, few
+    // enough that each can add up the totals of those before it
+    L->slabs_per_group = (int)std::max<int64_t>(
+        std::min<int64_t>(64, std::max<int64_t>(spd::kPeakGroupSlabs, ceil_div(L->n_slabs, spd::kPeakGroupsWanted))),
+        ceil_div(L->n_slabs, spd::kPeakGroups));
+    L->n_groups = (int)ceil_div(L->n_slabs, L->slabs_per_group);
 
     // the exhaustive kernel's masked tail group reads up to kExhGroup entries past the tables;
     // with a sigma table every row has its own
     L->scale_ld = (!lossy && p->rho) ? (int64_t)L->n_scale + spd::kExhGroup : 0;
     L->off_scale = take(((int64_t)L->n_scale + spd::kExhGroup) * 4 * (L->scale_ld ? n_dm : 1));
     L->off_mask = take(s.dense ? 4 : (ceil_div(s.l_end, 32) + 4) * 4);
-    L->off_cnt = take(L->n_slabs * 4);
-    L->off_ent = take(L->n_slabs * L->slab_cap * 4);
-    L->off_surv = take(L->n_slabs * 4);
-    L->off_msk = take(L->n_slabs * 8);
-    L->off_wtot = take((int64_t)L->n_waves * 8);
-    L->off_woff = take((int64_t)L->n_waves * 8);
+    L->off_above = take(L->n_slabs * 4);
+    L->off_tot = take((int64_t)L->n_groups * 4);
+    L->off_base = take(8);
     if (!(p->flags & SPD_WRITE_PLANES)) {
         if (lossy) {
-            // candidates only: no planes anywhere; the cascade leaves one bit per group of
-            // kGroup slots (any of them above the threshold or not) and the peak finder forms
-            // the few slot values it needs again from each step's record
+            // candidates only: no planes anywhere; the cascade leaves a record of every chunk with
+            // a slot above the threshold.  The pool holds 3 units per chunk, at most 32 per slab (a
+            // record takes 4 and one per slot above: room for about half of all chunks, where noise
+            // at 5 sigma needs one in a hundred); the slots of a chunk that finds no room are
+            // formed again by the peak finder from the step's record.
             L->off_rec = take((int64_t)L->steps.size() * (int64_t)sizeof(spd::RecStep));
-            int64_t words = 0;
+            int64_t entries = 0;
             for (int k = 0; k < nlev; ++k) {
-                L->mask_wps[k] = (int)ceil_div(ceil_div(L->tile_slots[k], spd::kGroup), 32);
-                L->mask_off[k] = words;
-                words += (int64_t)n_dm * L->tiles_per_row[k] * L->mask_wps[k];
+                const int64_t slabs = (int64_t)n_dm * L->tiles_per_row[k];
+                L->dir_off[k] = entries;
+                entries += slabs * L->cpt[k];
+                L->pool_units += slabs * std::min(spd::kPoolUnitsPerChunk * L->cpt[k], spd::kPoolUnitsPerSlab);
             }
-            L->off_amask = take(words * 4);
-            L->amask_words = words;
+            L->pool_units = std::min<int64_t>(L->pool_units, 0x7fffffff);
+            L->off_dir = take(entries * 4);
+            L->off_pool = take(L->pool_units * 8);
+            L->off_used = take(8);
             for (StepPlan &st : L->steps)
-                for (int j = 0; j < st.J; ++j) {
-                    st.lv[j].mask_off = L->mask_off[st.k0 + j];
-                    st.lv[j].mask_wps = L->mask_wps[st.k0 + j];
-                }
+                for (int j = 0; j < st.J; ++j) st.lv[j].dir_off = L->dir_off[st.k0 + j];
         } else {
             // the exhaustive search is bound by arithmetic: its planes go to the workspace
             L->off_Y = take(I.plane_elems * 4);
@@ -663,11 +672,11 @@ int run_filter(const spd_params *params, const Prepared &P, const float *x, int6
                int32_t n_dm, int32_t n_in, int32_t n_out, const float *mean, const float *sigma,
                void *hip_stream, LaunchMarks *marks = nullptr, const Gate *gate = nullptr) {
     auto mark = [&]() { return marks ? marks->mark() : 0; };
-    if (P.L.off_amask >= 0) {
-        // candidates only: the cascade sets only the bits of slots above the threshold (this
-        // clearing is not one of the filter's listed launches)
-        const int err = spd::launch_fill_u32(reinterpret_cast<uint32_t *>(P.ws + P.L.off_amask),
-                                             P.L.amask_words, 0u, hip_stream);
+    if (P.L.off_used >= 0) {
+        // candidates only: the pool of chunk records is empty (this clearing is not one of the
+        // filter's listed launches)
+        const int err = spd::launch_fill_u32(reinterpret_cast<uint32_t *>(P.ws + P.L.off_used), 2, 0u,
+                                             hip_stream);
         if (err) return hip_fail(err);
     }
     if (const int err = mark()) return hip_fail(err);
@@ -675,8 +684,7 @@ int run_filter(const spd_params *params, const Prepared &P, const float *x, int6
     const Layout &L = P.L;
     const spd_plan_info &I = L.info;
     const bool want_cand = params->flags & SPD_WRITE_CANDIDATES;
-    uint32_t *slab_cnt = reinterpret_cast<uint32_t *>(P.ws + L.off_cnt);
-    uint32_t *slab_ent = reinterpret_cast<uint32_t *>(P.ws + L.off_ent);
+    uint32_t *above = reinterpret_cast<uint32_t *>(P.ws + L.off_above);
     const int vec_ok = (((uintptr_t)x & 15) == 0) && (ld % 4 == 0);
     if (s.method != SPD_EXHAUSTIVE) {
         const float *in = x;
@@ -696,8 +704,7 @@ int run_filter(const spd_params *params, const Prepared &P, const float *x, int6
             a.sigma = sigma;
             a.Y = P.Y;
             a.W = P.W;
-            a.slab_cnt = slab_cnt;
-            a.slab_ent = slab_ent;
+            a.above = above;
             a.ld_in = ld_in;
             a.ld_cin = ld_in;
             a.ld_out = st.ld_out;
@@ -707,7 +714,12 @@ int run_filter(const spd_params *params, const Prepared &P, const float *x, int6
             a.n_tiles = st.tiles;
             a.vec_ok = si == 0 ? vec_ok : 1;
             if (L.off_rec >= 0) a.rec = reinterpret_cast<spd::RecStep *>(P.ws + L.off_rec) + si;
-            if (L.off_amask >= 0) a.amask = reinterpret_cast<uint32_t *>(P.ws + L.off_amask);
+            if (L.off_dir >= 0) {
+                a.dir = reinterpret_cast<uint32_t *>(P.ws + L.off_dir);
+                a.pool = reinterpret_cast<uint64_t *>(P.ws + L.off_pool);
+                a.pool_used = reinterpret_cast<unsigned long long *>(P.ws + L.off_used);
+                a.pool_units = (uint32_t)L.pool_units;
+            }
             const int err = spd::launch_step(a, s.fam, st.lds_bytes, hip_stream);
             if (err) return hip_fail(err);
             if (const int e2 = mark()) return hip_fail(e2);
@@ -754,8 +766,7 @@ int run_filter(const spd_params *params, const Prepared &P, const float *x, int6
     a.scale = scale;
     a.scale_ld = L.scale_ld;
     a.evalmask = evalmask;
-    a.slab_cnt = slab_cnt;
-    a.slab_ent = slab_ent;
+    a.above = above;
     a.pitch = I.plane_pitch[0];
     a.n_dm = n_dm;
     a.n_in = n_in;
@@ -786,20 +797,16 @@ spd::PeakArgs peak_args(const spd_params *params, const Prepared &P, int32_t n_d
     std::memset(&a, 0, sizeof(a));
     a.Y = P.Y;
     a.W = P.W;
-    a.slab_cnt = reinterpret_cast<uint32_t *>(P.ws + L.off_cnt);
-    a.slab_ent = reinterpret_cast<uint32_t *>(P.ws + L.off_ent);
-    a.surv = reinterpret_cast<uint32_t *>(P.ws + L.off_surv);
-    a.mask = reinterpret_cast<uint64_t *>(P.ws + L.off_msk);
-    a.wave_tot = reinterpret_cast<int64_t *>(P.ws + L.off_wtot);
-    a.wave_off = reinterpret_cast<int64_t *>(P.ws + L.off_woff);
+    a.above = reinterpret_cast<const uint32_t *>(P.ws + L.off_above);
+    a.group_tot = reinterpret_cast<uint32_t *>(P.ws + L.off_tot);
+    a.base_copy = reinterpret_cast<int64_t *>(P.ws + L.off_base);
     a.cand = cand;
     a.cand_cap = cand_cap;
     a.cand_count = cand_count;
     a.t0 = t0;
     a.n_slabs = L.n_slabs;
-    a.slabs_per_wave = L.slabs_per_wave;
-    a.n_waves = L.n_waves;
-    a.slab_cap = L.slab_cap;
+    a.slabs_per_group = L.slabs_per_group;
+    a.n_groups = L.n_groups;
     a.n_levels = I.n_levels;
     a.n_dm = n_dm;
     a.threshold = params->threshold;
@@ -810,19 +817,18 @@ spd::PeakArgs peak_args(const spd_params *params, const Prepared &P, int32_t n_d
         a.level_off[i] = I.plane_offset[i];
         a.tiles_per_row[i] = L.tiles_per_row[i];
         a.tile_slots[i] = L.tile_slots[i];
+        a.cpt[i] = L.cpt[i];
+        a.bit_shift[i] = L.bit_shift[i];
     }
     for (int i = 0; i <= I.n_levels; ++i) a.slab_base[i] = L.slab_base[i];
     for (int i = 0; i < I.n_levels; ++i) {
         a.cnt_off[i] = L.cnt_off[i];
         a.cnt_stride[i] = L.cnt_stride[i];
     }
-    a.rec = nullptr;
-    if (L.off_amask >= 0) {
-        a.amask = reinterpret_cast<const uint32_t *>(P.ws + L.off_amask);
-        for (int i = 0; i < I.n_levels; ++i) {
-            a.mask_off[i] = L.mask_off[i];
-            a.mask_wps[i] = L.mask_wps[i];
-        }
+    if (L.off_dir >= 0) {
+        a.dir = reinterpret_cast<const uint32_t *>(P.ws + L.off_dir);
+        a.pool = reinterpret_cast<const uint64_t *>(P.ws + L.off_pool);
+        for (int i = 0; i < I.n_levels; ++i) a.dir_off[i] = L.dir_off[i];
     }
     if (L.off_rec >= 0) {
         a.rec = reinterpret_cast<const spd::RecStep *>(P.ws + L.off_rec);
@@ -861,11 +867,12 @@ struct BatchPlan {
     std::vector<Layout> L;
     std::vector<int64_t> ws_off;
     int64_t ws_total = 0;
+    int64_t used_off = 0;       // candidates only: the beams' pool counters, apart
     int64_t table_bytes = 0;
     int64_t base_off = 0;       // offset of the item_base arrays in the table
     int64_t peak_off = 0;       // offset of the per-beam peak-finder arguments
-    int64_t wbase_off = 0;      // offset of the peak finder's wave_base array
-    int64_t n_waves = 0;        // peak-finder waves of all beams
+    int64_t gbase_off = 0;      // offset of the peak finder's group_base array
+    int64_t n_groups = 0;       // peak-finder work-groups of all beams
     int n_steps = 0;
 };
 
@@ -893,13 +900,15 @@ int batch_plan(const spd_params *params, int32_t n_beams, const spd_beam *beams,
         off += round_up(B->L[b].info.workspace_bytes, 256);
     }
     B->n_steps = (int)B->L[0].steps.size();
+    B->used_off = off;
+    if (B->L[0].off_used >= 0) off += (int64_t)n_beams * spd::kPoolCounterWords * 4;
     B->ws_total = off;
     B->base_off = round_up((int64_t)B->n_steps * n_beams * (int64_t)sizeof(spd::BeamView), 256);
     B->peak_off = round_up(B->base_off + (int64_t)B->n_steps * (n_beams + 1) * 8, 256);
-    B->wbase_off = round_up(B->peak_off + (int64_t)n_beams * (int64_t)sizeof(spd::PeakArgs), 256);
-    B->table_bytes = B->wbase_off + (int64_t)(n_beams + 1) * 8;
-    B->n_waves = 0;
-    for (int b = 0; b < n_beams; ++b) B->n_waves += B->L[b].n_waves;
+    B->gbase_off = round_up(B->peak_off + (int64_t)n_beams * (int64_t)sizeof(spd::PeakArgs), 256);
+    B->table_bytes = B->gbase_off + (int64_t)(n_beams + 1) * 8;
+    B->n_groups = 0;
+    for (int b = 0; b < n_beams; ++b) B->n_groups += B->L[b].n_groups;
     return SPD_OK;
 }
 
@@ -932,13 +941,18 @@ spd::BeamView beam_view(const spd_params *params, const BatchPlan &B, const spd_
     v.Y = planes ? bm.snr : nullptr;           // lossy only: candidates-only stores no planes
     v.W = planes ? bm.width : nullptr;
     v.rec = L.off_rec >= 0 ? reinterpret_cast<spd::RecStep *>(ws + L.off_rec) + si : nullptr;
-    v.amask = L.off_amask >= 0 ? reinterpret_cast<uint32_t *>(ws + L.off_amask) : nullptr;
+    if (L.off_dir >= 0) {
+        v.dir = reinterpret_cast<uint32_t *>(ws + L.off_dir);
+        v.pool = reinterpret_cast<uint64_t *>(ws + L.off_pool);
+        v.pool_used = reinterpret_cast<unsigned long long *>(ws_base + B.used_off +
+                                                             (int64_t)b * spd::kPoolCounterWords * 4);
+        v.pool_units = (uint32_t)L.pool_units;
+    }
     for (int j = 0; j < st.J; ++j) {
-        v.mask_off[j] = st.lv[j].mask_off;
+        v.dir_off[j] = st.lv[j].dir_off;
         v.cnt_off[j] = st.lv[j].cnt_off;
     }
-    v.slab_cnt = reinterpret_cast<uint32_t *>(ws + L.off_cnt);
-    v.slab_ent = reinterpret_cast<uint32_t *>(ws + L.off_ent);
+    v.above = reinterpret_cast<uint32_t *>(ws + L.off_above);
     v.n_dm = bm.n_dm;
     v.n_in = bm.n_in;
     v.in_len = (int32_t)st.in_len;
@@ -946,7 +960,6 @@ spd::BeamView beam_view(const spd_params *params, const BatchPlan &B, const spd_
     for (int j = 0; j < st.J; ++j) {
         v.plane_off[j] = st.lv[j].plane_off;
         v.pitch[j] = st.lv[j].pitch;
-        v.slab_base[j] = st.lv[j].slab_base;
         v.slots[j] = st.lv[j].slots;
     }
     return v;
@@ -1143,16 +1156,16 @@ int spd_batch_table(const spd_params *params, int32_t n_beams, const spd_beam *b
     }
     if (params->flags & SPD_WRITE_CANDIDATES) {
         spd::PeakArgs *pk = reinterpret_cast<spd::PeakArgs *>(t + B.peak_off);
-        int64_t *wb = reinterpret_cast<int64_t *>(t + B.wbase_off);
-        int64_t waves = 0;
+        int64_t *gb = reinterpret_cast<int64_t *>(t + B.gbase_off);
+        int64_t groups = 0;
         for (int b = 0; b < n_beams; ++b) {
             const Prepared P = beam_prepared(params, B, beams[b], b, static_cast<char *>(workspace));
             pk[b] = peak_args(params, P, beams[b].n_dm, beams[b].t0, beams[b].cand,
                               beams[b].cand_cap, beams[b].cand_count);
-            wb[b] = waves;
-            waves += B.L[b].n_waves;
+            gb[b] = groups;
+            groups += B.L[b].n_groups;
         }
-        wb[n_beams] = waves;
+        gb[n_beams] = groups;
     }
     return SPD_OK;
 }
@@ -1172,12 +1185,10 @@ int spd_batch_search(const spd_params *params, int32_t n_beams, const spd_beam *
         if (st != SPD_OK) return st;
     }
     const char *t = static_cast<const char *>(table_dev);
-    for (int b = 0; b < n_beams; ++b) {
-        const Layout &L = B.L[b];
-        if (L.off_amask < 0) continue;
+    if (B.L[0].off_used >= 0) {
         const int err = spd::launch_fill_u32(
-            reinterpret_cast<uint32_t *>(static_cast<char *>(workspace) + B.ws_off[b] + L.off_amask),
-            L.amask_words, 0u, hip_stream);
+            reinterpret_cast<uint32_t *>(static_cast<char *>(workspace) + B.used_off),
+            (int64_t)n_beams * spd::kPoolCounterWords, 0u, hip_stream);
         if (err) return hip_fail(err);
     }
     for (int si = 0; si < B.n_steps; ++si) {
@@ -1198,9 +1209,10 @@ int spd_batch_search(const spd_params *params, int32_t n_beams, const spd_beam *
     // the peak finder of every beam: one launch per pass, arguments from the table
     spd::PeakBatchArgs pb;
     pb.tab = reinterpret_cast<const spd::PeakArgs *>(t + B.peak_off);
-    pb.wave_base = reinterpret_cast<const int64_t *>(t + B.wbase_off);
-    pb.n_waves = B.n_waves;
+    pb.group_base = reinterpret_cast<const int64_t *>(t + B.gbase_off);
+    pb.n_groups = B.n_groups;
     pb.n_beams = n_beams;
+    pb.records = B.L[0].off_dir >= 0;
     const int err = spd::launch_peaks_batch(pb, hip_stream);
     if (err) return hip_fail(err);
     return SPD_OK;

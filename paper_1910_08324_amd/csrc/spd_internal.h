@@ -19,10 +19,16 @@ constexpr int kExhSlots = 256;        // output slots per exhaustive work item (
 constexpr int kExhBlock = 512;        // widths per LDS window refill in the exhaustive kernel
 constexpr int kExhGroup = 64;         // most widths per max-only group (argmax recovered afterwards)
 constexpr int kExhSmallGroupMax = 4096;  // largest L_end searched in groups of 16 widths
-constexpr int kSlabCap = 64;          // pre-candidates kept per (level, row, tile): one per lane
-constexpr int kExhSlabCap = 16;       // pre-candidates kept per exhaustive work item
+constexpr int kChunk = 256;           // slots the peak finder tests together (64 lanes x kGroup)
 constexpr int kExhItemsPerWave = 4;   // work items per wave when every width fits one block
-constexpr int kPeakWaves = 8192;      // waves of the peak-finder passes
+constexpr int kPeakGroups = 16384;    // most work-groups of a peak-finder pass
+constexpr int kPeakGroupSlabs = 16;   // fewest (level, row, tile) slabs of one of them ...
+constexpr int kPeakGroupsWanted = 4096;   // ... which grow to 64 (a wave's reach) beyond this many groups
+constexpr int kPoolUnitsPerChunk = 3; // candidates only: room for records, in 8-byte units per chunk
+constexpr int kPoolUnitsPerSlab = 32; //   of a slab, and the most for one slab
+constexpr int kPoolCounterWords = 64; // a batch's pool counters lie 256 bytes apart
+constexpr uint32_t kNoRecord = 0xffffffffu;   // a chunk above the threshold found no room for its record
+constexpr uint32_t kEmptyChunk = 0xfffffffeu; // nothing of the chunk is above the threshold
 
 // One level of a cascade step.  The step's input series is y_{k0} (for the first step the
 // normalised samples); level j of the step is the absolute level k = k0 + j, whose unit n is
@@ -45,11 +51,10 @@ struct StepLevel {
     uint64_t evalmask;       // bit U-1: U units is one of the level's widths
     int64_t plane_off;       // element offset of the level's plane
     int64_t pitch;           // elements between rows of the plane
-    int64_t slab_base;       // first pre-candidate slab of the level
-    int64_t cnt_off;         // pre-candidate count of (row d, tile t) at cnt_off + (d n_tiles + t) J
-    int64_t mask_off;        // candidates only: first word of the level's above-threshold bits
-    int32_t mask_wps;        // words of above-threshold group bits per (row, tile) slab
-    int32_t pad1;
+    int64_t cnt_off;         // chunk bits of (row d, tile t) at cnt_off + (d n_tiles + t) J
+    int64_t dir_off;         // candidates only: first directory entry of the level
+    int32_t cpt;             // chunks of kChunk slots per tile
+    int32_t bit_shift;       // chunk c of a tile is bit c >> bit_shift of its word
 };
 
 // What the peak finder needs to form any slot of a cascade step again, bit for bit, when the
@@ -81,8 +86,7 @@ struct StepArgs {
     const float *sigma;
     float *Y;                 // planes (caller's or workspace)
     uint16_t *W;
-    uint32_t *slab_cnt;
-    uint32_t *slab_ent;
+    uint32_t *above;          // chunk bits of every (level, row, tile)
     int64_t ld_in, ld_cin, ld_out;
     int32_t n_dm;
     int32_t n_in;             // raw samples per row (valid-only boundary)
@@ -103,7 +107,14 @@ struct StepArgs {
     int32_t write_planes;     // store the planes (else the peak finder recomputes what it reads)
     int32_t nth;              // threads per work-group (the planner's choice; single-beam launches)
     RecStep *rec;             // where the first work-group records the step, or null
-    uint32_t *amask;          // above-threshold bits of the slots (candidates only), or null
+    // candidates only (else null): the record of a chunk with a slot above the threshold is at
+    // 8-byte unit dir[dir_off + (d n_tiles + t) cpt + c] of the pool: 256 bits (slot i of the
+    // chunk is above), then {SNR, width} of each set bit in order
+    uint32_t *dir;
+    uint64_t *pool;
+    unsigned long long *pool_used;   // units asked for (may exceed pool_units: the rest has no record)
+    uint32_t pool_units;
+    uint32_t pad1;
     StepLevel lv[kStepMaxLevels + 1];
     float rtab[kStepMaxLevels][kMaxLevelWidths];   // 1/sqrt(base + U 2^k) at [j][U-1]
 };
@@ -119,18 +130,20 @@ struct BeamView {
     const float *sigma;
     float *Y;
     uint16_t *W;
-    uint32_t *slab_cnt;
-    uint32_t *slab_ent;
+    uint32_t *above;
     int64_t ld_in, ld_cin, ld_out;
-    int32_t n_dm, n_in, in_len, n_tiles, vec_ok, pad0;
+    int32_t n_dm, n_in, in_len, n_tiles, vec_ok;
+    uint32_t pool_units;
     RecStep *rec;               // the beam's record of this step (candidates only), or null
-    uint32_t *amask;            // the beam's above-threshold bits (candidates only), or null
-    int64_t mask_off[kStepMaxLevels];
+    uint32_t *dir;              // the beam's chunk records (candidates only), or null
+    uint64_t *pool;
+    unsigned long long *pool_used;
+    int64_t dir_off[kStepMaxLevels];
     int64_t cnt_off[kStepMaxLevels];
     int64_t plane_off[kStepMaxLevels];
     int64_t pitch[kStepMaxLevels];
-    int64_t slab_base[kStepMaxLevels];
     int32_t slots[kStepMaxLevels];
+    int32_t pad0[2];
 };
 
 struct StepBatchArgs {
@@ -151,8 +164,7 @@ struct ExhArgs {
     const float *scale;       // 1/sqrt(L) (or 1/sigma-table ratio), L = 1..l_end at index L-1
     int64_t scale_ld;         // 0: one table for every row; else row d's table at d * scale_ld
     const uint32_t *evalmask; // bit (L-1) set if width L is evaluated (list mode only)
-    uint32_t *slab_cnt;
-    uint32_t *slab_ent;
+    uint32_t *above;          // per work item (one chunk): 1 if a slot is above the threshold
     int64_t pitch;
     int32_t n_dm, n_in, n_out, l_end;
     int32_t n_seg;
@@ -182,53 +194,50 @@ struct MaskArgs {
     uint32_t bits[SPD_MAX_LIST_LEND / 32];
 };
 
-// Pre-candidate slabs: one per (level, row, tile); the slabs of level k start at slab_base[k]
-// and are ordered by row, then tile.  Tile t of level k covers slots
-// [t tile_slots[k], min((t+1) tile_slots[k], slots[k])).
+// Slabs: one per (level, row, tile); the slabs of level k start at slab_base[k] and are ordered by
+// row, then tile.  Tile t of level k covers slots [t tile_slots[k], min((t+1) tile_slots[k],
+// slots[k])) in chunks of kChunk slots; the search set a bit for every chunk (or run of
+// 2^bit_shift chunks) with a slot above the threshold.
 struct PeakArgs {
-    const float *Y;
+    const float *Y;           // planes, or null: slot values from the chunk records
     const uint16_t *W;
-    uint32_t *slab_cnt;
-    uint32_t *slab_ent;       // sorted in place by the count pass
-    uint32_t *surv;           // survivors per slab
-    uint64_t *mask;           // survivor bitmask per slab (entries mode)
-    int64_t *wave_tot;
-    int64_t *wave_off;
+    const uint32_t *above;    // chunk bits
+    uint32_t *group_tot;      // candidates of each group of slabs
+    int64_t *base_copy;       // *base_count as the count pass found it
     spd_candidate *cand;
     int64_t cand_cap;
     int64_t *cand_count;
     int64_t t0;
     int64_t n_slabs;
-    int64_t slabs_per_wave;
-    int32_t n_waves;
-    int32_t slab_cap;
+    int32_t slabs_per_group;
+    int32_t n_groups;
     int32_t n_levels, n_dm;
     float threshold;
     int32_t level_shift[kMaxLevels];
     int32_t level_slots[kMaxLevels];
     int32_t tiles_per_row[kMaxLevels];
     int32_t tile_slots[kMaxLevels];
+    int32_t cpt[kMaxLevels];
+    int32_t bit_shift[kMaxLevels];
     int64_t slab_base[kMaxLevels + 1];
     int64_t level_pitch[kMaxLevels];
     int64_t level_off[kMaxLevels];
-    // the count of slab s = slab_base[k] + r (r = d tiles_per_row[k] + t) is slab_cnt[cnt_off[k] +
-    // r cnt_stride[k]]: a cascade launch writes the counts of its levels for one tile together
+    // the word of slab s = slab_base[k] + r (r = d tiles_per_row[k] + t) is above[cnt_off[k] +
+    // r cnt_stride[k]]: a cascade launch writes the words of its levels for one tile together
     int64_t cnt_off[kMaxLevels];
     int32_t cnt_stride[kMaxLevels];
-    // planes not written (lossy, candidates only): slot values are formed again from the
-    // records of the cascade steps; level k is level level_j[k] of step level_step[k]
+    // planes not written (lossy, candidates only): the records of the chunks, and the records of
+    // the cascade steps from which the slots of a chunk without one are formed again; level k is
+    // level level_j[k] of step level_step[k]
+    const uint32_t *dir;
+    const uint64_t *pool;
+    int64_t dir_off[kMaxLevels];
     const RecStep *rec;
     int8_t level_step[kMaxLevels];
     int8_t level_j[kMaxLevels];
-    // bit g % 32 of word mask_off[k] + (d tiles_per_row[k] + t) mask_wps[k] + g / 32, with
-    // g = (m - t tile_slots[k]) / kGroup: some slot of that group of level k in row d is above
-    // the threshold (candidates only)
-    const uint32_t *amask;
-    int64_t mask_off[kMaxLevels];
-    int32_t mask_wps[kMaxLevels];
     // tile gating: flag_mode 0 = every slot; 1 = candidates only in tiles whose flag is clear
     // (the planes are complete); 2 = only in tiles whose flag is set, where the plane exists
-    // (neighbours in other tiles are absent).  Tile of (d, sample s): (d / tile_rows, s / tile_len).
+    // (elsewhere no chunk bit is set).  Tile of (d, sample s): (d / tile_rows, s / tile_len).
     const uint8_t *tile_flag;
     int32_t flag_mode, tile_rows, tile_len, n_col_tiles;
     const int64_t *base_count;  // candidates already in the list (written before it), or null
@@ -248,12 +257,13 @@ int launch_peaks(const PeakArgs &a, void *stream);
 int launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, void *stream);
 
 // the peak finder over every beam of a batch: a device table of PeakArgs (16-byte aligned) and
-// the first global wave index of each beam (n_beams + 1 entries)
+// the first global work-group of each beam (n_beams + 1 entries)
 struct PeakBatchArgs {
     const PeakArgs *tab;
-    const int64_t *wave_base;
-    int64_t n_waves;
+    const int64_t *group_base;
+    int64_t n_groups;
     int32_t n_beams;
+    int32_t records;          // slot values from the chunk records, not from planes
 };
 int launch_peaks_batch(const PeakBatchArgs &a, void *stream);
 const char *hip_error_text(int err);

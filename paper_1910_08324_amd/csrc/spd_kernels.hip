@@ -7,7 +7,7 @@
 // exh_kernel         exhaustive search (every width 1..L_end): one wave per 256 output slots,
 //                    4 consecutive starts per lane, the input window streamed through an LDS ring.
 // peak_* kernels     thresholded 3x3 peak finding over the per-level planes, with output in
-//                    (level, dm, start) order: count -> scan -> scatter.
+//                    (level, dm, start) order: count -> scatter.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -79,8 +79,8 @@ __global__ void evalmask_kernel(const MaskArgs A) {
 //      thread from a register window, writing the SNR/width planes (BoxDIT adds the carried
 //      prefix and hands each level's longest boxcar on as the next level's prefix);
 //   4. hand the last formed level (and its prefixes) to the next step through HBM.
-// Slots whose SNR is above the threshold and not below its time neighbours are recorded as
-// pre-candidates for the peak finder (a superset of the final candidates).
+// A bit per chunk of 256 slots says whether any of them is above the threshold (what the peak
+// finder has to look at); candidates-only launches also leave the values and widths of those slots.
 //
 // The width sets of the paper's configurations are compiled in (FAM selects one): the unit
 // counts of a level are then constants, so the bank is straight-line code with 4 VALU
@@ -194,13 +194,13 @@ __device__ __forceinline__ void bank_fixed(const float *y, const float *rt, floa
 }
 
 // Any width set, with the valid-only check per slot.  Xc receives the sum over `ufull` units
-// (the carry handed to the next BoxDIT level).  W as for bank_fixed.
+// (the carry handed to the next BoxDIT level).  room: the most units a boxcar of the first slot
+// may have inside the data (one less per further slot).  W as for bank_fixed.
 template <bool W>
 __device__ __forceinline__ void bank_generic(const float *y, const float *rt, int umax,
-                                             uint64_t emask, int ufull, int k, int base,
-                                             const int64_t room[kGroup], float X[kGroup],
-                                             float Xc[kGroup], float best[kGroup],
-                                             int bu[kGroup]) {
+                                             uint64_t emask, int ufull, int room,
+                                             float X[kGroup], float Xc[kGroup],
+                                             float best[kGroup], int bu[kGroup]) {
     float4 wa = *reinterpret_cast<const float4 *>(y);
     for (int u4 = 0; u4 < umax; u4 += 4) {
         const float4 wb = *reinterpret_cast<const float4 *>(y + u4 + 4);
@@ -213,11 +213,10 @@ __device__ __forceinline__ void bank_generic(const float *y, const float *rt, in
             for (int q = 0; q < kGroup; ++q) X[q] += w[q + t];
             if ((emask >> u) & 1ull) {
                 const float r = rt[u];
-                const int64_t Lw = (int64_t)base + ((int64_t)(u + 1) << k);
 #pragma unroll
                 for (int q = 0; q < kGroup; ++q) {
                     float v = X[q] * r;
-                    if (Lw > room[q]) v = SPD_NEG_INF;
+                    if (u + 1 + q > room) v = SPD_NEG_INF;
                     if (W) {
                         const bool gt = v > best[q];
                         best[q] = gt ? v : best[q];
@@ -236,6 +235,34 @@ __device__ __forceinline__ void bank_generic(const float *y, const float *rt, in
     }
 }
 
+// The same maxima and widths once more for the few chunks that get a record (candidates only),
+// one unit after another: few registers, so that the launch keeps its occupancy.
+__device__ __forceinline__ void bank_record(const float *y, const float *rt, int umax, uint64_t emask,
+                                            int room, float X[kGroup], float best[kGroup],
+                                            int bu[kGroup]) {
+    float w[kGroup];
+#pragma unroll
+    for (int q = 1; q < kGroup; ++q) w[q] = y[q - 1];
+#pragma unroll 1
+    for (int u = 0; u < umax; ++u) {
+#pragma unroll
+        for (int q = 1; q < kGroup; ++q) w[q - 1] = w[q];
+        w[kGroup - 1] = y[u + kGroup - 1];
+#pragma unroll
+        for (int q = 0; q < kGroup; ++q) X[q] += w[q];
+        if ((emask >> u) & 1ull) {
+            const float r = rt[u];
+#pragma unroll
+            for (int q = 0; q < kGroup; ++q) {
+                const float v = X[q] * r;
+                const bool gt = u + 1 + q <= room && v > best[q];
+                best[q] = gt ? v : best[q];
+                bu[q] = gt ? (u + 1) : bu[q];
+            }
+        }
+    }
+}
+
 // Where a tile finds its beam's buffers and sizes: in the launch arguments (one beam per
 // launch) or in a table in device memory (many beams per launch).
 struct ArgGeom {
@@ -248,8 +275,7 @@ struct ArgGeom {
     __device__ const float *sigma() const { return A.sigma; }
     __device__ float *Y() const { return A.Y; }
     __device__ uint16_t *W() const { return A.W; }
-    __device__ uint32_t *slab_cnt() const { return A.slab_cnt; }
-    __device__ uint32_t *slab_ent() const { return A.slab_ent; }
+    __device__ uint32_t *above() const { return A.above; }
     __device__ int64_t ld_in() const { return A.ld_in; }
     __device__ int64_t ld_cin() const { return A.ld_cin; }
     __device__ int64_t ld_out() const { return A.ld_out; }
@@ -259,11 +285,13 @@ struct ArgGeom {
     __device__ int vec_ok() const { return A.vec_ok; }
     __device__ int64_t plane_off(int j) const { return A.lv[j].plane_off; }
     __device__ int64_t pitch(int j) const { return A.lv[j].pitch; }
-    __device__ int64_t slab_base(int j) const { return A.lv[j].slab_base; }
     __device__ int slots(int j) const { return A.lv[j].slots; }
     __device__ RecStep *rec() const { return A.rec; }
-    __device__ uint32_t *amask() const { return A.amask; }
-    __device__ int64_t mask_off(int j) const { return A.lv[j].mask_off; }
+    __device__ uint32_t *dir() const { return A.dir; }
+    __device__ uint64_t *pool() const { return A.pool; }
+    __device__ unsigned long long *pool_used() const { return A.pool_used; }
+    __device__ uint32_t pool_units() const { return A.pool_units; }
+    __device__ int64_t dir_off(int j) const { return A.lv[j].dir_off; }
     __device__ int64_t cnt_off(int j) const { return A.lv[j].cnt_off; }
 };
 
@@ -282,8 +310,7 @@ struct TabGeom {
     __device__ const float *sigma() const { return V->sigma; }
     __device__ float *Y() const { return V->Y; }
     __device__ uint16_t *W() const { return V->W; }
-    __device__ uint32_t *slab_cnt() const { return V->slab_cnt; }
-    __device__ uint32_t *slab_ent() const { return V->slab_ent; }
+    __device__ uint32_t *above() const { return V->above; }
     __device__ int64_t ld_in() const { return V->ld_in; }
     __device__ int64_t ld_cin() const { return V->ld_cin; }
     __device__ int64_t ld_out() const { return V->ld_out; }
@@ -293,13 +320,61 @@ struct TabGeom {
     __device__ int vec_ok() const { return V->vec_ok; }
     __device__ int64_t plane_off(int j) const { return V->plane_off[j]; }
     __device__ int64_t pitch(int j) const { return V->pitch[j]; }
-    __device__ int64_t slab_base(int j) const { return V->slab_base[j]; }
     __device__ int slots(int j) const { return V->slots[j]; }
     __device__ RecStep *rec() const { return V->rec; }
-    __device__ uint32_t *amask() const { return V->amask; }
-    __device__ int64_t mask_off(int j) const { return V->mask_off[j]; }
+    __device__ uint32_t *dir() const { return V->dir; }
+    __device__ uint64_t *pool() const { return V->pool; }
+    __device__ unsigned long long *pool_used() const { return V->pool_used; }
+    __device__ uint32_t pool_units() const { return V->pool_units; }
+    __device__ int64_t dir_off(int j) const { return V->dir_off[j]; }
     __device__ int64_t cnt_off(int j) const { return V->cnt_off[j]; }
 };
+
+// Candidates only: the record of a wave's chunk (its 64 groups of kGroup slots): the chunk's slots
+// above the threshold with their SNRs and widths, so that the peak finder reads values instead of
+// forming them again.  `left`: plane slots from this lane's first one on; `write`: the chunk exists
+// in the tile.  Records take their room from one pool per beam; a chunk that finds none is marked and
+// the peak finder forms its slots again.  Returns whether any slot is above.
+__device__ __forceinline__ bool put_record(uint64_t *pool, unsigned long long *used, uint32_t units, uint32_t *dir,
+                                           bool write, int lane, int left, float threshold,
+                                           const float best[kGroup], const int bu[kGroup], int k,
+                                           int base) {
+    uint32_t nib = 0;
+    uint32_t total = 0;
+    int pos = 0;
+    const uint64_t below = lanes_below(lane);
+#pragma unroll
+    for (int q = 0; q < kGroup; ++q) {
+        const bool on = q < left && best[q] > threshold;
+        const uint64_t b = __ballot(on);
+        nib |= on ? 1u << q : 0u;
+        pos += __popcll(b & below);
+        total += (uint32_t)__popcll(b);
+    }
+    uint32_t off = kEmptyChunk;
+    if (total) {
+        const uint32_t need = kChunk / 64 + total;
+        if (lane == 0) {
+            // (64 bits: every chunk of a search may ask, also when the pool is full)
+            const unsigned long long at = atomicAdd(used, (unsigned long long)need);
+            off = at + need <= units ? (uint32_t)at : kNoRecord;
+        }
+        off = (uint32_t)__builtin_amdgcn_readfirstlane((int)off);
+        if (off != kNoRecord) {
+            const uint32_t up = (uint32_t)__shfl_down((int)nib, 1);
+            uint8_t *bits = reinterpret_cast<uint8_t *>(pool + off);
+            if ((lane & 1) == 0) bits[lane >> 1] = (uint8_t)(nib | (up << 4));
+            uint2 *ent = reinterpret_cast<uint2 *>(pool + off + kChunk / 64);
+#pragma unroll
+            for (int q = 0; q < kGroup; ++q)
+                if ((nib >> q) & 1u)
+                    ent[pos++] = make_uint2(__float_as_uint(best[q]),
+                                            bu[q] ? (uint32_t)(base + (bu[q] << k)) : 0u);
+        }
+    }
+    if (lane == 0 && write) *dir = off;
+    return total != 0;
+}
 
 // The step's record for the peak finder (candidates only): pointers, sizes and level constants,
 // exactly those the tiles of this launch use.  Written by one work-group.
@@ -466,8 +541,8 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
         const float *rt = RHO ? lds + A.lds_sc + j * kMaxLevelWidths : A.rtab[j];
         float *rowY = V.Y() + V.plane_off(j) + (int64_t)d * V.pitch(j);
         uint16_t *rowW = V.W() + V.plane_off(j) + (int64_t)d * V.pitch(j);
-        // a group is "fast" when the widest boxcar of its last slot ends inside the data
-        const int64_t fast_lim = (int64_t)V.n_in() - base - ((int64_t)umax << k);
+        // U units from slot m end inside the data when m + U is at most this
+        const int ends = (int)(((int64_t)V.n_in() - base) >> k);
         // the first kP4 float4 of a group's window are read from LDS before the previous batch's
         // barrier (they lie above every unit that batch writes), so their latency overlaps the
         // previous batch's stores and barrier
@@ -507,7 +582,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
                 float X[kGroup];
 #pragma unroll
                 for (int q = 0; q < kGroup; ++q) X[q] = has_carry ? cj[m0 + q] : 0.0f;
-                const bool fast = ((int64_t)(ma + kGroup - 1) << k) <= fast_lim;
+                const bool fast = ma + kGroup - 1 + umax <= ends;   // every width of every slot fits
                 if (FAM != 0 && fast && pat == 1) {
                     if constexpr (kPre) {
                         if constexpr (kNW > kP4) window_load<kNW - kP4>(yj + m0 + 4 * kP4, win2);
@@ -527,10 +602,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
 #pragma unroll
                     for (int q = 0; q < kGroup; ++q) Xc[q] = X[q];
                 } else {
-                    int64_t room[kGroup];
-#pragma unroll
-                    for (int q = 0; q < kGroup; ++q) room[q] = (int64_t)V.n_in() - ((int64_t)(ma + q) << k);
-                    bank_generic<W>(yj + m0, rt, umax, L.evalmask, L.ufull, k, base, room, X, Xc, best, bu);
+                    bank_generic<W>(yj + m0, rt, umax, L.evalmask, L.ufull, ends - ma, X, Xc, best, bu);
                 }
                 if (cg) {
                     // the last level's longest boxcar is the next step's carried prefix
@@ -560,49 +632,33 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
             if (kPre && g + NTH < ngroups) window_load<(kPre ? kP4 : 1)>(yj + (g + NTH) * kGroup, win);
             if (A.want_cand) {
                 const float gmax = fmaxf(fmaxf(best[0], best[1]), fmaxf(best[2], best[3]));
-                if (__ballot(gmax > A.threshold)) {
-                    if (V.amask()) {
-                        // candidates only: one bit per group of kGroup slots, set where any of
-                        // them is above the threshold (the bits start cleared): the wave's
-                        // ballot is its 64 groups, two words of the slab
-                        const uint64_t gbits = __ballot(act && gmax > A.threshold);
-                        const int word = (gb + 64 * (tid >> 6)) >> 5;
-                        if (lane == 0) {
-                            uint32_t *mw = V.amask() + V.mask_off(j) +
-                                           ((int64_t)d * V.n_tiles() + tile) * L.mask_wps + word;
-                            if ((uint32_t)gbits && word < L.mask_wps) mw[0] = (uint32_t)gbits;
-                            if ((uint32_t)(gbits >> 32) && word + 1 < L.mask_wps)
-                                mw[1] = (uint32_t)(gbits >> 32);
-                        }
-                    }
-                    // time neighbours: inside the group, or the adjacent groups of the
-                    // neighbouring lanes; unknown neighbours (wave edges) count as -inf
-                    float left = __shfl_up(best[kGroup - 1], 1);
-                    float right = __shfl_down(best[0], 1);
-                    if (lane == 0) left = SPD_NEG_INF;
-                    if (lane == 63) right = SPD_NEG_INF;
-                    int nh = 0;
-                    bool hit[kGroup];
-#pragma unroll
-                    for (int q = 0; q < kGroup; ++q) {
-                        const float l = q > 0 ? best[q - 1] : left;
-                        const float rr = q + 1 < kGroup ? best[q + 1] : right;
-                        hit[q] = act && (ma + q < V.slots(j)) && best[q] > A.threshold &&
-                                 best[q] > l && best[q] >= rr;
-                        nh += hit[q];
-                    }
-                    if (nh) {
-                        const int64_t slab = V.slab_base(j) + (int64_t)d * V.n_tiles() + tile;
-                        uint32_t pos = atomicAdd(&st_cnt[j], (uint32_t)nh);
+                const bool any = __ballot(act && gmax > A.threshold) != 0;
+                if (any || (!W && L.bit_shift)) {
+                    // this wave's 64 groups are one chunk of the tile
+                    const int chunk = (gb >> 6) + (tid >> 6);
+                    bool set = any;
+                    if constexpr (!W) {
+                        // candidates only: the chunk's record holds its slots above the
+                        // threshold with their widths, which this launch has not tracked; the
+                        // window is still in LDS, so the widths are evaluated once more
+                        float rb[kGroup];
+                        int ru[kGroup];
 #pragma unroll
                         for (int q = 0; q < kGroup; ++q) {
-                            if (hit[q]) {
-                                if (pos < (uint32_t)kSlabCap)
-                                    V.slab_ent()[slab * kSlabCap + pos] = (uint32_t)(ma + q);
-                                ++pos;
-                            }
+                            rb[q] = SPD_NEG_INF;
+                            ru[q] = 0;
                         }
+                        if (any && act) {
+                            float X[kGroup];
+#pragma unroll
+                            for (int q = 0; q < kGroup; ++q) X[q] = has_carry ? cj[m0 + q] : 0.0f;
+                            bank_record(yj + m0, rt, umax, L.evalmask, ends - ma, X, rb, ru);
+                        }
+                        const int64_t di = V.dir_off(j) + ((int64_t)d * V.n_tiles() + tile) * L.cpt + chunk;
+                        set = put_record(V.pool(), V.pool_used(), V.pool_units(), V.dir() + di, chunk < L.cpt,
+                                         lane, V.slots(j) - ma, A.threshold, rb, ru, k, base);
                     }
+                    if (set && lane == 0) atomicOr(&st_cnt[j], 1u << (chunk >> L.bit_shift));
                 }
             }
             if (sync_batches) {
@@ -637,9 +693,9 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
     }
     if (A.want_cand) {
         lds_barrier();
-        // the tile's counts of all its levels side by side (one short write per work-group)
+        // the tile's chunk bits of all its levels side by side (one short write per work-group)
         if (tid < A.J)
-            V.slab_cnt()[V.cnt_off(tid) + ((int64_t)d * V.n_tiles() + tile) * A.J] = st_cnt[tid];
+            V.above()[V.cnt_off(tid) + ((int64_t)d * V.n_tiles() + tile) * A.J] = st_cnt[tid];
     }
 }
 
@@ -763,7 +819,7 @@ __global__ __launch_bounds__(64) void exh_kernel(const ExhArgs A) {
         const int64_t t = (int64_t)(d / A.tile_rows) * A.n_col_tiles + (g0 * kExhSlots) / A.tile_len;
         if (!A.tile_flag[t]) {
             if (A.want_cand && lane == 0)
-                for (int g = g0; g < g_end; ++g) A.slab_cnt[(int64_t)d * A.n_seg + g] = 0;
+                for (int g = g0; g < g_end; ++g) A.above[(int64_t)d * A.n_seg + g] = 0;
             return;
         }
     }
@@ -904,42 +960,11 @@ __global__ __launch_bounds__(64) void exh_kernel(const ExhArgs A) {
         }
     }
     if (A.want_cand) {
-        // pre-candidates: above the threshold and not below either time neighbour (neighbours
-        // held by other work items are unknown and treated as -inf)
-        float left = __shfl_up(best[3], 1);
-        float right = __shfl_down(best[0], 1);
-        if (lane == 0) left = SPD_NEG_INF;
-        if (lane == 63) right = SPD_NEG_INF;
-        bool hit[4];
-        int mine = 0;
+        bool on = false;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const float l = v > 0 ? best[v - 1] : left;
-            const float r = v < 3 ? best[v + 1] : right;
-            hit[v] = (m0 + v < A.n_out) && best[v] > A.threshold && best[v] > l && best[v] >= r;
-            mine += hit[v];
-        }
-        const uint64_t any = __ballot(mine > 0);
-        uint32_t total = 0;
-        if (any) {
-            int pre = mine;                              // inclusive prefix over lanes
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int t = __shfl_up(pre, off);
-                if (lane >= off) pre += t;
-            }
-            total = (uint32_t)__shfl(pre, 63);
-            int pos = pre - mine;
-            const int64_t slab = (int64_t)d * A.n_seg + g;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                if (hit[v]) {
-                    if (pos < kExhSlabCap) A.slab_ent[slab * kExhSlabCap + pos] = (uint32_t)(m0 + v);
-                    ++pos;
-                }
-            }
-        }
-        if (lane == 0) A.slab_cnt[(int64_t)d * A.n_seg + g] = total;
+        for (int v = 0; v < 4; ++v) on = on || (m0 + v < A.n_out && best[v] > A.threshold);
+        const bool any = __ballot(on) != 0;
+        if (lane == 0) A.above[(int64_t)d * A.n_seg + g] = any ? 1u : 0u;
     }
     if (fetch) {
         ring_put(ring4, (((loaded_to - base) >> 2) + lane) & (kRing4 - 1), nx);
@@ -952,19 +977,33 @@ __global__ __launch_bounds__(64) void exh_kernel(const ExhArgs A) {
 // ----------------------------------------------------------------------------------------
 // Peak finding (candidate selection).  A slot is a candidate iff its SNR is above the
 // threshold and it passes the 3x3 neighbour test (strict against neighbours earlier in
-// row-major order, non-strict against later ones).  The search kernels recorded, per
-// (level, row, tile) slab, the slots above the threshold that are not below their time
-// neighbours; a slab that overflowed is rescanned densely over its tile.  Three passes keep the
-// output in (level, dm, start) order without a global sort: per-wave survivor counts (each
-// slab's entries sorted in the wave), one scan, scatter.
+// row-major order, non-strict against later ones; a neighbour at or below the threshold can
+// never block one above it).
+//
+// The search left one bit per chunk of 256 slots that holds a slot above the threshold.  A
+// work-group takes a run of (level, row, tile) slabs, deals the set bits out to its waves, and a
+// wave tests a whole chunk at once, four slots per lane: its own values and those of the rows on
+// either side (loaded only where their bits are set), time neighbours from the adjacent lanes.
+// Two passes keep the output in (level, dm, start) order without a sort or a scan kernel: the
+// first counts the candidates of each group of slabs, the second adds up the totals of the
+// groups before its own, tests again (where there is anything to write) and writes the list.
+// What bounds it is the latency of the chain word -> neighbours' words -> values, hence many
+// small groups: a bright pulse sets a run of chunks, and a wave that takes a long range of slabs
+// spends its time on that run alone.  Both passes together, against pre-candidate lists of 64 a slab
+// with dense rescans of the slabs that overflowed them, a scan kernel between: 500 x 95908 slots
+// IG(1) 162 -> 21 us; 1024 x 131072 BD-16 269 -> 30 us; 4096 x 262144 IG(1) 253 -> 95 us;
+// 512 x 131072 BD-32 candidates only (its rescans formed every slot of a tile again) 4290 -> 32 us.
+//
+// Values come from the planes or, candidates only, from the records the cascade left of every
+// such chunk.  A chunk that found no room for its record has its slots formed again from the step's record:
+// the units of the level as pairwise sums of the step's input series (level by level, as the
+// cascade forms them), the BoxDIT carried prefix through the levels below, and the level's
+// widths in increasing order with the same FP32 operations as step_tile, so value and width
+// are bitwise those the planes would hold.
 // ----------------------------------------------------------------------------------------
-// When only candidates are requested the lossy searches store no planes, and the peak finder
-// forms each slot value it reads again from the step's record: the units of the level as
-// pairwise sums of the step's input series (level by level, as the cascade forms them), the
-// BoxDIT carried prefix through the levels below, and the level's widths in increasing order
-// with the same FP32 operations as step_tile.  Value and width are therefore bitwise those the
-// planes would hold; the work is small because only slots near pre-candidates are formed.
-// ----------------------------------------------------------------------------------------
+constexpr int kPeakThreads = 256;
+constexpr int kPeakGroupWaves = kPeakThreads / 64;
+
 __device__ __forceinline__ float rec_in(const RecStep &R, const float *inr, float mu, float inv,
                                         int64_t r) {
     if (r >= R.in_len) return 0.0f;                   // the tile pads past the data with zeros
@@ -996,9 +1035,14 @@ __device__ __noinline__ float rec_unit(const RecStep &R, const float *inr, float
         case 1: return rec_tree<1>(R, inr, mu, inv, a);
         case 2: return rec_tree<2>(R, inr, mu, inv, a);
         case 3: return rec_tree<3>(R, inr, mu, inv, a);
-        case 4: return rec_tree<4>(R, inr, mu, inv, a);
-        default: return rec_tree<5>(R, inr, mu, inv, a);
+        default: break;
     }
+    // levels 4 and 5 from sums of 8, pairwise as before (fewer registers than a tree of 32)
+    float s[2] = {0.0f, 0.0f};
+    const int halves = j == 4 ? 1 : 2;
+    for (int i = 0; i < halves; ++i)
+        s[i] = rec_tree<3>(R, inr, mu, inv, a + 16 * i) + rec_tree<3>(R, inr, mu, inv, a + 16 * i + 8);
+    return j == 4 ? s[0] : s[0] + s[1];
 }
 
 // Y and W of slot m (absolute) of level j of the step, row d
@@ -1046,77 +1090,115 @@ __device__ __noinline__ float rec_slot(const RecStep &R, int d, int j, int64_t m
     return best;
 }
 
-// Y of the slots m0, m0+1, m0+2 of level j in row d whose bit in `need` (bit i: slot m0+i) is
-// set, into y[i]: each unit of the level is formed once and added, in order, to the running sum
-// of every slot that covers it, so every slot's sum and SNR are those rec_slot forms.
-__device__ __noinline__ void rec_slots3(const RecStep &R, int d, int j, int64_t m0, int need,
-                                       float y[3]) {
-    const float *inr = R.in + (int64_t)d * R.ld_in;
-    float mu = 0.0f, inv = 1.0f;
-    if (R.normalise) {
-        mu = R.mean[d];
-        inv = 1.0f / R.sigma[d];
-    }
-    const RecLevel &L = R.lv[j];
-    float X[3] = {0.0f, 0.0f, 0.0f}, best[3];
-    int64_t room[3];
-    for (int i = 0; i < 3; ++i) {
-        best[i] = SPD_NEG_INF;
-        room[i] = 0;
-        if (!((need >> i) & 1)) continue;                   // (m0 + i may be -1 then)
-        room[i] = (int64_t)R.n_in - ((m0 + i) << L.k);
-        if (R.carry && (j > 0 || R.cin != nullptr)) {
-            const int64_t m = m0 + i, p0 = m << j;
-            if (R.cin && p0 < R.lv[0].slots) X[i] = R.cin[(int64_t)d * R.ld_cin + p0];
-            for (int l = 0; l < j; ++l) {
-                const int64_t p = m << (j - l);
-                const int uf = R.lv[l].ufull;
-                for (int u = 0; u < uf; ++u) X[i] += rec_unit(R, inr, mu, inv, l, p + u);
-            }
-        }
-    }
-    const float *rr = R.rho ? R.rho + (int64_t)d * R.ld_rho : nullptr;
-    const int first = (need & 1) ? 0 : (need & 2) ? 1 : 2;
-    const int last = (need & 4) ? 2 : (need & 2) ? 1 : 0;
-    for (int v = first; v < L.umax + last; ++v) {           // unit m0 + v
-        const float yu = rec_unit(R, inr, mu, inv, j, m0 + v);
-        for (int i = first; i <= last; ++i) {
-            const int u = v - i;                            // width index of slot m0 + i
-            if (!((need >> i) & 1) || u < 0 || u >= L.umax) continue;
-            X[i] += yu;
-            if ((L.evalmask >> u) & 1ull) {
-                float r = L.rt[u];
-                if (rr) {
-                    const double Lw = (double)L.base + ldexp((double)(u + 1), L.k);
-                    r = (float)((double)L.rt[u] / rho_of_width(rr, R.n_rho, Lw));
-                }
-                float val = X[i] * r;
-                if ((int64_t)L.base + ((int64_t)(u + 1) << L.k) > room[i]) val = SPD_NEG_INF;
-                if (val > best[i]) best[i] = val;
-            }
-        }
-    }
-    for (int i = 0; i < 3; ++i) y[i] = best[i];
-}
 
 // The helpers take the arguments either from the launch (one beam) or from a per-beam table in
 // the constant address space (a batch); PA is the (qualified) PeakArgs type.
-// SNR (and width, if w) of slot m of level k in row d: from the planes, or formed again.
+// the chunk bits of tile t of level k in row d
 template <class PA>
-__device__ __forceinline__ float slot_value(PA &A, int k, int d, int m, int *w) {
-    if (A.rec) {
-        int wl;
-        const float y = rec_slot(A.rec[A.level_step[k]], d, A.level_j[k], m, &wl);
-        if (w) *w = wl;
-        return y;
-    }
-    const int64_t i = A.level_off[k] + (int64_t)d * A.level_pitch[k] + m;
-    if (w) *w = A.W[i];
-    return A.Y[i];
+__device__ __forceinline__ uint32_t slab_word(PA &A, int k, int d, int t) {
+    return A.above[A.cnt_off[k] + ((int64_t)d * A.tiles_per_row[k] + t) * A.cnt_stride[k]];
 }
 
-// tile gating of the candidates (flag_mode): may slot m of level k in row d be a candidate, and
-// does its value exist (mode 2: only inside flagged tiles)?
+// where the record of chunk c of tile t of level k in row d is (or kNoRecord, kEmptyChunk)
+template <class PA>
+__device__ __forceinline__ uint32_t chunk_record(PA &A, int k, int d, int t, int c) {
+    return A.dir[A.dir_off[k] + ((int64_t)d * A.tiles_per_row[k] + t) * A.cpt[k] + c];
+}
+
+// SNRs (and widths, if w is not null) of slots m0 .. m0 + 3 of level k in row d, slots m0 + 4 lane
+// of chunk c of tile t whose bit is set; slots past m_end are -inf.  From records, so are the
+// slots at or below the threshold.
+template <bool REC, class PA>
+__device__ __forceinline__ void chunk_values(PA &A, int k, int d, int t, int c, int lane, int m0,
+                                             int m_end, float y[kGroup], int *w) {
+#pragma unroll
+    for (int q = 0; q < kGroup; ++q) y[q] = SPD_NEG_INF;
+    if constexpr (!REC) {
+        const int64_t i = A.level_off[k] + (int64_t)d * A.level_pitch[k] + m0;
+        if (m0 + kGroup <= m_end) {
+            const float4 v = *reinterpret_cast<const float4 *>(A.Y + i);
+            y[0] = v.x;
+            y[1] = v.y;
+            y[2] = v.z;
+            y[3] = v.w;
+        } else {
+#pragma unroll
+            for (int q = 0; q < kGroup; ++q)
+                if (m0 + q < m_end) y[q] = A.Y[i + q];
+        }
+        (void)w;                                   // (the scatter pass reads the widths it needs)
+    } else {
+        const uint32_t off = chunk_record(A, k, d, t, c);
+        if (off == kEmptyChunk) return;
+        if (off == kNoRecord) {
+            const RecStep &R = A.rec[A.level_step[k]];
+            for (int q = 0; q < kGroup; ++q) {
+                if (m0 + q >= m_end) break;
+                int wq;
+                y[q] = rec_slot(R, d, A.level_j[k], m0 + q, &wq);
+                if (w) w[q] = wq;
+            }
+            return;
+        }
+        const uint64_t *r = A.pool + off;
+        const int word = lane >> 4, bit = (lane & 15) * kGroup;
+        int pos = 0;
+        uint64_t own = 0;
+#pragma unroll
+        for (int i = 0; i < kChunk / 64; ++i) {
+            const uint64_t b = r[i];
+            if (i < word) pos += __popcll(b);
+            if (i == word) own = b;
+        }
+        pos += __popcll(own & ((1ull << bit) - 1));
+        const uint2 *ent = reinterpret_cast<const uint2 *>(r + kChunk / 64);
+        const uint32_t nib = (uint32_t)(own >> bit) & 15u;
+#pragma unroll
+        for (int q = 0; q < kGroup; ++q) {
+            if ((nib >> q) & 1u) {
+                const uint2 e = ent[pos++];
+                y[q] = __uint_as_float(e.x);
+                if (w) w[q] = (int)e.y;
+            }
+        }
+    }
+}
+
+// SNR of slot m of level k in row d, -inf if its chunk's bit is clear (one lane on its own: the
+// slots beside a chunk)
+template <bool REC, class PA>
+__device__ __forceinline__ float slot_value(PA &A, int k, int d, int m) {
+    const int ts = A.tile_slots[k];
+    const int t = m / ts;
+    const int i = m - t * ts;
+    const int c = i / kChunk;
+    if (!((slab_word(A, k, d, t) >> (c >> A.bit_shift[k])) & 1u)) return SPD_NEG_INF;
+    if constexpr (!REC) {
+        return A.Y[A.level_off[k] + (int64_t)d * A.level_pitch[k] + m];
+    } else {
+        const uint32_t off = chunk_record(A, k, d, t, c);
+        if (off == kEmptyChunk) return SPD_NEG_INF;
+        if (off == kNoRecord) {
+            int w;
+            return rec_slot(A.rec[A.level_step[k]], d, A.level_j[k], m, &w);
+        }
+        const uint64_t *r = A.pool + off;
+        const int b = i - c * kChunk;
+        int pos = 0;
+        uint64_t own = 0;
+#pragma unroll
+        for (int q = 0; q < kChunk / 64; ++q) {
+            const uint64_t v = r[q];
+            if (q < (b >> 6)) pos += __popcll(v);
+            if (q == (b >> 6)) own = v;
+        }
+        if (!((own >> (b & 63)) & 1ull)) return SPD_NEG_INF;
+        pos += __popcll(own & ((1ull << (b & 63)) - 1));
+        return __uint_as_float(reinterpret_cast<const uint2 *>(r + kChunk / 64)[pos].x);
+    }
+}
+
+// tile gating of the candidates (flag_mode): may slot m of level k in row d be a candidate?
 template <class PA>
 __device__ __forceinline__ bool slot_kept(PA &A, int k, int d, int m) {
     if (A.flag_mode == 0) return true;
@@ -1125,350 +1207,213 @@ __device__ __forceinline__ bool slot_kept(PA &A, int k, int d, int m) {
     return A.flag_mode == 2 ? f : !f;
 }
 
-// candidates only: may slot m of level k in row d be above the threshold?  (The bit of its
-// group of kGroup slots: clear means every slot of the group is at or below the threshold.)
-template <class PA>
-__device__ __forceinline__ bool slot_above(PA &A, int k, int d, int m) {
+// The candidates of chunk c of tile t of level k in row d, whose bit is set: bit q of the result
+// for slot m0 + q of this lane.  y receives the slots' SNRs and, from records, w their widths.
+template <bool REC, class PA>
+__device__ __forceinline__ uint32_t chunk_test(PA &A, int k, int d, int t, int c, int lane, int &m0,
+                                               float y[kGroup], int w[kGroup]) {
     const int ts = A.tile_slots[k];
-    const int t = m / ts, g = (m - t * ts) / kGroup;
-    const uint32_t w = A.amask[A.mask_off[k] + ((int64_t)d * A.tiles_per_row[k] + t) * A.mask_wps[k] +
-                               (g >> 5)];
-    return (w >> (g & 31)) & 1u;
-}
-
-// The 3x3 test when the planes are not stored: a neighbour at or below the threshold cannot
-// block a slot above it, so only neighbours whose group bit is set are formed again, with the
-// slot itself if any is (y_known: its value is already y_in); the slots of one row are formed
-// together.
-// time_tested: m is a pre-candidate, so the cascade already compared it exactly with its time
-// neighbours that lie in the same wave's 256 slots of the tile (only those across a wave or
-// tile edge are unknown to it).
-template <class PA>
-__device__ __forceinline__ bool peak_test_rec(PA &A, int k, int d, int m, bool y_known = false,
-                                              float y_in = 0.0f, bool time_tested = false) {
     const int slots = A.level_slots[k];
-    const int ts = A.tile_slots[k];
-    const int lm = m - (m / ts) * ts;                     // slot within its tile
-    const bool left_known = time_tested && (lm & 255) != 0;
-    const bool right_known = time_tested && ((lm + 1) & 255) != 0 && lm + 1 < ts;
-    int need[3] = {0, 0, 0};
-    bool any = false;
+    const int m_end = min((t + 1) * ts, slots);
+    const int mc = t * ts + c * kChunk;                   // the chunk's first slot
+    m0 = mc + kGroup * lane;
+    const int bit = c >> A.bit_shift[k];
+    const bool up = d > 0 && ((slab_word(A, k, d - 1, t) >> bit) & 1u);
+    const bool down = d + 1 < A.n_dm && ((slab_word(A, k, d + 1, t) >> bit) & 1u);
+    chunk_values<REC>(A, k, d, t, c, lane, m0, m_end, y, w);
+    float yn[2][kGroup];
 #pragma unroll
-    for (int a = -1; a <= 1; ++a) {
-        const int dn = d + a;
-        if (dn < 0 || dn >= A.n_dm) continue;
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = -1; b <= 1; ++b) {
-            if (a == 0 && b == 0) continue;
-            if (a == 0 && ((b < 0 && left_known) || (b > 0 && right_known))) continue;
-            const int mn = m + b;
-            if (mn < 0 || mn >= slots) continue;
-            if (slot_above(A, k, dn, mn)) {
-                need[a + 1] |= 1 << (b + 1);
-                any = true;
-            }
+        for (int q = 0; q < kGroup; ++q) yn[a][q] = SPD_NEG_INF;
+    if (up) chunk_values<REC>(A, k, d - 1, t, c, lane, m0, m_end, yn[0], nullptr);
+    if (down) chunk_values<REC>(A, k, d + 1, t, c, lane, m0, m_end, yn[1], nullptr);
+
+    // time neighbours outside this lane's four slots: the adjacent lanes', or the adjacent
+    // chunks' at either end (looked up only by a lane whose slot there is above the threshold)
+    float l[3], r[3];
+    l[0] = __shfl_up(yn[0][kGroup - 1], 1);
+    l[1] = __shfl_up(y[kGroup - 1], 1);
+    l[2] = __shfl_up(yn[1][kGroup - 1], 1);
+    r[0] = __shfl_down(yn[0][0], 1);
+    r[1] = __shfl_down(y[0], 1);
+    r[2] = __shfl_down(yn[1][0], 1);
+    if (lane == 0) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int dn = d + a - 1;
+            l[a] = (y[0] > A.threshold && m0 > 0 && dn >= 0 && dn < A.n_dm) ? slot_value<REC>(A, k, dn, m0 - 1)
+                                                                           : SPD_NEG_INF;
         }
     }
-    if (!any) return true;
-    const RecStep &R = A.rec[A.level_step[k]];
-    const int j = A.level_j[k];
-    float y = y_in;
-    if (!y_known) need[1] |= 2;                 // the slot itself, formed with its row
-    float v[3][3];
+    const int last = min(mc + kChunk, (t + 1) * ts) - kGroup;   // first slot of the chunk's last lane
+    if (m0 == last) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
-        if (need[a]) rec_slots3(R, d + a - 1, j, (int64_t)m - 1, need[a], v[a]);
-    if (!y_known) y = v[1][1];
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            if (!((need[a] >> b) & 1) || (a == 1 && b == 1)) continue;
-            const bool earlier = (a < 1) || (a == 1 && b < 1);
-            if (earlier ? !(y > v[a][b]) : !(y >= v[a][b])) return false;
-        }
-    return true;
-}
-
-template <class PA>
-__device__ __forceinline__ bool peak_test(PA &A, int k, int d, int m, float y) {
-    const int slots = A.level_slots[k];
-#pragma unroll
-    for (int a = -1; a <= 1; ++a) {
-        const int dn = d + a;
-        if (dn < 0 || dn >= A.n_dm) continue;
-#pragma unroll
-        for (int b = -1; b <= 1; ++b) {
-            if (a == 0 && b == 0) continue;
-            const int mn = m + b;
-            if (mn < 0 || mn >= slots) continue;
-            if (A.flag_mode == 2 && !slot_kept(A, k, dn, mn)) continue;   // no value there
-            const float yn = slot_value(A, k, dn, mn, nullptr);
-            const bool earlier = (a < 0) || (a == 0 && b < 0);
-            if (earlier ? !(y > yn) : !(y >= yn)) return false;
+        for (int a = 0; a < 3; ++a) {
+            const int dn = d + a - 1;
+            r[a] = (y[kGroup - 1] > A.threshold && m0 + kGroup < slots && dn >= 0 && dn < A.n_dm)
+                       ? slot_value<REC>(A, k, dn, m0 + kGroup) : SPD_NEG_INF;
         }
     }
-    return true;
+    uint32_t hit = 0;
+#pragma unroll
+    for (int q = 0; q < kGroup; ++q) {
+        const float v = y[q];
+        const float ul = q > 0 ? yn[0][q - 1] : l[0], ur = q + 1 < kGroup ? yn[0][q + 1] : r[0];
+        const float sl = q > 0 ? y[q - 1] : l[1], sr = q + 1 < kGroup ? y[q + 1] : r[1];
+        const float dl = q > 0 ? yn[1][q - 1] : l[2], dr = q + 1 < kGroup ? yn[1][q + 1] : r[2];
+        const bool ok = v > A.threshold && v > ul && v > yn[0][q] && v > ur && v > sl && v >= sr &&
+                        v >= dl && v >= yn[1][q] && v >= dr;
+        if (ok && slot_kept(A, k, d, m0 + q)) hit |= 1u << q;
+    }
+    return hit;
 }
 
-struct SlabPos {
-    int k, d, t, mlo, mhi;
-};
-
+// level of slab s
 template <class PA>
-__device__ __forceinline__ SlabPos slab_decode(PA &A, int64_t s) {
-    SlabPos p;
+__device__ __forceinline__ int slab_level(PA &A, int64_t s) {
     int k = 0;
     while (k + 1 < A.n_levels && s >= A.slab_base[k + 1]) ++k;
-    const int64_t r = s - A.slab_base[k];
-    p.k = k;
-    p.d = (int)(r / A.tiles_per_row[k]);
-    p.t = (int)(r - (int64_t)p.d * A.tiles_per_row[k]);
-    p.mlo = p.t * A.tile_slots[k];
-    p.mhi = min(p.mlo + A.tile_slots[k], A.level_slots[k]);
-    return p;
+    return k;
 }
 
-template <class PA>
-__device__ __forceinline__ int64_t slab_cnt_index(PA &A, int64_t s) {
-    int k = 0;
-    while (k + 1 < A.n_levels && s >= A.slab_base[k + 1]) ++k;
-    return A.cnt_off[k] + (s - A.slab_base[k]) * A.cnt_stride[k];
-}
-
-template <class PA>
-__device__ __forceinline__ float plane_at(PA &A, int k, int d, int m) {
-    return slot_value(A, k, d, m, nullptr);
-}
-
-__device__ __forceinline__ uint32_t wave_sort_u32(uint32_t key, int lane) {
-    // bitonic sort of one key per lane, ascending across the 64 lanes
+// One group of slabs of a pass.  SCATTER false: count its candidates; true: write them.
+template <bool REC, bool SCATTER, class PA>
+__device__ __forceinline__ void peak_group(PA &A, int g) {
+    __shared__ int64_t part[kPeakGroupWaves];
+    __shared__ uint32_t cnt[2][kPeakGroupWaves];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t sbeg = (int64_t)g * A.slabs_per_group;
+    const int64_t send = min(sbeg + A.slabs_per_group, A.n_slabs);
+    int64_t run = 0;                     // SCATTER: where the next candidate goes
+    if constexpr (SCATTER) {
+        const uint32_t mine = A.group_tot[g];
+        const bool last = g + 1 == A.n_groups;
+        if (mine == 0 && !last) return;
+        int64_t sum = 0;
+        for (int i = threadIdx.x; i < g; i += kPeakThreads) sum += A.group_tot[i];
 #pragma unroll
-    for (int k = 2; k <= 64; k <<= 1) {
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+        if (lane == 0) part[wave] = sum;
+        __syncthreads();
+        run = *A.base_copy;
 #pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            const uint32_t other = (uint32_t)__shfl_xor((int)key, j);
-            const bool asc = (lane & k) == 0;
-            const bool low = (lane & j) == 0;
-            key = (asc == low) ? min(key, other) : max(key, other);
-        }
+        for (int i = 0; i < kPeakGroupWaves; ++i) run += part[i];
+        if (last && threadIdx.x == 0) *A.cand_count = run + mine;
+        if (mine == 0) return;
+    } else {
+        // candidates already in the list (the scatter pass may overwrite the same count)
+        if (g == 0 && threadIdx.x == 0) *A.base_copy = A.base_count ? *A.base_count : 0;
     }
-    return key;
-}
-
-// count pass of wave w of a beam
-template <class PA>
-__device__ __forceinline__ void peak_count_wave(PA &A, int w, int lane) {
-    const int64_t sbeg = (int64_t)w * A.slabs_per_wave;
-    const int64_t send = min(sbeg + A.slabs_per_wave, A.n_slabs);
-    int64_t total = 0;
+    uint32_t total = 0;                  // SCATTER false: this wave's candidates
+    int turn = 0;
     for (int64_t sb = sbeg; sb < send; sb += 64) {
         const int64_t s = sb + lane;
-        const uint32_t c = (s < send) ? A.slab_cnt[slab_cnt_index(A, s)] : 0u;
-        if (s < send && c == 0) A.surv[s] = 0;
-        uint64_t nz = __ballot(c != 0);
-        while (nz) {
-            const int l = __ffsll((unsigned long long)nz) - 1;
-            nz &= nz - 1;
-            const int64_t ss = sb + l;
-            const uint32_t cc = (uint32_t)__shfl((int)c, l);
-            const SlabPos p = slab_decode(A, ss);
-            uint32_t nsurv = 0;
-            uint64_t msk = 0;
-            if (cc <= (uint32_t)A.slab_cap) {
-                uint32_t key = (lane < (int)cc) ? A.slab_ent[ss * A.slab_cap + lane] : 0xffffffffu;
-                key = wave_sort_u32(key, lane);
-                bool ok = false;
-                if (lane < (int)cc) {
-                    A.slab_ent[ss * A.slab_cap + lane] = key;
-                    const int m = (int)key;
-                    if (A.amask)
-                        ok = slot_kept(A, p.k, p.d, m) &&
-                             peak_test_rec(A, p.k, p.d, m, false, 0.0f, true);
-                    else
-                        ok = slot_kept(A, p.k, p.d, m) &&
-                             peak_test(A, p.k, p.d, m, plane_at(A, p.k, p.d, m));
-                }
-                msk = __ballot(ok);
-                nsurv = __popcll(msk);
+        uint32_t word = 0;
+        int shift = 0;
+        if (s < send) {
+            const int k = slab_level(A, s);
+            word = A.above[A.cnt_off[k] + (s - A.slab_base[k]) * A.cnt_stride[k]];
+            shift = A.bit_shift[k];
+        }
+        if (!__ballot(word != 0)) continue;
+        // the chunks of the 64 slabs in order: inclusive prefix of their numbers over the lanes
+        int incl = __popc(word) << shift;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int v = __shfl_up(incl, o);
+            if (lane >= o) incl += v;
+        }
+        const int items = __builtin_amdgcn_readlane(incl, 63);
+        for (int i0 = 0; i0 < items; i0 += kPeakGroupWaves) {
+            const int it = i0 + wave;
+            uint32_t hit = 0;
+            int k = 0, d = 0, m0 = 0;
+            float y[kGroup];
+            int w[kGroup];
+            if (it < items) {
+                const int l = __ffsll((unsigned long long)__ballot(incl > it)) - 1;
+                uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)word, l);
+                k = slab_level(A, sb + l);
+                const int sh = A.bit_shift[k];
+                const int r = it - (__builtin_amdgcn_readlane(incl, l) - (__popc(bits) << sh));
+                for (int i = r >> sh; i > 0; --i) bits &= bits - 1;
+                const int c = ((__ffs((int)bits) - 1) << sh) + (r & ((1 << sh) - 1));
+                const uint32_t rs = (uint32_t)(sb + l - A.slab_base[k]);   // (rows x tiles fits 31 bits)
+                d = (int)(rs / (uint32_t)A.tiles_per_row[k]);
+                const int t = (int)(rs - (uint32_t)d * (uint32_t)A.tiles_per_row[k]);
+                if (c < A.cpt[k]) hit = chunk_test<REC>(A, k, d, t, c, lane, m0, y, w);
+            }
+            uint32_t n = 0;
+            int pos = 0;
+#pragma unroll
+            for (int q = 0; q < kGroup; ++q) {
+                const uint64_t b = __ballot((hit >> q) & 1u);
+                n += (uint32_t)__popcll(b);
+                if (SCATTER) pos += __popcll(b & lanes_below(lane));
+            }
+            if constexpr (!SCATTER) {
+                total += n;
             } else {
-                for (int mb = p.mlo; mb < p.mhi; mb += 64) {
-                    const int m = mb + lane;
-                    bool ok = false;
-                    if (m < p.mhi && slot_kept(A, p.k, p.d, m)) {
-                        if (A.amask) {
-                            if (slot_above(A, p.k, p.d, m)) {
-                                const float y = plane_at(A, p.k, p.d, m);
-                                ok = (y > A.threshold) && peak_test_rec(A, p.k, p.d, m, true, y);
-                            }
-                        } else {
-                            const float y = plane_at(A, p.k, p.d, m);
-                            ok = (y > A.threshold) && peak_test(A, p.k, p.d, m, y);
-                        }
+                if (lane == 0) cnt[turn][wave] = n;
+                __syncthreads();
+                int64_t at = run + pos;
+#pragma unroll
+                for (int i = 0; i < kPeakGroupWaves; ++i) {
+                    if (i < wave) at += cnt[turn][i];
+                    run += cnt[turn][i];
+                }
+                turn ^= 1;
+#pragma unroll
+                for (int q = 0; q < kGroup; ++q) {
+                    if (!((hit >> q) & 1u)) continue;
+                    if (at < A.cand_cap) {
+                        spd_candidate o;
+                        o.start = A.t0 + ((int64_t)(m0 + q) << A.level_shift[k]);
+                        o.dm = d;
+                        o.width = REC ? w[q] : A.W[A.level_off[k] + (int64_t)d * A.level_pitch[k] + m0 + q];
+                        o.level = k;
+                        o.snr = y[q];
+                        A.cand[at] = o;
                     }
-                    nsurv += __popcll(__ballot(ok));
+                    ++at;
                 }
             }
-            if (lane == 0) {
-                A.surv[ss] = nsurv;
-                A.mask[ss] = msk;
-            }
-            total += nsurv;
         }
     }
-    if (lane == 0) A.wave_tot[w] = total;
-}
-
-__global__ __launch_bounds__(256) void peak_count_kernel(const PeakArgs A) {
-    const int w = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (w >= A.n_waves) return;
-    peak_count_wave(A, w, threadIdx.x & 63);
-}
-
-// exclusive scan of a beam's per-wave totals by one 1024-thread work-group
-template <class PA>
-__device__ __forceinline__ void peak_scan_block(PA &A, int64_t *part) {
-    const int t = threadIdx.x;
-    const int per = (A.n_waves + 1023) / 1024;
-    // candidates already written before this list (read before the first barrier: the last
-    // thread may overwrite the same count at the end)
-    const int64_t base = A.base_count ? *A.base_count : 0;
-    int64_t loc = 0;
-    for (int i = 0; i < per; ++i) {
-        const int w = t * per + i;
-        if (w < A.n_waves) loc += A.wave_tot[w];
-    }
-    part[t] = loc;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        const int64_t v = (t >= off) ? part[t - off] : 0;
+    if constexpr (!SCATTER) {
+        if (lane == 0) cnt[0][wave] = total;
         __syncthreads();
-        part[t] += v;
-        __syncthreads();
-    }
-    int64_t run = base + part[t] - loc;               // exclusive prefix
-    for (int i = 0; i < per; ++i) {
-        const int w = t * per + i;
-        if (w < A.n_waves) {
-            A.wave_off[w] = run;
-            run += A.wave_tot[w];
-        }
-    }
-    if (t == 1023) *A.cand_count = base + part[1023];
-}
-
-__global__ __launch_bounds__(1024) void peak_scan_kernel(const PeakArgs A) {
-    __shared__ int64_t part[1024];
-    peak_scan_block(A, part);
-}
-
-template <class PA>
-__device__ __forceinline__ void put_cand(PA &A, int64_t idx, int k, int d, int m, float y, int w) {
-    if (idx >= A.cand_cap) return;
-    spd_candidate c;
-    c.start = A.t0 + ((int64_t)m << A.level_shift[k]);
-    c.dm = d;
-    c.width = w;
-    c.level = k;
-    c.snr = y;
-    A.cand[idx] = c;
-}
-
-// scatter pass of wave w of a beam
-template <class PA>
-__device__ __forceinline__ void peak_scatter_wave(PA &A, int w, int lane) {
-    const int64_t sbeg = (int64_t)w * A.slabs_per_wave;
-    const int64_t send = min(sbeg + A.slabs_per_wave, A.n_slabs);
-    int64_t off = A.wave_off[w];
-    for (int64_t sb = sbeg; sb < send; sb += 64) {
-        const int64_t s = sb + lane;
-        const uint32_t sv = (s < send) ? A.surv[s] : 0u;
-        uint64_t nz = __ballot(sv != 0);
-        while (nz) {
-            const int l = __ffsll((unsigned long long)nz) - 1;
-            nz &= nz - 1;
-            const int64_t ss = sb + l;
-            const uint32_t nsurv = (uint32_t)__shfl((int)sv, l);
-            const uint32_t cc = A.slab_cnt[slab_cnt_index(A, ss)];
-            const SlabPos p = slab_decode(A, ss);
-            if (cc <= (uint32_t)A.slab_cap) {
-                const uint64_t msk = A.mask[ss];
-                if (lane < (int)cc && ((msk >> lane) & 1ull)) {
-                    const int m = (int)A.slab_ent[ss * A.slab_cap + lane];
-                    int w;
-                    const float y = slot_value(A, p.k, p.d, m, &w);
-                    put_cand(A, off + __popcll(msk & lanes_below(lane)), p.k, p.d, m, y, w);
-                }
-            } else {
-                int64_t run = 0;
-                for (int mb = p.mlo; mb < p.mhi; mb += 64) {
-                    const int m = mb + lane;
-                    bool ok = false;
-                    float y = 0.0f;
-                    int w = 0;
-                    if (m < p.mhi && slot_kept(A, p.k, p.d, m)) {
-                        if (A.amask) {
-                            if (slot_above(A, p.k, p.d, m)) {
-                                y = slot_value(A, p.k, p.d, m, &w);
-                                ok = (y > A.threshold) && peak_test_rec(A, p.k, p.d, m, true, y);
-                            }
-                        } else {
-                            y = slot_value(A, p.k, p.d, m, &w);
-                            ok = (y > A.threshold) && peak_test(A, p.k, p.d, m, y);
-                        }
-                    }
-                    const uint64_t b = __ballot(ok);
-                    if (ok) put_cand(A, off + run + __popcll(b & lanes_below(lane)), p.k, p.d, m, y, w);
-                    run += __popcll(b);
-                }
-            }
-            off += nsurv;
+        if (threadIdx.x == 0) {
+            uint32_t sum = 0;
+#pragma unroll
+            for (int i = 0; i < kPeakGroupWaves; ++i) sum += cnt[0][i];
+            A.group_tot[g] = sum;
         }
     }
 }
 
-__global__ __launch_bounds__(256) void peak_scatter_kernel(const PeakArgs A) {
-    const int w = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (w >= A.n_waves) return;
-    peak_scatter_wave(A, w, threadIdx.x & 63);
+template <bool REC, bool SCATTER>
+__global__ __launch_bounds__(kPeakThreads) void peak_kernel(const PeakArgs A) {
+    peak_group<REC, SCATTER>(A, blockIdx.x);
 }
 
 // Batched: the peak-finder arguments of every beam in a table in the constant address space
-// (read with scalar loads), the waves of all beams in one index space: wave i belongs to beam b
-// with wave_base[b] <= i < wave_base[b + 1].  One launch per pass for the whole batch; the scan
-// takes one work-group per beam.
+// (read with scalar loads), the groups of all beams in one index space: group i belongs to beam b
+// with group_base[b] <= i < group_base[b + 1].  One launch per pass for the whole batch.
 typedef __attribute__((address_space(4))) const PeakArgs CPeakArgs;
 
-__device__ __forceinline__ int peak_beam_of(const PeakBatchArgs &B, int64_t wg) {
-    const ConstI64Ptr base = (ConstI64Ptr)B.wave_base;
-    int lo = 0, hi = B.n_beams - 1;                     // last b with base[b] <= wg
+template <bool REC, bool SCATTER>
+__global__ __launch_bounds__(kPeakThreads) void peak_batch_kernel(const PeakBatchArgs B) {
+    const ConstI64Ptr base = (ConstI64Ptr)B.group_base;
+    int lo = 0, hi = B.n_beams - 1;                     // last b with base[b] <= this group
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (base[mid] <= wg) lo = mid; else hi = mid - 1;
+        if (base[mid] <= (int64_t)blockIdx.x) lo = mid; else hi = mid - 1;
     }
-    return lo;
-}
-
-__global__ __launch_bounds__(256) void peak_count_batch_kernel(const PeakBatchArgs B) {
-    const int64_t wg = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (wg >= B.n_waves) return;
-    const int b = peak_beam_of(B, wg);
-    CPeakArgs &A = ((CPeakArgs *)B.tab)[b];
-    peak_count_wave(A, (int)(wg - ((ConstI64Ptr)B.wave_base)[b]), threadIdx.x & 63);
-}
-
-__global__ __launch_bounds__(1024) void peak_scan_batch_kernel(const PeakBatchArgs B) {
-    __shared__ int64_t part[1024];
-    CPeakArgs &A = ((CPeakArgs *)B.tab)[blockIdx.x];
-    peak_scan_block(A, part);
-}
-
-__global__ __launch_bounds__(256) void peak_scatter_batch_kernel(const PeakBatchArgs B) {
-    const int64_t wg = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (wg >= B.n_waves) return;
-    const int b = peak_beam_of(B, wg);
-    CPeakArgs &A = ((CPeakArgs *)B.tab)[b];
-    peak_scatter_wave(A, (int)(wg - ((ConstI64Ptr)B.wave_base)[b]), threadIdx.x & 63);
+    CPeakArgs &A = ((CPeakArgs *)B.tab)[lo];
+    peak_group<REC, SCATTER>(A, (int)((int64_t)blockIdx.x - base[lo]));
 }
 
 // ----------------------------------------------------------------------------------------
@@ -1623,30 +1568,35 @@ int launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, void *stream) {
     return (int)hipGetLastError();
 }
 
+template <bool SCATTER>
+static int launch_peak_pass(const PeakArgs &a, hipStream_t st) {
+    const dim3 grid((unsigned)a.n_groups);
+    if (a.dir)
+        hipLaunchKernelGGL((peak_kernel<true, SCATTER>), grid, dim3(kPeakThreads), 0, st, a);
+    else
+        hipLaunchKernelGGL((peak_kernel<false, SCATTER>), grid, dim3(kPeakThreads), 0, st, a);
+    return (int)hipGetLastError();
+}
+
 int launch_peaks(const PeakArgs &a, void *stream) {
-    const dim3 grid((unsigned)((a.n_waves + 3) / 4));
-    hipLaunchKernelGGL(peak_count_kernel, grid, dim3(256), 0, (hipStream_t)stream, a);
-    int err = (int)hipGetLastError();
-    if (err) return err;
-    hipLaunchKernelGGL(peak_scan_kernel, dim3(1), dim3(1024), 0, (hipStream_t)stream, a);
-    err = (int)hipGetLastError();
-    if (err) return err;
-    hipLaunchKernelGGL(peak_scatter_kernel, grid, dim3(256), 0, (hipStream_t)stream, a);
+    const int err = launch_peak_pass<false>(a, (hipStream_t)stream);
+    return err ? err : launch_peak_pass<true>(a, (hipStream_t)stream);
+}
+
+template <bool SCATTER>
+static int launch_peak_batch_pass(const PeakBatchArgs &a, hipStream_t st) {
+    const dim3 grid((unsigned)a.n_groups);
+    if (a.records)
+        hipLaunchKernelGGL((peak_batch_kernel<true, SCATTER>), grid, dim3(kPeakThreads), 0, st, a);
+    else
+        hipLaunchKernelGGL((peak_batch_kernel<false, SCATTER>), grid, dim3(kPeakThreads), 0, st, a);
     return (int)hipGetLastError();
 }
 
 int launch_peaks_batch(const PeakBatchArgs &a, void *stream) {
-    if (a.n_waves <= 0) return 0;
-    const dim3 grid((unsigned)((a.n_waves + 3) / 4));
-    hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(peak_count_batch_kernel, grid, dim3(256), 0, st, a);
-    int err = (int)hipGetLastError();
-    if (err) return err;
-    hipLaunchKernelGGL(peak_scan_batch_kernel, dim3((unsigned)a.n_beams), dim3(1024), 0, st, a);
-    err = (int)hipGetLastError();
-    if (err) return err;
-    hipLaunchKernelGGL(peak_scatter_batch_kernel, grid, dim3(256), 0, st, a);
-    return (int)hipGetLastError();
+    if (a.n_groups <= 0) return 0;
+    const int err = launch_peak_batch_pass<false>(a, (hipStream_t)stream);
+    return err ? err : launch_peak_batch_pass<true>(a, (hipStream_t)stream);
 }
 
 const char *hip_error_text(int err) { return hipGetErrorString((hipError_t)err); }

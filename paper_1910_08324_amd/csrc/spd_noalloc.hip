@@ -1,15 +1,14 @@
 // spd_search_noalloc: spd_search with its workspace in a fixed device array of the library,
 // for callers that cannot allocate device memory.
 //
-// The workspace of spd_search (hand-off series of the cascade steps, pre-candidate slabs,
-// peak-finder counters and offsets, and the planes when only candidates are requested) lives
+// The workspace of spd_search (hand-off series of the cascade steps, chunk bits and
+// records, peak-finder totals, and the planes when only candidates are requested) lives
 // here in `scratch`, one copy per GPU, held until the process ends.  Host code never passes the
 // array's name to a kernel: in host code that name is only a stand-in for the symbol.  The
 // first call on a device, with that device current, resolves the device address of its copy
 // with hipGetSymbolAddress and keeps it; every later call on that device uses the kept address.
 //
-// Nothing in the workspace needs clearing between calls: every slab count, survivor count,
-// mask and per-wave total is written by the launch that produces it before any kernel reads it.
+// Nothing in the workspace needs clearing between calls: every chunk bit, record and total is written by the launch that produces it before any kernel reads it.
 // Calls on one GPU share the array, so calls that overlap in time on one GPU (several streams or
 // threads) race on it; such callers serialise their calls.
 #include <hip/hip_runtime.h>
