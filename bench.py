@@ -90,8 +90,8 @@ def launch_kernel_name(method: str, info, i: int, planes: bool = True) -> str:
         if info.launch_first_level[i] < 0:
             return "spd::scales_kernel"
         multi = "true" if int(info.segment) > 256 else "false"      # items per wave > 1
-        group = 16 if int(info.max_width) <= 4096 else 64          # widths per max-only group
-        return f"spd::exh_kernel<true, {multi}, {group}>"
+        prune = "true" if int(info.max_width) > 512 else "false"   # groups of widths bounded first
+        return f"spd::exh_kernel<true, {multi}, {prune}>"
     first = "true" if info.launch_first_level[i] == 0 else "false"
     return (f"spd::step_kernel<{first}, {FAMILY.get(method, 0)}, false, {int(info.launch_threads[i])}, "
             f"{'true' if planes else 'false'}>")

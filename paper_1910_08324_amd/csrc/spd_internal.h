@@ -17,8 +17,8 @@ constexpr int kSmallTileMax = 3072;    // longest tile (units) run on kSmallStep
 constexpr int kGroup = 4;             // consecutive slots evaluated together by one thread
 constexpr int kExhSlots = 256;        // output slots per exhaustive work item (64 lanes x 4)
 constexpr int kExhBlock = 512;        // widths per LDS window refill in the exhaustive kernel
-constexpr int kExhGroup = 64;         // most widths per max-only group (argmax recovered afterwards)
-constexpr int kExhSmallGroupMax = 4096;  // largest L_end searched in groups of 16 widths
+constexpr int kExhGroup = 64;         // widths bounded together (evaluated in groups of a quarter)
+constexpr int kExhBoundFrom = 256;    // widths up to here are always evaluated
 constexpr int kChunk = 256;           // slots the peak finder tests together (64 lanes x kGroup)
 constexpr int kExhItemsPerWave = 4;   // work items per wave when every width fits one block
 constexpr int kPeakGroups = 16384;    // most work-groups of a peak-finder pass

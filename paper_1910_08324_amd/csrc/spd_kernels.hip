@@ -737,15 +737,32 @@ __global__ __launch_bounds__(kStepThreads, (StepShape<FAM, W>::WAVES)) void step
 //
 // Work item = (row d, 256 output slots starting at s0).  Lane l owns the 4 consecutive starts
 // s0 + 4l + v.  Widths are visited in increasing order with one running sum per start, in
-// groups of 16 or 64 widths: inside a group only the maximum is tracked (add, multiply, max per
-// start and width); after the group the best group, and the running sum entering it, are
-// kept.  The winning width inside the winning group is recovered at the end by replaying that
-// group's steps with the same FP32 operations, so it is the smallest width attaining the
-// maximum, exactly as a per-width argmax would give.
+// groups of 16: inside a group only the maximum is tracked (add, multiply, max per start and
+// width); after the group the best group, and the running sum entering it, are kept.  The
+// winning width inside the winning group is recovered at the end by replaying that group's steps
+// with the same FP32 operations, so it is the smallest width attaining the maximum, exactly as a
+// per-width argmax would give.
 // The input window z[s0 .. s0 + 256 + L_end) streams through a 1024-float LDS ring, 512 new
-// samples per block of 512 widths.  The ring's first 16 float4 are mirrored after its end, so a
-// group reads its 17 consecutive float4 at immediate offsets from one base address.
-// ----------------------------------------------------------------------------------------
+// samples per block of 512 widths.  The ring's first 18 float4 are mirrored after its end, so a
+// group reads its consecutive float4 at immediate offsets from one base address.
+//
+// Long width sets (PRUNE) are bound by the vector issue rate: 2.5 instructions per (start, width)
+// and the groups' bookkeeping.  Most groups of 64 widths at large L raise no start's best, and an
+// upper bound that shows it needs little more than the running sums themselves (exh_bound): 1.3
+// instructions per pair, and the group is then skipped.  Only where the bound does not rule a new best out
+// for every start of the wave is the group evaluated; a group that did raise one is followed by
+// plain evaluation, since such groups come in runs.  On white noise about one group in six is
+// evaluated up to L_end 8192, half of those below 1024, so bounds start at width 257.  Measured:
+// 128 x 131072 at L_end 8192 7.63 -> 5.78 ms (2.0 instead of 2.9 vector instructions per pair, 85% of
+// the issue rate); 64 x 65536 at L_end 256, where the replay's fetches one after another cost as
+// much as the widths, 137 -> 111 us.
+// four consecutive floats at any address (global loads need no more than 4-byte alignment)
+__device__ __forceinline__ float4 load_f4(const float *p) {
+    typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));
+    const v4u v = *reinterpret_cast<const v4u *>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+
 __device__ __forceinline__ float load_z(const float *xr, int r, int n_in, float mu, float inv) {
     return r < n_in ? (xr[r] - mu) * inv : 0.0f;
 }
@@ -755,7 +772,7 @@ __device__ __forceinline__ float load_z(const float *xr, int r, int n_in, float 
 typedef __attribute__((address_space(4))) const float *ConstFloatPtr;
 
 constexpr int kRing4 = 256;        // float4 slots of the ring (1024 samples)
-constexpr int kGuard4 = 16;        // mirrored slots after the ring's end
+constexpr int kGuard4 = 18;        // mirrored slots after the ring's end
 
 __device__ __forceinline__ void ring_put(float4 *ring4, int i, float4 v) {   // 0 <= i < kRing4
     ring4[i] = v;
@@ -797,11 +814,51 @@ __device__ __forceinline__ void exh_group(const float4 *ring4, int jb4, int L0, 
     }
 }
 
-// G: widths per max-only group.  L_end up to 4096 takes groups of 16 (a shorter argmax replay
-// per start, which there costs as much as the width loop: 2x faster at L_end 256, 1.8x at 1024);
-// larger L_end groups of 64 (less bookkeeping per width).
-template <bool DENSE, bool MULTI, int G>
-__global__ __launch_bounds__(64) void exh_kernel(const ExhArgs A) {
+// Upper bound of each start's SNR over the kExhGroup widths from L0, and the running sums past
+// them.  Only start 0's sums are followed by a running maximum, over three widths more than the
+// group's; the group's sums of start v are, but for rounding, start 0's v widths later, shifted by a
+// constant:  X_v(L) = X_0(L + v) + (Xs_v - Xs_0) - (the first v samples start 0 adds).
+// Both sides are chains of at most kExhGroup + 3 additions of samples no larger than zmax, so
+// every partial sum is at most A = |Xs_0| + |Xs_v| + 70 zmax and their roundings together stay
+// below 145 2^-24 A < 1e-5 A.  The scale falls with the width, so r_first bounds a sum above zero
+// and r_last one below.  (A sum or sample that is not finite makes the bound fail its comparison.)
+__device__ __forceinline__ void exh_bound(const float4 *ring4, int jb4, float zmax, float r_first,
+                                          float r_last, float X[4], float ub[4]) {
+    typedef float v4f __attribute__((ext_vector_type(4)));
+    const v4f *win = reinterpret_cast<const v4f *>(ring4 + (jb4 & (kRing4 - 1)));
+    v4f wa = win[0];
+    const float d[4] = {0.0f, wa.x, wa.x + wa.y, (wa.x + wa.y) + wa.z};
+    float xs[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) xs[v] = X[v];
+    float m = SPD_NEG_INF;
+#pragma unroll 4
+    for (int t = 0; t < kExhGroup / 4; ++t) {
+        const v4f wb = win[t + 1];
+        const float w[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) X[v] += w[v + tt];
+            m = fmaxf(m, X[0]);
+        }
+        wa = wb;
+    }
+    const float x1 = X[0] + wa.x, x2 = x1 + wa.y, x3 = x2 + wa.z;
+    m = fmaxf(m, fmaxf(x1, fmaxf(x2, x3)));
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const float A = fabsf(xs[0]) + fabsf(xs[v]) + 70.0f * zmax;
+        const float top = (m + (xs[v] - xs[0])) - d[v] + 1e-5f * A;
+        ub[v] = fmaxf(top * r_first, top * r_last);
+        if (!(fabsf(top) < __builtin_huge_valf())) ub[v] = __builtin_huge_valf();
+    }
+}
+
+template <bool DENSE, bool MULTI, bool PRUNE>
+__global__ __launch_bounds__(64, 6) void exh_kernel(const ExhArgs A) {
+    static_assert(!PRUNE || (DENSE && !MULTI), "bounds are for long dense width sets");
+    constexpr int G = kExhGroup / 4;
     __shared__ float4 ring4[kRing4 + kGuard4];
 
     // A wave takes `per` consecutive work items of a row (MULTI: several, when every width fits
@@ -831,10 +888,11 @@ __global__ __launch_bounds__(64) void exh_kernel(const ExhArgs A) {
     const int Lw = A.l_end;
     const int n_in = A.n_in;
 
-    auto load4 = [&](int r) -> float4 {          // z[r .. r + 3], r a multiple of 4
+    float zmax = 0.0f;                           // PRUNE: largest |z| this lane has loaded
+    auto load4 = [&](int r) -> float4 {          // z[r .. r + 3]
         float4 v;
-        if (A.vec_ok && r + 3 < n_in) {
-            v = *reinterpret_cast<const float4 *>(xr + r);
+        if (r + 3 < n_in) {
+            v = load_f4(xr + r);
             v.x = (v.x - mu) * inv;
             v.y = (v.y - mu) * inv;
             v.z = (v.z - mu) * inv;
@@ -847,11 +905,17 @@ __global__ __launch_bounds__(64) void exh_kernel(const ExhArgs A) {
         }
         return v;
     };
+    auto note = [&](const float4 &v) {
+        // (a maximum ignores NaN; a NaN sample shows in the running sums instead)
+        if (PRUNE) zmax = fmaxf(zmax, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+    };
 
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int j = q * 256 + lane * 4;
-        ring_put(ring4, j >> 2, load4(base + j));
+        const float4 v = load4(base + j);
+        note(v);
+        ring_put(ring4, j >> 2, v);
     }
     int loaded_to = base + 1024;
     __syncthreads();
@@ -872,6 +936,9 @@ __global__ __launch_bounds__(64) void exh_kernel(const ExhArgs A) {
     int room[4];                                    // widest valid width per start
 #pragma unroll
     for (int v = 0; v < 4; ++v) room[v] = n_in - (s0 + 4 * lane + v);
+    // (a sigma table's scales need not fall with the width)
+    const bool may_bound = PRUNE && A.scale_ld == 0;
+    bool bounds = may_bound;                        // the last group raised no start's best
 
     for (int b = 0; b < nblk; ++b) {
         const bool refill = (b + 1 < nblk);
@@ -881,34 +948,58 @@ __global__ __launch_bounds__(64) void exh_kernel(const ExhArgs A) {
             pf0 = load4(s0 + jn + lane * 4);
             pf1 = load4(s0 + jn + 256 + lane * 4);
         }
-        for (int gi = 0; gi < kExhBlock / G; ++gi) {
-            const int L0 = b * kExhBlock + gi * G + 1;
+        float zm = 0.0f;                            // largest |z| of the ring, over the wave
+        if (PRUNE) {
+            zm = zmax;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) zm = fmaxf(zm, __shfl_xor(zm, o));
+        }
+        for (int gi = 0; gi < kExhBlock / kExhGroup; ++gi) {
+            const int L0 = b * kExhBlock + gi * kExhGroup + 1;
             if (L0 > Lw) break;
-            // wave-uniform: every width of the group fits at every start of the work item
-            const bool fast = (L0 + G - 1 <= Lw) &&
-                              ((int64_t)s0 + kExhSlots - 1 + L0 + G - 1 <= n_in);
-            float Xs[4], gm[4];
+            if (PRUNE && bounds && L0 > kExhBoundFrom && L0 + kExhGroup - 1 <= Lw &&
+                (int64_t)s0 + kExhSlots - 1 + L0 + kExhGroup - 1 <= n_in) {
+                float xs[4], ub[4];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                Xs[v] = X[v];
-                gm[v] = SPD_NEG_INF;
+                for (int v = 0; v < 4; ++v) xs[v] = X[v];
+                exh_bound(ring4, ro4 + lane + ((L0 - 1) >> 2), zm, ((ConstFloatPtr)srow)[L0 - 1],
+                          ((ConstFloatPtr)srow)[L0 + kExhGroup - 2], X, ub);
+                const bool may = !(ub[0] <= best[0] && ub[1] <= best[1] && ub[2] <= best[2] && ub[3] <= best[3]);
+                if (!__ballot(may)) continue;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) X[v] = xs[v];
             }
-            const int jb4 = ro4 + lane + ((L0 - 1) >> 2);
-            if (fast)
-                exh_group<false, DENSE, G>(ring4, jb4, L0, (ConstFloatPtr)srow, A.evalmask, Lw, room, X, gm);
-            else
-                exh_group<true, DENSE, G>(ring4, jb4, L0, (ConstFloatPtr)srow, A.evalmask, Lw, room, X, gm);
+            bool raised = false;
+            for (int L1 = L0; L1 < L0 + kExhGroup && L1 <= Lw; L1 += G) {
+                // wave-uniform: every width of the group fits at every start of the work item
+                const bool fast = (L1 + G - 1 <= Lw) && ((int64_t)s0 + kExhSlots - 1 + L1 + G - 1 <= n_in);
+                float Xs[4], gm[4];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                if (gm[v] > best[v]) {
-                    best[v] = gm[v];
-                    bg[v] = (L0 - 1) / G;
-                    bx[v] = Xs[v];
+                for (int v = 0; v < 4; ++v) {
+                    Xs[v] = X[v];
+                    gm[v] = SPD_NEG_INF;
+                }
+                const int jb4 = ro4 + lane + ((L1 - 1) >> 2);
+                if (fast)
+                    exh_group<false, DENSE, G>(ring4, jb4, L1, (ConstFloatPtr)srow, A.evalmask, Lw, room, X, gm);
+                else
+                    exh_group<true, DENSE, G>(ring4, jb4, L1, (ConstFloatPtr)srow, A.evalmask, Lw, room, X, gm);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if (gm[v] > best[v]) {
+                        best[v] = gm[v];
+                        bg[v] = (L1 - 1) / G;
+                        bx[v] = Xs[v];
+                        raised = true;
+                    }
                 }
             }
+            if (PRUNE) bounds = may_bound && !__ballot(raised);
         }
         if (refill) {
             __syncthreads();
+            note(pf0);
+            note(pf1);
             ring_put(ring4, ((jn >> 2) + lane) & (kRing4 - 1), pf0);
             ring_put(ring4, ((jn >> 2) + 64 + lane) & (kRing4 - 1), pf1);
             __syncthreads();
@@ -917,28 +1008,59 @@ __global__ __launch_bounds__(64) void exh_kernel(const ExhArgs A) {
 
     // ---- recover the smallest width attaining the maximum inside the winning group.  With a
     // single block of widths the ring still holds the whole window (it was never refilled), so
-    // the replay reads the same values from LDS; otherwise it reloads them.
+    // the replay reads the same values from LDS; otherwise it loads them again.  The group's
+    // samples and scales are fetched together: one at a time, their latency would cost a short
+    // width set as much as its whole width loop.
     int bw[4] = {0, 0, 0, 0};
     const float *ring = reinterpret_cast<const float *>(ring4);
+#pragma unroll 1
+    for (int v = 0; v < 4; ++v) {                  // one start at a time: few registers
+        const int Lb = bg[0] * G + 1;
+        float z[G], r[G];
+        if (nblk == 1) {
+            const float *p = ring + (((ro4 + lane + (Lb - 1) / 4) & (kRing4 - 1)) * 4 + v);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        if (best[v] == SPD_NEG_INF) continue;
-        const int sv = s0 + 4 * lane + v;
-        const int Lb = bg[v] * G + 1;
-        float Xr = bx[v], bm = SPD_NEG_INF;
-        for (int t = 0; t < G; ++t) {
-            const int L = Lb + t;
-            if (L > Lw) break;
-            Xr += (nblk == 1) ? ring[(4 * ro4 + 4 * lane + v + L - 1) & (4 * kRing4 - 1)]
-                              : load_z(xr, sv + L - 1, n_in, mu, inv);
-            float snr = Xr * srow[L - 1];
-            bool ok = L <= room[v];
-            if (!DENSE) ok = ok && ((A.evalmask[(L - 1) >> 5] >> ((L - 1) & 31)) & 1u);
-            if (ok && snr > bm) {
-                bm = snr;
-                bw[v] = L;
+            for (int t = 0; t < G; ++t) z[t] = p[t];
+        } else {
+#pragma unroll
+            for (int i = 0; i < G / 4; ++i) {
+                const float4 f = load4(s0 + 4 * lane + v + Lb - 1 + 4 * i);
+                z[4 * i + 0] = f.x;
+                z[4 * i + 1] = f.y;
+                z[4 * i + 2] = f.z;
+                z[4 * i + 3] = f.w;
             }
         }
+#pragma unroll
+        for (int i = 0; i < G / 4; ++i) {
+            const float4 f = load_f4(srow + Lb - 1 + 4 * i);   // (the tables hold kExhGroup more)
+            r[4 * i + 0] = f.x;
+            r[4 * i + 1] = f.y;
+            r[4 * i + 2] = f.z;
+            r[4 * i + 3] = f.w;
+        }
+        const uint32_t on = DENSE ? 0xffffu : A.evalmask[(Lb - 1) >> 5] >> ((Lb - 1) & 31);
+        const int fit = min(Lw, room[0] - v);
+        float Xr = bx[0], bm = SPD_NEG_INF;
+        int w = 0;
+#pragma unroll
+        for (int t = 0; t < G; ++t) {
+            Xr += z[t];
+            const float snr = Xr * r[t];
+            const bool ok = Lb + t <= fit && (DENSE || ((on >> t) & 1u));
+            if (ok && snr > bm) {
+                bm = snr;
+                w = Lb + t;
+            }
+        }
+        // the next start's group and sum to the front, this one's width to the back
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            bg[q] = bg[q + 1];
+            bx[q] = bx[q + 1];
+            bw[q] = bw[q + 1];
+        }
+        bw[3] = w;
     }
 
     // ---- outputs
@@ -1532,24 +1654,21 @@ int launch_exhaustive(const ExhArgs &a, bool dense, void *stream) {
     const int64_t per_row = (a.n_seg + a.segs_per_wave - 1) / a.segs_per_wave;
     const dim3 grid((unsigned)((int64_t)a.n_dm * per_row));
     const bool multi = a.segs_per_wave > 1;
-    // groups of 16 widths up to L_end 4096, of 64 above (measured crossover on gfx950)
-    const bool small = a.l_end <= kExhSmallGroupMax;
+    // bounds pay once a width set goes past one ring window (shorter ones raise a best in most groups)
+    const bool prune = dense && a.l_end > kExhBlock;
     hipStream_t st = (hipStream_t)stream;
     if (multi) {
         if (dense)
-            hipLaunchKernelGGL((exh_kernel<true, true, 16>), grid, dim3(64), 0, st, a);
+            hipLaunchKernelGGL((exh_kernel<true, true, false>), grid, dim3(64), 0, st, a);
         else
-            hipLaunchKernelGGL((exh_kernel<false, true, 16>), grid, dim3(64), 0, st, a);
-    } else if (small) {
-        if (dense)
-            hipLaunchKernelGGL((exh_kernel<true, false, 16>), grid, dim3(64), 0, st, a);
-        else
-            hipLaunchKernelGGL((exh_kernel<false, false, 16>), grid, dim3(64), 0, st, a);
+            hipLaunchKernelGGL((exh_kernel<false, true, false>), grid, dim3(64), 0, st, a);
+    } else if (prune) {
+        hipLaunchKernelGGL((exh_kernel<true, false, true>), grid, dim3(64), 0, st, a);
     } else {
         if (dense)
-            hipLaunchKernelGGL((exh_kernel<true, false, 64>), grid, dim3(64), 0, st, a);
+            hipLaunchKernelGGL((exh_kernel<true, false, false>), grid, dim3(64), 0, st, a);
         else
-            hipLaunchKernelGGL((exh_kernel<false, false, 64>), grid, dim3(64), 0, st, a);
+            hipLaunchKernelGGL((exh_kernel<false, false, false>), grid, dim3(64), 0, st, a);
     }
     return (int)hipGetLastError();
 }
