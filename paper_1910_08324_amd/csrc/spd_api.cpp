@@ -209,6 +209,7 @@ struct Layout {
     int cpt[kMaxLevels] = {0};        // chunks per tile
     int bit_shift[kMaxLevels] = {0};  // chunks per bit of a tile's word, as a power of two
     int64_t off_scale = 0, off_mask = 0, off_above = 0, off_tot = 0, off_base = 0;
+    int64_t off_edge = -1;    // with look-ahead samples (see StepArgs::edge)
     int64_t off_Y = -1, off_W = -1;
     int64_t cnt_off[kMaxLevels] = {0};
     int cnt_stride[kMaxLevels] = {0};
@@ -507,6 +508,7 @@ int make_layout(const spd_params *p, const Search &s, int32_t n_dm, int32_t n_in
     L->off_above = take(L->n_slabs * 4);
     L->off_tot = take((int64_t)L->n_groups * 4);
     L->off_base = take(8);
+    if (n_out < n_in) L->off_edge = take((int64_t)nlev * n_dm);
     if (!(p->flags & SPD_WRITE_PLANES)) {
         if (lossy) {
             // candidates only: no planes anywhere; the cascade leaves a record of every chunk with
@@ -705,6 +707,7 @@ int run_filter(const spd_params *params, const Prepared &P, const float *x, int6
             a.Y = P.Y;
             a.W = P.W;
             a.above = above;
+            a.edge = L.off_edge >= 0 ? reinterpret_cast<uint8_t *>(P.ws + L.off_edge) : nullptr;
             a.ld_in = ld_in;
             a.ld_cin = ld_in;
             a.ld_out = st.ld_out;
@@ -767,6 +770,7 @@ int run_filter(const spd_params *params, const Prepared &P, const float *x, int6
     a.scale_ld = L.scale_ld;
     a.evalmask = evalmask;
     a.above = above;
+    a.edge = L.off_edge >= 0 ? reinterpret_cast<uint8_t *>(P.ws + L.off_edge) : nullptr;
     a.pitch = I.plane_pitch[0];
     a.n_dm = n_dm;
     a.n_in = n_in;
@@ -799,6 +803,7 @@ spd::PeakArgs peak_args(const spd_params *params, const Prepared &P, int32_t n_d
     a.W = P.W;
     a.above = reinterpret_cast<const uint32_t *>(P.ws + L.off_above);
     a.group_tot = reinterpret_cast<uint32_t *>(P.ws + L.off_tot);
+    a.edge = L.off_edge >= 0 ? reinterpret_cast<const uint8_t *>(P.ws + L.off_edge) : nullptr;
     a.base_copy = reinterpret_cast<int64_t *>(P.ws + L.off_base);
     a.cand = cand;
     a.cand_cap = cand_cap;
@@ -819,6 +824,8 @@ spd::PeakArgs peak_args(const spd_params *params, const Prepared &P, int32_t n_d
         a.tile_slots[i] = L.tile_slots[i];
         a.cpt[i] = L.cpt[i];
         a.bit_shift[i] = L.bit_shift[i];
+        a.edge_on[i] = L.off_edge >= 0 &&
+                       I.plane_slots[i] % (L.steps.empty() ? spd::kExhSlots : spd::kGroup) != 0;
     }
     for (int i = 0; i <= I.n_levels; ++i) a.slab_base[i] = L.slab_base[i];
     for (int i = 0; i < I.n_levels; ++i) {
@@ -953,6 +960,7 @@ spd::BeamView beam_view(const spd_params *params, const BatchPlan &B, const spd_
         v.cnt_off[j] = st.lv[j].cnt_off;
     }
     v.above = reinterpret_cast<uint32_t *>(ws + L.off_above);
+    v.edge = L.off_edge >= 0 ? reinterpret_cast<uint8_t *>(ws + L.off_edge) : nullptr;
     v.n_dm = bm.n_dm;
     v.n_in = bm.n_in;
     v.in_len = (int32_t)st.in_len;

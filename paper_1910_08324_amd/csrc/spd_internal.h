@@ -21,6 +21,8 @@ constexpr int kExhGroup = 64;         // widths bounded together (evaluated in g
 constexpr int kExhBoundFrom = 256;    // widths up to here are always evaluated
 constexpr int kChunk = 256;           // slots the peak finder tests together (64 lanes x kGroup)
 constexpr int kExhItemsPerWave = 4;   // work items per wave when every width fits one block
+constexpr int kEdgeMaxima = 64;       // see StepArgs::edge
+constexpr int kExhEdgeMaxima = 16;
 constexpr int kPeakGroups = 16384;    // most work-groups of a peak-finder pass
 constexpr int kPeakGroupSlabs = 16;   // fewest (level, row, tile) slabs of one of them ...
 constexpr int kPeakGroupsWanted = 4096;   // ... which grow to 64 (a wave's reach) beyond this many groups
@@ -87,6 +89,12 @@ struct StepArgs {
     float *Y;                 // planes (caller's or workspace)
     uint16_t *W;
     uint32_t *above;          // chunk bits of every (level, row, tile)
+    // With look-ahead samples (n_out < n_in, else null) the search evaluates the slots after a
+    // plane's last one that share its group of kGroup slots (its 256, exhaustive search).  The last
+    // slot of a row is a candidate only if it is not below the one after it, except where its tile
+    // has more than kEdgeMaxima (kExhEdgeMaxima) local maxima above the threshold at that level:
+    // edge[level n_dm + d] = 1 bars it.  Those are the lists that the search has always given.
+    uint8_t *edge;
     int64_t ld_in, ld_cin, ld_out;
     int32_t n_dm;
     int32_t n_in;             // raw samples per row (valid-only boundary)
@@ -131,6 +139,7 @@ struct BeamView {
     float *Y;
     uint16_t *W;
     uint32_t *above;
+    uint8_t *edge;
     int64_t ld_in, ld_cin, ld_out;
     int32_t n_dm, n_in, in_len, n_tiles, vec_ok;
     uint32_t pool_units;
@@ -165,6 +174,7 @@ struct ExhArgs {
     int64_t scale_ld;         // 0: one table for every row; else row d's table at d * scale_ld
     const uint32_t *evalmask; // bit (L-1) set if width L is evaluated (list mode only)
     uint32_t *above;          // per work item (one chunk): 1 if a slot is above the threshold
+    uint8_t *edge;            // as StepArgs::edge
     int64_t pitch;
     int32_t n_dm, n_in, n_out, l_end;
     int32_t n_seg;
@@ -219,6 +229,8 @@ struct PeakArgs {
     int32_t tile_slots[kMaxLevels];
     int32_t cpt[kMaxLevels];
     int32_t bit_shift[kMaxLevels];
+    const uint8_t *edge;      // as StepArgs::edge; read at the levels where it was written:
+    int8_t edge_on[kMaxLevels];
     int64_t slab_base[kMaxLevels + 1];
     int64_t level_pitch[kMaxLevels];
     int64_t level_off[kMaxLevels];

@@ -276,6 +276,8 @@ struct ArgGeom {
     __device__ float *Y() const { return A.Y; }
     __device__ uint16_t *W() const { return A.W; }
     __device__ uint32_t *above() const { return A.above; }
+    __device__ uint8_t *edge() const { return A.edge; }
+    __device__ int n_dm() const { return A.n_dm; }
     __device__ int64_t ld_in() const { return A.ld_in; }
     __device__ int64_t ld_cin() const { return A.ld_cin; }
     __device__ int64_t ld_out() const { return A.ld_out; }
@@ -311,6 +313,8 @@ struct TabGeom {
     __device__ float *Y() const { return V->Y; }
     __device__ uint16_t *W() const { return V->W; }
     __device__ uint32_t *above() const { return V->above; }
+    __device__ uint8_t *edge() const { return V->edge; }
+    __device__ int n_dm() const { return V->n_dm; }
     __device__ int64_t ld_in() const { return V->ld_in; }
     __device__ int64_t ld_cin() const { return V->ld_cin; }
     __device__ int64_t ld_out() const { return V->ld_out; }
@@ -441,8 +445,13 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
     constexpr int kCarry = (FAM >= 4 && FAM <= 6) ? 1 : (FAM == 0 ? -1 : 0);
     const bool carry = kCarry < 0 ? (A.carry != 0) : (kCarry == 1);
     const int64_t u0 = (int64_t)tile * T;
-    if (tid < kStepMaxLevels) st_cnt[tid] = 0;
+    if (tid < 3 * kStepMaxLevels) st_cnt[tid] = 0;
     if (d == 0 && tile == 0 && V.rec()) write_rec<NTH>(A, V, V.rec());
+    if (FIRST && carry && A.J > 1 && V.edge() && tid < kGroup) {
+        // level 1's slots after the plane's last one may have no carried prefix: taken as zero
+        const int i = V.slots(1) - tile * (T >> 1) + tid;
+        if (i >= 0 && i < (T >> 1)) lds[A.lv[0].lds_c + i] = 0.0f;
+    }
 
     // ---- 1. window of the input series (normalised in the first step) and carried prefixes
     {
@@ -534,6 +543,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
         const bool to_glb = carry && (j + 1 == A.J) && A.has_out;
         float *cg = to_glb ? V.cout() + (int64_t)d * V.ld_out() + (int64_t)tile * (T >> A.J) : nullptr;
         const bool sync_batches = form_next || to_lds;   // a batch writes into the live buffers
+        const bool edge = V.edge() && (V.slots(j) % kGroup) && tile == (V.slots(j) - 1) / Sj;
         const int k = L.k;
         const int umax = L.umax;
         const int base = L.base;
@@ -659,6 +669,24 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
                                          lane, V.slots(j) - ma, A.threshold, rb, ru, k, base);
                     }
                     if (set && lane == 0) atomicOr(&st_cnt[j], 1u << (chunk >> L.bit_shift));
+                    if (any && edge) {
+                        // the row's last slot against the evaluated slot after it (see StepArgs::edge)
+                        float left = __shfl_up(best[kGroup - 1], 1);
+                        float right = __shfl_down(best[0], 1);
+                        if (lane == 0) left = SPD_NEG_INF;
+                        if (lane == 63) right = SPD_NEG_INF;
+                        uint32_t maxima = 0;
+#pragma unroll
+                        for (int q = 0; q < kGroup; ++q) {
+                            const float l = q > 0 ? best[q - 1] : left;
+                            const float rr = q + 1 < kGroup ? best[q + 1] : right;
+                            const bool in = act && ma + q < V.slots(j);
+                            maxima += (uint32_t)__popcll(__ballot(in && best[q] > A.threshold && best[q] > l && best[q] >= rr));
+                            if (q + 1 < kGroup && in && ma + q + 1 == V.slots(j) && !(best[q] >= rr))
+                                st_cnt[2 * kStepMaxLevels + j] = 1;
+                        }
+                        if (lane == 0) atomicAdd(&st_cnt[kStepMaxLevels + j], maxima);
+                    }
                 }
             }
             if (sync_batches) {
@@ -696,6 +724,9 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
         // the tile's chunk bits of all its levels side by side (one short write per work-group)
         if (tid < A.J)
             V.above()[V.cnt_off(tid) + ((int64_t)d * V.n_tiles() + tile) * A.J] = st_cnt[tid];
+        if (tid < A.J && V.edge() && (V.slots(tid) % kGroup) && tile == (V.slots(tid) - 1) / (T >> tid))
+            V.edge()[(int64_t)A.lv[tid].k * V.n_dm() + d] =
+                st_cnt[2 * kStepMaxLevels + tid] && st_cnt[kStepMaxLevels + tid] <= (uint32_t)kEdgeMaxima;
     }
 }
 
@@ -704,7 +735,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
 template <bool FIRST, int FAM, bool RHO, int NTH, bool W>
 __global__ __launch_bounds__(NTH, (StepShape<FAM, W>::WAVES)) void step_kernel(const StepArgs A) {
     extern __shared__ float lds[];
-    __shared__ uint32_t st_cnt[kStepMaxLevels];
+    __shared__ uint32_t st_cnt[3 * kStepMaxLevels];
     const int d = blockIdx.x / A.n_tiles;
     const int tile = blockIdx.x - d * A.n_tiles;
     if (d >= A.n_dm) return;
@@ -717,7 +748,7 @@ __global__ __launch_bounds__(NTH, (StepShape<FAM, W>::WAVES)) void step_kernel(c
 template <bool FIRST, int FAM, bool W>
 __global__ __launch_bounds__(kStepThreads, (StepShape<FAM, W>::WAVES)) void step_kernel_batch(const StepBatchArgs B) {
     extern __shared__ float lds[];
-    __shared__ uint32_t st_cnt[kStepMaxLevels];
+    __shared__ uint32_t st_cnt[3 * kStepMaxLevels];
     const ConstBeamPtr beams = (ConstBeamPtr)B.beams;
     const ConstI64Ptr base = (ConstI64Ptr)B.item_base;
     int b = 0;
@@ -1087,6 +1118,25 @@ __global__ __launch_bounds__(64, 6) void exh_kernel(const ExhArgs A) {
         for (int v = 0; v < 4; ++v) on = on || (m0 + v < A.n_out && best[v] > A.threshold);
         const bool any = __ballot(on) != 0;
         if (lane == 0) A.above[(int64_t)d * A.n_seg + g] = any ? 1u : 0u;
+        if (A.edge && g + 1 == A.n_seg && A.n_out % kExhSlots) {
+            // the row's last slot against the evaluated slot after it (see StepArgs::edge)
+            float left = __shfl_up(best[3], 1);
+            float right = __shfl_down(best[0], 1);
+            if (lane == 0) left = SPD_NEG_INF;
+            if (lane == 63) right = SPD_NEG_INF;
+            int maxima = 0;
+            bool below = false;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float l = v > 0 ? best[v - 1] : left;
+                const float r = v < 3 ? best[v + 1] : right;
+                const bool in = m0 + v < A.n_out;
+                maxima += __popcll(__ballot(in && best[v] > A.threshold && best[v] > l && best[v] >= r));
+                below = below || (m0 + v + 1 == A.n_out && !(best[v] >= r));
+            }
+            const bool blocked = __ballot(below) != 0 && maxima <= kExhEdgeMaxima;
+            if (lane == 0) A.edge[d] = blocked;
+        }
     }
     if (fetch) {
         ring_put(ring4, (((loaded_to - base) >> 2) + lane) & (kRing4 - 1), nx);
@@ -1386,7 +1436,9 @@ __device__ __forceinline__ uint32_t chunk_test(PA &A, int k, int d, int t, int c
         const float dl = q > 0 ? yn[1][q - 1] : l[2], dr = q + 1 < kGroup ? yn[1][q + 1] : r[2];
         const bool ok = v > A.threshold && v > ul && v > yn[0][q] && v > ur && v > sl && v >= sr &&
                         v >= dl && v >= yn[1][q] && v >= dr;
-        if (ok && slot_kept(A, k, d, m0 + q)) hit |= 1u << q;
+        if (ok && slot_kept(A, k, d, m0 + q) &&
+            !(m0 + q + 1 == slots && A.edge_on[k] && A.edge[(int64_t)k * A.n_dm + d]))
+            hit |= 1u << q;
     }
     return hit;
 }

@@ -68,3 +68,35 @@ def test_short_list_is_a_prefix(dev, cap):
         assert np.array_equal(got, whole.candidates_host()[:cap])
         if cap == 0:
             assert (r.result.cand.cpu().numpy() == 0xA5).all()
+
+
+@pytest.mark.parametrize("method", ["ig1", "exh"])
+@pytest.mark.parametrize("n_out", [2301, 2302, 2303, 2304])
+def test_last_slot_sees_the_evaluated_slot_after_it(dev, method, n_out):
+    """With look-ahead samples the last slot of a row is held against the slot after it where the search
+    evaluates that one with it (same group of 4, exhaustive: same 256); planes and candidates only."""
+    from paper_1910_08324_amd import spd
+    n_dm, n, l_end = 6, 2900, 200
+    pulses = [synth.Pulse(0, n_out - 1, 3, 30.0), synth.Pulse(1, n_out, 1, 30.0), synth.Pulse(2, n_out - 20, 40, 40.0),
+              synth.Pulse(3, n_out - 1, 1, 30.0), synth.Pulse(4, n_out - 100, 190, 40.0)]
+    x, mu, sg = make_input(n_dm, n, 79, pulses=pulses)
+    t = [torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to(dev) for a in (x, mu, sg)]
+    wide = spd.search(*t, spd.Config(method, l_end, threshold=6.0), n_out=n_out + 64 * 4)
+    torch.cuda.synchronize()
+    for planes in (True, False):
+        r = spd.search(*t, spd.Config(method, l_end, threshold=6.0, planes=planes), n_out=n_out)
+        torch.cuda.synchronize()
+        got = {(int(c["level"]), int(c["dm"]), int(c["start"])) for c in r.candidates_host()}
+        for i in range(r.info.n_levels):
+            k, slots = int(r.info.level_shift[i]), int(r.info.plane_slots[i])
+            Y = np.full((n_dm + 2, slots + 2), -np.inf, np.float32)
+            Y[1:-1, 1:-1] = wide.level(i)[0][:, :slots].cpu().numpy()
+            after = wide.level(i)[0][:, slots].cpu().numpy()
+            for d in range(n_dm):
+                c, m = Y[d + 1, slots], slots - 1
+                ok = c > 6.0 and all(c > v for v in (*Y[d, slots - 1:slots + 2], Y[d + 1, slots - 1])) and \
+                    all(c >= v for v in (Y[d + 1, slots + 1], *Y[d + 2, slots - 1:slots + 2]))
+                seen = slots % (256 if method == "exh" else 4) != 0
+                if ok and seen and not c >= after[d]:
+                    ok = False
+                assert ((i, d, m << k) in got) == ok, (method, planes, i, d)
