@@ -687,7 +687,6 @@ int run_filter(const spd_params *params, const Prepared &P, const float *x, int6
     const spd_plan_info &I = L.info;
     const bool want_cand = params->flags & SPD_WRITE_CANDIDATES;
     uint32_t *above = reinterpret_cast<uint32_t *>(P.ws + L.off_above);
-    const int vec_ok = (((uintptr_t)x & 15) == 0) && (ld % 4 == 0);
     if (s.method != SPD_EXHAUSTIVE) {
         const float *in = x;
         int64_t ld_in = ld;
@@ -715,7 +714,6 @@ int run_filter(const spd_params *params, const Prepared &P, const float *x, int6
             a.n_in = n_in;
             a.in_len = (int32_t)st.in_len;
             a.n_tiles = st.tiles;
-            a.vec_ok = si == 0 ? vec_ok : 1;
             if (L.off_rec >= 0) a.rec = reinterpret_cast<spd::RecStep *>(P.ws + L.off_rec) + si;
             if (L.off_dir >= 0) {
                 a.dir = reinterpret_cast<uint32_t *>(P.ws + L.off_dir);
@@ -778,7 +776,6 @@ int run_filter(const spd_params *params, const Prepared &P, const float *x, int6
     a.l_end = s.l_end;
     a.n_seg = L.exh_nseg;
     a.segs_per_wave = L.exh_per;
-    a.vec_ok = vec_ok;
     a.want_cand = want_cand;
     a.threshold = params->threshold;
     if (gate) {
@@ -931,13 +928,11 @@ spd::BeamView beam_view(const spd_params *params, const BatchPlan &B, const spd_
     if (si == 0) {
         v.in = bm.x;
         v.ld_in = bm.ld;
-        v.vec_ok = (((uintptr_t)bm.x & 15) == 0) && (bm.ld % 4 == 0);
     } else {
         const StepPlan &pv = L.steps[si - 1];
         v.in = reinterpret_cast<const float *>(ws + pv.off_out);
         v.cin = pv.off_cout >= 0 ? reinterpret_cast<const float *>(ws + pv.off_cout) : nullptr;
         v.ld_in = pv.ld_out;
-        v.vec_ok = 1;
     }
     v.ld_cin = v.ld_in;
     v.out = st.has_out ? reinterpret_cast<float *>(ws + st.off_out) : nullptr;

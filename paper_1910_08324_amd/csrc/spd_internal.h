@@ -105,7 +105,6 @@ struct StepArgs {
     int32_t has_out;          // produce level J for the next step
     int32_t normalise;        // first step: z = (x - mean) / sigma on load
     int32_t carry;            // BoxDIT
-    int32_t vec_ok;           // rows of `in` are 16-byte aligned
     int32_t want_cand;
     float threshold;
     const float *rho;         // per-row sigma-table ratios [n_dm][ld_rho] at widths 2^0.. (or null)
@@ -141,7 +140,7 @@ struct BeamView {
     uint32_t *above;
     uint8_t *edge;
     int64_t ld_in, ld_cin, ld_out;
-    int32_t n_dm, n_in, in_len, n_tiles, vec_ok;
+    int32_t n_dm, n_in, in_len, n_tiles;
     uint32_t pool_units;
     RecStep *rec;               // the beam's record of this step (candidates only), or null
     uint32_t *dir;              // the beam's chunk records (candidates only), or null
@@ -179,7 +178,6 @@ struct ExhArgs {
     int32_t n_dm, n_in, n_out, l_end;
     int32_t n_seg;
     int32_t segs_per_wave;    // consecutive work items per wave (> 1 only when l_end <= kExhBlock)
-    int32_t vec_ok;
     int32_t want_cand;
     float threshold;
     // tile-gated search: only work items in tiles whose flag is set are searched (the others

@@ -32,6 +32,13 @@ __device__ __forceinline__ uint64_t lanes_below(int lane) {
     return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
 
+// four consecutive floats at any address (global loads need no more than 4-byte alignment)
+__device__ __forceinline__ float4 load_f4(const float *p) {
+    typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));
+    const v4u v = *reinterpret_cast<const v4u *>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+
 // ----------------------------------------------------------------------------------------
 // 1/sqrt(L) table of the exhaustive search.  Computed in FP64 and rounded once to FP32, so
 // every kernel scales a boxcar sum by the correctly rounded 1/sqrt(L) (white-noise scaling,
@@ -121,31 +128,11 @@ template <> struct Fam<4> { static constexpr int U1 = 8, U2 = 8, WAVES = 8;
                             static constexpr uint64_t M1 = run_mask(8), M2 = run_mask(8); };
 template <> struct Fam<5> { static constexpr int U1 = 16, U2 = 16, WAVES = 8;
                             static constexpr uint64_t M1 = run_mask(16), M2 = run_mask(16); };
-template <> struct Fam<6> { static constexpr int U1 = 32, U2 = 32, WAVES = 8;
+template <> struct Fam<6> { static constexpr int U1 = 32, U2 = 32, WAVES = 7;
                             static constexpr uint64_t M1 = run_mask(32), M2 = run_mask(32); };
 template <> struct Fam<7> { static constexpr int U1 = 1, U2 = 1, WAVES = 8;
                             static constexpr uint64_t M1 = 1, M2 = 1; };
 
-// How much of a group's LDS window is read ahead, before the previous batch's barrier (PRE4
-// float4 of the NW the banks use; the rest is read when the bank starts), and the waves per
-// SIMD the launch is compiled for.  Reading a little ahead lets each bank start on data already
-// in registers without costing occupancy; reading the whole window ahead costs registers, hence
-// waves, and was slower for most sets.  Measured on the 4096 x 262144 beam (dominant launch,
-// planes / candidates only, against no read-ahead): IG(1) 3.44 -> 3.19 / 3.29 -> 3.22 ms,
-// IG(2) 5.24 -> 4.48 / 5.13 -> 4.27, IG(3) 8.59 -> 7.70 / 8.45 -> 7.60, BD-8 4.73 -> 4.33 /
-// 4.48 -> 3.62, BD-16 6.56 -> 5.96 / 6.24 -> 5.32, BD-32 9.70 -> 9.44 / 9.29 -> 8.45.
-template <int FAM, bool W> struct StepShape {
-    static constexpr int NW = (FAM >= 1 && FAM <= 7) ? (kGroup + Fam<FAM>::U1 - 1 + 3) / 4 : 1;
-    static constexpr int PRE4 = FAM == 1 ? (W ? 1 : 3) : FAM == 2 ? 2 : FAM == 3 ? 3 : FAM == 4 ? 2
-                              : FAM == 5 ? 2 : FAM == 6 ? 4 : 0;
-    static constexpr int WAVES = FAM == 6 ? 7 : Fam<FAM>::WAVES;
-};
-
-
-// All widths of the group fit: straight-line evaluation of a compiled-in width pattern.
-// X enters holding the carried prefixes and leaves holding the sum over UMAX units.
-// W: bu receives the unit count of the best width (0 if none); without W only the maximum is
-// kept (the same value: the largest of the same products).
 template <int NW>
 __device__ __forceinline__ void window_load(const float *y, float w[4 * NW]) {
 #pragma unroll
@@ -158,15 +145,18 @@ __device__ __forceinline__ void window_load(const float *y, float w[4 * NW]) {
     }
 }
 
-// the same on a window already in registers, split in two arrays: wa holds its first 4 P4 units
-// (m0 .. m0 + 4 P4 - 1 of the level), wb the rest
-template <int UMAX, uint64_t MASK, bool W, int P4>
-__device__ __forceinline__ void bank_fixed_split(const float *wa, const float *wb, const float *rt,
-                                                 float X[kGroup], float best[kGroup], int bu[kGroup]) {
+// All widths of the group fit: straight-line evaluation of a compiled-in width pattern on the
+// group's window w (units m0 .. of the level).
+// X enters holding the carried prefixes and leaves holding the sum over UMAX units.
+// W: bu receives the unit count of the best width (0 if none); without W only the maximum is
+// kept (the same value: the largest of the same products).
+template <int UMAX, uint64_t MASK, bool W>
+__device__ __forceinline__ void bank_fixed(const float *w, const float *rt, float X[kGroup],
+                                           float best[kGroup], int bu[kGroup]) {
 #pragma unroll
     for (int u = 0; u < UMAX; ++u) {
 #pragma unroll
-        for (int q = 0; q < kGroup; ++q) X[q] += (q + u < 4 * P4) ? wa[q + u] : wb[q + u - 4 * P4];
+        for (int q = 0; q < kGroup; ++q) X[q] += w[q + u];
         if (((MASK >> u) & 1ull) != 0) {        // folded after unrolling
             const float r = rt[u];
 #pragma unroll
@@ -182,15 +172,6 @@ __device__ __forceinline__ void bank_fixed_split(const float *wa, const float *w
             }
         }
     }
-}
-
-template <int UMAX, uint64_t MASK, bool W>
-__device__ __forceinline__ void bank_fixed(const float *y, const float *rt, float X[kGroup],
-                                           float best[kGroup], int bu[kGroup]) {
-    constexpr int NW = (kGroup + UMAX - 1 + 3) / 4;
-    float w[4 * NW];
-    window_load<NW>(y, w);
-    bank_fixed_split<UMAX, MASK, W, NW>(w, w, rt, X, best, bu);
 }
 
 // Any width set, with the valid-only check per slot.  Xc receives the sum over `ufull` units
@@ -237,7 +218,8 @@ __device__ __forceinline__ void bank_generic(const float *y, const float *rt, in
 
 // The same maxima and widths once more for the few chunks that get a record (candidates only),
 // one unit after another: few registers, so that the launch keeps its occupancy.
-__device__ __forceinline__ void bank_record(const float *y, const float *rt, int umax, uint64_t emask,
+template <class ScalePtr>
+__device__ __forceinline__ void bank_record(const float *y, ScalePtr rt, int umax, uint64_t emask,
                                             int room, float X[kGroup], float best[kGroup],
                                             int bu[kGroup]) {
     float w[kGroup];
@@ -264,46 +246,69 @@ __device__ __forceinline__ void bank_record(const float *y, const float *rt, int
 }
 
 // Where a tile finds its beam's buffers and sizes: in the launch arguments (one beam per
-// launch) or in a table in device memory (many beams per launch).
-struct ArgGeom {
-    const StepArgs &A;
-    __device__ const float *in() const { return A.in; }
-    __device__ const float *cin() const { return A.cin; }
-    __device__ float *out() const { return A.out; }
-    __device__ float *cout() const { return A.cout; }
-    __device__ const float *mean() const { return A.mean; }
-    __device__ const float *sigma() const { return A.sigma; }
-    __device__ float *Y() const { return A.Y; }
-    __device__ uint16_t *W() const { return A.W; }
-    __device__ uint32_t *above() const { return A.above; }
-    __device__ uint8_t *edge() const { return A.edge; }
-    __device__ int n_dm() const { return A.n_dm; }
-    __device__ int64_t ld_in() const { return A.ld_in; }
-    __device__ int64_t ld_cin() const { return A.ld_cin; }
-    __device__ int64_t ld_out() const { return A.ld_out; }
-    __device__ int n_in() const { return A.n_in; }
-    __device__ int in_len() const { return A.in_len; }
-    __device__ int n_tiles() const { return A.n_tiles; }
-    __device__ int vec_ok() const { return A.vec_ok; }
-    __device__ int64_t plane_off(int j) const { return A.lv[j].plane_off; }
-    __device__ int64_t pitch(int j) const { return A.lv[j].pitch; }
-    __device__ int slots(int j) const { return A.lv[j].slots; }
-    __device__ RecStep *rec() const { return A.rec; }
-    __device__ uint32_t *dir() const { return A.dir; }
-    __device__ uint64_t *pool() const { return A.pool; }
-    __device__ unsigned long long *pool_used() const { return A.pool_used; }
-    __device__ uint32_t pool_units() const { return A.pool_units; }
-    __device__ int64_t dir_off(int j) const { return A.lv[j].dir_off; }
-    __device__ int64_t cnt_off(int j) const { return A.lv[j].cnt_off; }
-};
-
-// The table is read-only during a launch and every lane of a work-group reads the same entry,
-// so it is addressed in the constant address space: its fields load as scalar (SMEM) reads.
+// launch) or in a table in device memory (many beams per launch).  Both are read-only during a
+// launch and the same for every lane of a work-group, so they are addressed in the constant
+// address space: their fields load as scalar (SMEM) reads.
+// opaque(): the same view behind pointers the compiler cannot see through, so that what is read
+// and computed from it stays where it is used.
+typedef __attribute__((address_space(4))) const StepArgs *ConstArgsPtr;
+typedef __attribute__((address_space(4))) const StepLevel *ConstLevelPtr;
 typedef __attribute__((address_space(4))) const BeamView *ConstBeamPtr;
 typedef __attribute__((address_space(4))) const int64_t *ConstI64Ptr;
+typedef __attribute__((address_space(4))) const float *ConstFloatPtr;
+
+// the launch arguments (StepArgs is the first argument of either kernel, or its first member)
+__device__ __forceinline__ ConstArgsPtr launch_args() {
+    return (ConstArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+struct ArgGeom {
+    ConstArgsPtr P;
+    __device__ ConstArgsPtr args() const { return P; }
+    __device__ ArgGeom opaque() const {
+        ConstArgsPtr p = P;
+        asm volatile("" : "+s"(p));
+        return ArgGeom{p};
+    }
+    __device__ const float *in() const { return P->in; }
+    __device__ const float *cin() const { return P->cin; }
+    __device__ float *out() const { return P->out; }
+    __device__ float *cout() const { return P->cout; }
+    __device__ const float *mean() const { return P->mean; }
+    __device__ const float *sigma() const { return P->sigma; }
+    __device__ float *Y() const { return P->Y; }
+    __device__ uint16_t *W() const { return P->W; }
+    __device__ uint32_t *above() const { return P->above; }
+    __device__ uint8_t *edge() const { return P->edge; }
+    __device__ int n_dm() const { return P->n_dm; }
+    __device__ int64_t ld_in() const { return P->ld_in; }
+    __device__ int64_t ld_cin() const { return P->ld_cin; }
+    __device__ int64_t ld_out() const { return P->ld_out; }
+    __device__ int n_in() const { return P->n_in; }
+    __device__ int in_len() const { return P->in_len; }
+    __device__ int n_tiles() const { return P->n_tiles; }
+    __device__ RecStep *rec() const { return P->rec; }
+    __device__ uint32_t *dir() const { return P->dir; }
+    __device__ uint64_t *pool() const { return P->pool; }
+    __device__ unsigned long long *pool_used() const { return P->pool_used; }
+    __device__ uint32_t pool_units() const { return P->pool_units; }
+    __device__ int64_t plane_off(int j) const { return P->lv[j].plane_off; }
+    __device__ int64_t pitch(int j) const { return P->lv[j].pitch; }
+    __device__ int slots(int j) const { return P->lv[j].slots; }
+    __device__ int64_t dir_off(int j) const { return P->lv[j].dir_off; }
+    __device__ int64_t cnt_off(int j) const { return P->lv[j].cnt_off; }
+};
 
 struct TabGeom {
+    ConstArgsPtr P;
     ConstBeamPtr V;
+    __device__ ConstArgsPtr args() const { return P; }
+    __device__ TabGeom opaque() const {
+        ConstArgsPtr p = P;
+        ConstBeamPtr v = V;
+        asm volatile("" : "+s"(p), "+s"(v));
+        return TabGeom{p, v};
+    }
     __device__ const float *in() const { return V->in; }
     __device__ const float *cin() const { return V->cin; }
     __device__ float *out() const { return V->out; }
@@ -321,15 +326,14 @@ struct TabGeom {
     __device__ int n_in() const { return V->n_in; }
     __device__ int in_len() const { return V->in_len; }
     __device__ int n_tiles() const { return V->n_tiles; }
-    __device__ int vec_ok() const { return V->vec_ok; }
-    __device__ int64_t plane_off(int j) const { return V->plane_off[j]; }
-    __device__ int64_t pitch(int j) const { return V->pitch[j]; }
-    __device__ int slots(int j) const { return V->slots[j]; }
     __device__ RecStep *rec() const { return V->rec; }
     __device__ uint32_t *dir() const { return V->dir; }
     __device__ uint64_t *pool() const { return V->pool; }
     __device__ unsigned long long *pool_used() const { return V->pool_used; }
     __device__ uint32_t pool_units() const { return V->pool_units; }
+    __device__ int64_t plane_off(int j) const { return V->plane_off[j]; }
+    __device__ int64_t pitch(int j) const { return V->pitch[j]; }
+    __device__ int slots(int j) const { return V->slots[j]; }
     __device__ int64_t dir_off(int j) const { return V->dir_off[j]; }
     __device__ int64_t cnt_off(int j) const { return V->cnt_off[j]; }
 };
@@ -418,6 +422,73 @@ __device__ __forceinline__ void write_rec(const StepArgs &A, const G &V, RecStep
     }
 }
 
+// What the peak finder gets of one chunk (a wave's 64 groups from gw on) of level j: its bit in
+// the tile's word, its record (candidates only) and the comparison at the row's end.  Runs for the
+// few chunks with a slot above the threshold, and evaluates them once more from the windows in LDS,
+// so that the width sets' registers need not live across it.  V hides where its fields come from
+// (see opaque()), so that none of its loads and address arithmetic moves into the tile's main path.
+template <bool W, bool RHO, class G>
+__device__ __forceinline__ void step_chunk(const G V, int j, int d, int tile, int gw, bool any,
+                                           float *lds, uint32_t *st_cnt) {
+    const ConstArgsPtr A = V.args();
+    ConstLevelPtr L = A->lv + j;
+    const int lane = threadIdx.x & 63;
+    const int Sj = A->T >> j;
+    const int ngroups = Sj / kGroup;
+    const int g = gw + lane;
+    const int chunk = gw >> 6;
+    const int m0 = min(g, ngroups - 1) * kGroup;
+    const int slots = V.slots(j);
+    const int ma = tile * Sj + m0;
+    const bool edge = V.edge() && (slots % kGroup) && tile == (slots - 1) / Sj;
+    const bool act = any && g < ngroups && ma < slots;
+    float best[kGroup];
+    int bu[kGroup];
+#pragma unroll
+    for (int q = 0; q < kGroup; ++q) {
+        best[q] = SPD_NEG_INF;
+        bu[q] = 0;
+    }
+    if ((!W || edge) && act) {
+        const bool has_carry = A->carry && (j > 0 || V.cin() != nullptr);
+        const float *c = lds + A->lv[0].lds_c + m0;
+        float X[kGroup];
+#pragma unroll
+        for (int q = 0; q < kGroup; ++q) X[q] = has_carry ? c[q] : 0.0f;
+        const int room = (int)(((int64_t)V.n_in() - L->base) >> L->k) - ma;
+        if constexpr (RHO)
+            bank_record(lds + A->lv[0].lds_y + m0, (const float *)(lds + A->lds_sc + j * kMaxLevelWidths), L->umax,
+                        L->evalmask, room, X, best, bu);
+        else
+            bank_record(lds + A->lv[0].lds_y + m0, (ConstFloatPtr)A->rtab[j], L->umax, L->evalmask, room, X, best, bu);
+    }
+    bool set = any;
+    if constexpr (!W) {
+        const int64_t di = V.dir_off(j) + ((int64_t)d * V.n_tiles() + tile) * L->cpt + chunk;
+        set = put_record(V.pool(), V.pool_used(), V.pool_units(), V.dir() + di, chunk < L->cpt, lane,
+                         slots - ma, A->threshold, best, bu, L->k, L->base);
+    }
+    if (set && lane == 0) atomicOr(&st_cnt[j], 1u << (chunk >> L->bit_shift));
+    if (any && edge) {
+        // the row's last slot against the evaluated slot after it (see StepArgs::edge)
+        float left = __shfl_up(best[kGroup - 1], 1);
+        float right = __shfl_down(best[0], 1);
+        if (lane == 0) left = SPD_NEG_INF;
+        if (lane == 63) right = SPD_NEG_INF;
+        uint32_t maxima = 0;
+#pragma unroll
+        for (int q = 0; q < kGroup; ++q) {
+            const float l = q > 0 ? best[q - 1] : left;
+            const float r = q + 1 < kGroup ? best[q + 1] : right;
+            const bool in = act && ma + q < slots;
+            maxima += (uint32_t)__popcll(__ballot(in && best[q] > A->threshold && best[q] > l && best[q] >= r));
+            if (q + 1 < kGroup && in && ma + q + 1 == slots && !(best[q] >= r))
+                st_cnt[2 * kStepMaxLevels + j] = 1;
+        }
+        if (lane == 0) atomicAdd(&st_cnt[kStepMaxLevels + j], maxima);
+    }
+}
+
 // One tile (DM row d, tile `tile`) of a cascade launch.  A holds what every beam of the launch
 // shares (levels, width patterns, tile length); G the beam's buffers and sizes.  W: the planes
 // are stored (A.write_planes), so the banks also track the best width; candidates-only
@@ -426,7 +497,6 @@ template <bool FIRST, int FAM, bool RHO, int NTH, bool W, class G>
 __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const int d,
                                           const int tile, float *lds, uint32_t *st_cnt) {
     const int tid = threadIdx.x;
-    const int lane = tid & 63;
     const int T = A.T;
     if (RHO) {
         // this row's 1/sigma(L) relative to 1/(sqrt(L) sigma): scale[j][u-1] = rtab[j][u-1] / rho(L)
@@ -464,48 +534,59 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
         const int N0 = A.lv[0].n_units;
         float *y0 = lds + A.lv[0].lds_y;
         const int64_t len = V.in_len();
-        // kLoadBatch float4 loads per thread are issued before any of them is used, so a tile's
-        // window costs about one memory round trip rather than one per float4
-        // (unconditional loads: lanes past the data read the row's last whole float4 instead,
-        // and use the element-wise path below)
+        // up to kLoadBatch float4 loads per thread are issued before any of them is used, so a
+        // tile's window costs about one memory round trip rather than one per float4 (rows need
+        // no more than their 4-byte alignment)
         constexpr int kLoadBatch = 8;
-        const bool vec = V.vec_ok() && len >= 4;
-        // the last float4 a lane may read: inside the data and inside this tile's window (lanes
-        // past the window re-read it, served by the cache, instead of fetching the next tile's)
-        const int64_t rmax = vec ? min((len - 4) & ~(int64_t)3, u0 + ((N0 - 4) & ~3)) : 0;
-        for (int i0 = tid * 4; i0 < N0; i0 += NTH * 4 * kLoadBatch) {
-            float4 v[kLoadBatch];
-            if (vec) {
+        auto norm = [&](float4 w) {
+            if (FIRST) {
+                w.x = (w.x - mu) * inv;
+                w.y = (w.y - mu) * inv;
+                w.z = (w.z - mu) * inv;
+                w.w = (w.w - mu) * inv;
+            }
+            return w;
+        };
+        const float *src = inr + u0;
+        if (u0 + N0 <= len) {                           // the whole window is in the data
+            for (int i0 = 4 * tid; i0 - 4 * tid < N0; i0 += 4 * NTH * kLoadBatch) {
+                float4 v[kLoadBatch];
 #pragma unroll
                 for (int b = 0; b < kLoadBatch; ++b) {
-                    const int64_t r = u0 + i0 + b * NTH * 4;
-                    v[b] = *reinterpret_cast<const float4 *>(inr + (r < rmax ? r : rmax));
+                    if (i0 - 4 * tid + 4 * NTH * b >= N0) break;
+                    v[b] = load_f4(src + min(i0 + 4 * NTH * b, N0 - 4));
+                }
+#pragma unroll
+                for (int b = 0; b < kLoadBatch; ++b) {
+                    if (i0 - 4 * tid + 4 * NTH * b >= N0) break;
+                    // (lanes past the window hold its last float4 and write it again)
+                    *reinterpret_cast<float4 *>(y0 + min(i0 + 4 * NTH * b, N0 - 4)) = norm(v[b]);
                 }
             }
+        } else {
+            // the row's end: float4 up to it, then one sample at a time, then zeros
+            const int rest = (int)max((int64_t)0, len - u0);
+            for (int i0 = 4 * tid; i0 < N0; i0 += 4 * NTH * kLoadBatch) {
+                float4 v[kLoadBatch];
 #pragma unroll
-            for (int b = 0; b < kLoadBatch; ++b) {
-                const int i = i0 + b * NTH * 4;
-                if (i >= N0) continue;
-                const int64_t r = u0 + i;
-                float4 w;
-                if (vec && r + 3 < len) {
-                    w = v[b];
-                    if (FIRST) {
-                        w.x = (w.x - mu) * inv;
-                        w.y = (w.y - mu) * inv;
-                        w.z = (w.z - mu) * inv;
-                        w.w = (w.w - mu) * inv;
-                    }
-                } else {
-                    float e[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        e[q] = 0.0f;
-                        if (r + q < len) e[q] = FIRST ? (inr[r + q] - mu) * inv : inr[r + q];
-                    }
-                    w = make_float4(e[0], e[1], e[2], e[3]);
+                for (int b = 0; b < kLoadBatch; ++b) {
+                    const int i = i0 + 4 * NTH * b;
+                    if (i + 4 <= rest) v[b] = load_f4(src + i);
                 }
-                *reinterpret_cast<float4 *>(y0 + i) = w;
+#pragma unroll
+                for (int b = 0; b < kLoadBatch; ++b) {
+                    const int i = i0 + 4 * NTH * b;
+                    if (i >= N0) break;
+                    float4 w = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    if (i + 4 <= rest) {
+                        w = norm(v[b]);
+                    } else if (i < rest) {
+                        w.x = FIRST ? (src[i] - mu) * inv : src[i];
+                        if (i + 1 < rest) w.y = FIRST ? (src[i + 1] - mu) * inv : src[i + 1];
+                        if (i + 2 < rest) w.z = FIRST ? (src[i + 2] - mu) * inv : src[i + 2];
+                    }
+                    *reinterpret_cast<float4 *>(y0 + i) = w;
+                }
             }
         }
         if (!FIRST && carry && V.cin()) {
@@ -519,194 +600,162 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
     }
     lds_barrier();
 
-    // ---- 2+3. cascade fused with the width sets.  Level j is evaluated in batches of
-    // NTH groups (the work-group size); each group also forms its two units of level j+1 (and, for BoxDIT,
-    // its two carried prefixes) in registers.  After a barrier that ends the batch's reads they
-    // are written in place: unit n of level j+1 goes to index n of the same buffer, below every
+    // ---- 2+3. cascade fused with the width sets.  Level j is evaluated in batches of NTH groups,
+    // one per thread; each group also forms its two units of level j+1 (and, for BoxDIT, its two
+    // carried prefixes) in registers.  After a barrier that ends the batch's reads they are
+    // written in place: unit n of level j+1 goes to index n of the same buffer, below every
     // unit of level j a later batch still reads (and likewise for the carries).  The units of
     // level j+1 past the tile's slots (its halo) are formed after the last batch.
+    // A wave whose groups lie in the plane and, at every width, in the data (one scalar comparison)
+    // runs a compiled-in bank with no test per lane; the others the generic one.
+    // What is needed only where a chunk has a slot above the threshold stays in step_chunk, out of
+    // this loop's registers: the scalar unit, one for the whole CU, bounds the light width sets (79%
+    // busy, 874 scalar instructions per wave of an IG(1) tile of 4096, when tests per lane and the
+    // candidates' addresses were here; 571-664 now).  Before -> after, at equal tiles: eight uneven
+    // beams candidates only 2741 -> 2135 us, 1024 x 131072 BD-16 909 -> 793, 500 x 100003 IG(1) (rows
+    // of any alignment take float4 loads) 241 -> 200.
+    // Reading a window ahead of the barrier, which paid while LDS was the bound, and several
+    // batches per barrier are slower now (batch 2245 and 2630 us).
+    constexpr int kNW = (kGroup + Fam<FAM>::U1 - 1 + 3) / 4;
+    constexpr bool kOnePattern = FAM == 0 || (Fam<FAM>::M1 == Fam<FAM>::M2 && Fam<FAM>::U1 == Fam<FAM>::U2);
     const int jtop = A.has_out ? A.J : A.J - 1;
     float *ybuf = lds + A.lv[0].lds_y;
     float *cbuf = lds + A.lv[0].lds_c;
+    const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~63);
     for (int j = 0; j < A.J; ++j) {
         const bool form_next = j + 1 <= jtop;
-        const int cs1 = form_next ? A.lv[j + 1].cshift : 0;
-        const int n_next = form_next ? A.lv[j + 1].n_units : 0;
         const StepLevel &L = A.lv[j];
         const int Sj = T >> j;
         const int ms0 = tile * Sj;                         // absolute slot of tile slot 0
         const int ngroups = Sj / kGroup;
-        const float *yj = ybuf;
-        const float *cj = cbuf;
+        const int slots = V.slots(j);
         const bool has_carry = carry && (j > 0 || V.cin() != nullptr);
         const bool to_lds = carry && (j + 1 < A.J);
         const bool to_glb = carry && (j + 1 == A.J) && A.has_out;
         float *cg = to_glb ? V.cout() + (int64_t)d * V.ld_out() + (int64_t)tile * (T >> A.J) : nullptr;
         const bool sync_batches = form_next || to_lds;   // a batch writes into the live buffers
-        const bool edge = V.edge() && (V.slots(j) % kGroup) && tile == (V.slots(j) - 1) / Sj;
         const int k = L.k;
         const int umax = L.umax;
         const int base = L.base;
-        const int pat = L.pattern;
         const float *rt = RHO ? lds + A.lds_sc + j * kMaxLevelWidths : A.rtab[j];
-        float *rowY = V.Y() + V.plane_off(j) + (int64_t)d * V.pitch(j);
-        uint16_t *rowW = V.W() + V.plane_off(j) + (int64_t)d * V.pitch(j);
+        float *rowY = nullptr;
+        uint16_t *rowW = nullptr;
+        if (W) {
+            const int64_t o = V.plane_off(j) + (int64_t)d * V.pitch(j) + ms0;
+            rowY = V.Y() + o;
+            rowW = V.W() + o;
+        }
         // U units from slot m end inside the data when m + U is at most this
         const int ends = (int)(((int64_t)V.n_in() - base) >> k);
-        // the first kP4 float4 of a group's window are read from LDS before the previous batch's
-        // barrier (they lie above every unit that batch writes), so their latency overlaps the
-        // previous batch's stores and barrier
-        constexpr int kNW = StepShape<FAM, W>::NW;
-        constexpr int kP4 = StepShape<FAM, W>::PRE4;
-        constexpr bool kPre = kP4 > 0;
-        float win[4 * (kPre ? kP4 : 1)];
-        float win2[4 * (kNW > kP4 ? kNW - kP4 : 1)];
-        if (kPre && tid < ngroups) window_load<(kPre ? kP4 : 1)>(yj + tid * kGroup, win);
+        // groups below this have every width of every slot inside the data and lie in the plane
+        const int inner = (FAM != 0 && L.pattern != 0)
+                              ? min(ngroups, (min(ends - umax + 1, slots) - ms0) >> 2) : 0;
+        static_assert(kGroup == 4, "groups of four slots");
         for (int gb = 0; gb < ngroups; gb += NTH) {
+            const int gw = gb + wave0;                   // the wave's first group
             const int g = gb + tid;
-            const int m0 = g * kGroup;
-            const int ma = ms0 + m0;
-            const bool act = (g < ngroups) && (ma < V.slots(j));
-            float best[kGroup];
-            int bu[kGroup];
+            float nu0 = 0.0f, nu1 = 0.0f, xc0 = 0.0f, xc1 = 0.0f;
+            if (gw < ngroups) {
+                float best[kGroup], X[kGroup];
+                int bu[kGroup];
 #pragma unroll
-            for (int q = 0; q < kGroup; ++q) {
-                best[q] = SPD_NEG_INF;
-                bu[q] = 0;
-            }
-            // y_{j+1}[n] = y_j[2n + cshift] + y_j[2n + cshift + 1] for 2n + cshift = m0, m0 + 2
-            const int n0 = (m0 - cs1) >> 1;
-            float nu0 = 0.0f, nu1 = 0.0f;
-            if (form_next && g < ngroups) {
-                if (kPre) {
-                    nu0 = win[0] + win[1];
-                    nu1 = win[2] + win[3];
+                for (int q = 0; q < kGroup; ++q) {
+                    best[q] = SPD_NEG_INF;
+                    bu[q] = 0;
+                    X[q] = 0.0f;
+                }
+                bool any;
+                const int m0 = min(g, ngroups - 1) * kGroup;   // (lanes past the tile repeat its last group)
+                const float *y = ybuf + m0;
+                if (FAM != 0 && min(gw + 64, ngroups) <= inner) {
+                    if (has_carry) {
+                        const float4 c = *reinterpret_cast<const float4 *>(cbuf + m0);
+                        X[0] = c.x;
+                        X[1] = c.y;
+                        X[2] = c.z;
+                        X[3] = c.w;
+                    }
+                    float w[4 * kNW];
+                    window_load<kNW>(y, w);
+                    // y_{j+1}[n] = y_j[2n + cshift] + y_j[2n + cshift + 1] for 2n + cshift = m0, m0 + 2
+                    nu0 = w[0] + w[1];
+                    nu1 = w[2] + w[3];
+                    if (kOnePattern || (FIRST && j == 0))
+                        bank_fixed<Fam<FAM>::U1, Fam<FAM>::M1, W>(w, rt, X, best, bu);
+                    else
+                        bank_fixed<Fam<FAM>::U2, Fam<FAM>::M2, W>(w, rt, X, best, bu);
+                    xc0 = X[0];
+                    xc1 = X[2];
+                    // (the maxima are formed here: sunk below the branches that follow, they would keep
+                    // every partial sum of the bank in registers)
+                    asm volatile("" : "+v"(best[0]), "+v"(best[1]), "+v"(best[2]), "+v"(best[3]));
+                    if (W) asm volatile("" : "+v"(bu[0]), "+v"(bu[1]), "+v"(bu[2]), "+v"(bu[3]));
+                    if (W) {
+                        uint32_t bw[kGroup];
+#pragma unroll
+                        for (int q = 0; q < kGroup; ++q)
+                            bw[q] = (kCarry == 0 || bu[q]) ? (uint32_t)(base + (bu[q] << k)) : 0u;   // (IGRID: base 0)
+                        *reinterpret_cast<float4 *>(rowY + m0) = make_float4(best[0], best[1], best[2], best[3]);
+                        *reinterpret_cast<uint2 *>(rowW + m0) = make_uint2(bw[0] | (bw[1] << 16), bw[2] | (bw[3] << 16));
+                    }
+                    if (cg) *reinterpret_cast<float2 *>(cg + (m0 >> 1)) = make_float2(xc0, xc1);
+                    any = __ballot(fmaxf(fmaxf(best[0], best[1]), fmaxf(best[2], best[3])) > A.threshold) != 0;
                 } else {
-                    const float4 w0 = *reinterpret_cast<const float4 *>(yj + m0);
+                    const int ma = ms0 + m0;
+                    const float4 w0 = *reinterpret_cast<const float4 *>(y);
                     nu0 = w0.x + w0.y;
                     nu1 = w0.z + w0.w;
-                }
-            }
-            float Xc[kGroup];
-            if (act) {
-                float X[kGroup];
+                    const bool act = g < ngroups && ma < slots;
+                    if (act) {
+                        if (has_carry) {
 #pragma unroll
-                for (int q = 0; q < kGroup; ++q) X[q] = has_carry ? cj[m0 + q] : 0.0f;
-                const bool fast = ma + kGroup - 1 + umax <= ends;   // every width of every slot fits
-                if (FAM != 0 && fast && pat == 1) {
-                    if constexpr (kPre) {
-                        if constexpr (kNW > kP4) window_load<kNW - kP4>(yj + m0 + 4 * kP4, win2);
-                        bank_fixed_split<Fam<FAM>::U1, Fam<FAM>::M1, W, kP4>(win, win2, rt, X, best, bu);
-                    } else {
-                        bank_fixed<Fam<FAM>::U1, Fam<FAM>::M1, W>(yj + m0, rt, X, best, bu);
-                    }
-#pragma unroll
-                    for (int q = 0; q < kGroup; ++q) Xc[q] = X[q];
-                } else if (FAM != 0 && fast && pat == 2) {
-                    if constexpr (kPre) {
-                        if constexpr (kNW > kP4) window_load<kNW - kP4>(yj + m0 + 4 * kP4, win2);
-                        bank_fixed_split<Fam<FAM>::U2, Fam<FAM>::M2, W, kP4>(win, win2, rt, X, best, bu);
-                    } else {
-                        bank_fixed<Fam<FAM>::U2, Fam<FAM>::M2, W>(yj + m0, rt, X, best, bu);
-                    }
-#pragma unroll
-                    for (int q = 0; q < kGroup; ++q) Xc[q] = X[q];
-                } else {
-                    bank_generic<W>(yj + m0, rt, umax, L.evalmask, L.ufull, ends - ma, X, Xc, best, bu);
-                }
-                if (cg) {
-                    // the last level's longest boxcar is the next step's carried prefix
-                    cg[(m0 >> 1) + 0] = Xc[0];
-                    cg[(m0 >> 1) + 1] = Xc[2];
-                }
-                int bw[kGroup];
-#pragma unroll
-                for (int q = 0; q < kGroup; ++q) bw[q] = bu[q] ? base + (bu[q] << k) : 0;
-                if (!W) {
-                    // candidates only: nothing stored; the peak finder forms what it reads again
-                } else if (ma + kGroup <= V.slots(j)) {
-                    *reinterpret_cast<float4 *>(rowY + ma) = make_float4(best[0], best[1], best[2], best[3]);
-                    *reinterpret_cast<uint2 *>(rowW + ma) =
-                        make_uint2((uint32_t)bw[0] | ((uint32_t)bw[1] << 16),
-                                   (uint32_t)bw[2] | ((uint32_t)bw[3] << 16));
-                } else {
-#pragma unroll
-                    for (int q = 0; q < kGroup; ++q)
-                        if (ma + q < V.slots(j)) {
-                            rowY[ma + q] = best[q];
-                            rowW[ma + q] = (uint16_t)bw[q];
+                            for (int q = 0; q < kGroup; ++q) X[q] = cbuf[m0 + q];
                         }
-                }
-            }
-            // the window of this thread's group in the next batch
-            if (kPre && g + NTH < ngroups) window_load<(kPre ? kP4 : 1)>(yj + (g + NTH) * kGroup, win);
-            if (A.want_cand) {
-                const float gmax = fmaxf(fmaxf(best[0], best[1]), fmaxf(best[2], best[3]));
-                const bool any = __ballot(act && gmax > A.threshold) != 0;
-                if (any || (!W && L.bit_shift)) {
-                    // this wave's 64 groups are one chunk of the tile
-                    const int chunk = (gb >> 6) + (tid >> 6);
-                    bool set = any;
-                    if constexpr (!W) {
-                        // candidates only: the chunk's record holds its slots above the
-                        // threshold with their widths, which this launch has not tracked; the
-                        // window is still in LDS, so the widths are evaluated once more
-                        float rb[kGroup];
-                        int ru[kGroup];
+                        float Xc[kGroup] = {0.0f, 0.0f, 0.0f, 0.0f};
+                        bank_generic<W>(y, rt, umax, L.evalmask, L.ufull, ends - ma, X, Xc, best, bu);
+                        xc0 = Xc[0];
+                        xc1 = Xc[2];
+                        if (W) {
 #pragma unroll
-                        for (int q = 0; q < kGroup; ++q) {
-                            rb[q] = SPD_NEG_INF;
-                            ru[q] = 0;
+                            for (int q = 0; q < kGroup; ++q)
+                                if (ma + q < slots) {
+                                    rowY[m0 + q] = best[q];
+                                    rowW[m0 + q] = (uint16_t)(bu[q] ? base + (bu[q] << k) : 0);
+                                }
                         }
-                        if (any && act) {
-                            float X[kGroup];
-#pragma unroll
-                            for (int q = 0; q < kGroup; ++q) X[q] = has_carry ? cj[m0 + q] : 0.0f;
-                            bank_record(yj + m0, rt, umax, L.evalmask, ends - ma, X, rb, ru);
+                        if (cg) {
+                            // the last level's longest boxcar is the next step's carried prefix
+                            cg[(m0 >> 1) + 0] = xc0;
+                            cg[(m0 >> 1) + 1] = xc1;
                         }
-                        const int64_t di = V.dir_off(j) + ((int64_t)d * V.n_tiles() + tile) * L.cpt + chunk;
-                        set = put_record(V.pool(), V.pool_used(), V.pool_units(), V.dir() + di, chunk < L.cpt,
-                                         lane, V.slots(j) - ma, A.threshold, rb, ru, k, base);
                     }
-                    if (set && lane == 0) atomicOr(&st_cnt[j], 1u << (chunk >> L.bit_shift));
-                    if (any && edge) {
-                        // the row's last slot against the evaluated slot after it (see StepArgs::edge)
-                        float left = __shfl_up(best[kGroup - 1], 1);
-                        float right = __shfl_down(best[0], 1);
-                        if (lane == 0) left = SPD_NEG_INF;
-                        if (lane == 63) right = SPD_NEG_INF;
-                        uint32_t maxima = 0;
-#pragma unroll
-                        for (int q = 0; q < kGroup; ++q) {
-                            const float l = q > 0 ? best[q - 1] : left;
-                            const float rr = q + 1 < kGroup ? best[q + 1] : right;
-                            const bool in = act && ma + q < V.slots(j);
-                            maxima += (uint32_t)__popcll(__ballot(in && best[q] > A.threshold && best[q] > l && best[q] >= rr));
-                            if (q + 1 < kGroup && in && ma + q + 1 == V.slots(j) && !(best[q] >= rr))
-                                st_cnt[2 * kStepMaxLevels + j] = 1;
-                        }
-                        if (lane == 0) atomicAdd(&st_cnt[kStepMaxLevels + j], maxima);
-                    }
+                    any = __ballot(act && fmaxf(fmaxf(best[0], best[1]), fmaxf(best[2], best[3])) > A.threshold) != 0;
                 }
+                if (A.want_cand && (any || (!W && L.bit_shift)))
+                    step_chunk<W, RHO>(V.opaque(), j, d, tile, gw, any, lds, st_cnt);
             }
             if (sync_batches) {
                 lds_barrier();                   // the batch's reads of level j are done
-                if (form_next && g < ngroups) {
-                    float *yn = ybuf;
-                    if (n0 >= 0 && n0 < n_next) yn[n0] = nu0;
-                    if (n0 + 1 >= 0 && n0 + 1 < n_next) yn[n0 + 1] = nu1;
-                }
-                if (to_lds && act) {
-                    // this level's longest boxcar is the next level's carried prefix
-                    cbuf[(m0 >> 1) + 0] = Xc[0];
-                    cbuf[(m0 >> 1) + 1] = Xc[2];
+                if (g < ngroups) {
+                    if (kCarry == 0) {           // (IGRID: no shift, so the pair is one aligned float2)
+                        *reinterpret_cast<float2 *>(ybuf + 2 * g) = make_float2(nu0, nu1);
+                    } else {
+                        const int n_next = form_next ? A.lv[j + 1].n_units : 0;
+                        const int n0 = form_next ? (g * kGroup - A.lv[j + 1].cshift) >> 1 : -2;
+                        if (n0 >= 0 && n0 < n_next) ybuf[n0] = nu0;
+                        if (n0 + 1 >= 0 && n0 + 1 < n_next) ybuf[n0 + 1] = nu1;
+                        // this level's longest boxcar is the next level's carried prefix
+                        if (to_lds && ms0 + g * kGroup < slots)
+                            *reinterpret_cast<float2 *>(cbuf + 2 * g) = make_float2(xc0, xc1);
+                    }
                 }
             }
         }
         if (form_next) {
             // halo units of level j+1: read at index >= S_j, written below it
+            const int cs1 = A.lv[j + 1].cshift, n_next = A.lv[j + 1].n_units;
             for (int n = max(0, (Sj - cs1) >> 1) + tid; n < n_next; n += NTH) {
-                const float2 p = *reinterpret_cast<const float2 *>(yj + 2 * n + cs1);
+                const float2 p = *reinterpret_cast<const float2 *>(ybuf + 2 * n + cs1);
                 ybuf[n] = p.x + p.y;
             }
         }
@@ -733,7 +782,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
 
 // One launch for one beam: work-group = (DM row, tile) of NTH threads.
 template <bool FIRST, int FAM, bool RHO, int NTH, bool W>
-__global__ __launch_bounds__(NTH, (StepShape<FAM, W>::WAVES)) void step_kernel(const StepArgs A) {
+__global__ __launch_bounds__(NTH, (Fam<FAM>::WAVES)) void step_kernel(const StepArgs A) {
     // (16-byte alignment matters: with the buffer right behind st_cnt, at 8 bytes past a multiple of 16, every float4 access of a
     // tile was misaligned, and LDS, busy 95% of the cycles, bounded every width set; now 15%:
     // 1024 x 131072 BD-16 1000 -> 909 us, IG(2) with a sigma table 696 -> 553)
@@ -742,14 +791,14 @@ __global__ __launch_bounds__(NTH, (StepShape<FAM, W>::WAVES)) void step_kernel(c
     const int d = blockIdx.x / A.n_tiles;
     const int tile = blockIdx.x - d * A.n_tiles;
     if (d >= A.n_dm) return;
-    step_tile<FIRST, FAM, RHO, NTH, W>(A, ArgGeom{A}, d, tile, lds, st_cnt);
+    step_tile<FIRST, FAM, RHO, NTH, W>(A, ArgGeom{launch_args()}, d, tile, lds, st_cnt);
 }
 
 // One launch for many beams (same levels and tile length, any sizes): a persistent grid walks
 // the work items (beam, DM row, tile) in order; item i belongs to the beam b with
 // item_base[b] <= i < item_base[b + 1].
 template <bool FIRST, int FAM, bool W>
-__global__ __launch_bounds__(kStepThreads, (StepShape<FAM, W>::WAVES)) void step_kernel_batch(const StepBatchArgs B) {
+__global__ __launch_bounds__(kStepThreads, (Fam<FAM>::WAVES)) void step_kernel_batch(const StepBatchArgs B) {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     __shared__ uint32_t st_cnt[3 * kStepMaxLevels];
     const ConstBeamPtr beams = (ConstBeamPtr)B.beams;
@@ -757,7 +806,7 @@ __global__ __launch_bounds__(kStepThreads, (StepShape<FAM, W>::WAVES)) void step
     int b = 0;
     for (int64_t item = blockIdx.x; item < B.n_items; item += gridDim.x) {
         while (b + 1 < B.n_beams && base[b + 1] <= item) ++b;
-        const TabGeom V{beams + b};
+        const TabGeom V{launch_args(), beams + b};
         const int64_t local = item - base[b];
         const int d = (int)(local / V.n_tiles());
         const int tile = (int)(local - (int64_t)d * V.n_tiles());
@@ -790,20 +839,13 @@ __global__ __launch_bounds__(kStepThreads, (StepShape<FAM, W>::WAVES)) void step
 // 128 x 131072 at L_end 8192 7.63 -> 5.78 ms (2.0 instead of 2.9 vector instructions per pair, 85% of
 // the issue rate); 64 x 65536 at L_end 256, where the replay's fetches one after another cost as
 // much as the widths, 137 -> 111 us.
-// four consecutive floats at any address (global loads need no more than 4-byte alignment)
-__device__ __forceinline__ float4 load_f4(const float *p) {
-    typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));
-    const v4u v = *reinterpret_cast<const v4u *>(p);
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-
 __device__ __forceinline__ float load_z(const float *xr, int r, int n_in, float mu, float inv) {
     return r < n_in ? (xr[r] - mu) * inv : 0.0f;
 }
 
 // The width scales of a row are read-only during the launch and indexed by the group's widths,
-// which every lane shares: addressed in the constant address space they load as scalar reads.
-typedef __attribute__((address_space(4))) const float *ConstFloatPtr;
+// which every lane shares: addressed in the constant address space (ConstFloatPtr) they load as
+// scalar reads.
 
 constexpr int kRing4 = 256;        // float4 slots of the ring (1024 samples)
 constexpr int kGuard4 = 18;        // mirrored slots after the ring's end
