@@ -780,16 +780,32 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
 }
 
 
+// The tile of work-group i of n.  Consecutive work-groups go to the 8 XCDs in turn; here each XCD
+// takes runs of kXcdRun consecutive tiles instead.  A tile's halo is then in its XCD's L2, and an
+// XCD's requests no longer step by 8 tiles, which with tiles of a power of two kept them on few
+// channels: tiles of 4096, 1024 x 131072, 4 levels a launch: BD-16 782 -> 669 us, IG(2) 510 -> 453;
+// 4096 x 262144 IG(1) 3507 -> 3292, candidates only 1622 -> 1495.  (Runs of 4 and 16 gain less, of
+// 1024 the same; tiles of 3072 and 6144 gain 0-3%.)
+constexpr int kXcds = 8, kXcdRun = 64;
+__device__ __forceinline__ int64_t xcd_order(int64_t i, int64_t n) {
+    constexpr int kSpan = kXcds * kXcdRun;
+    const int64_t first = i / kSpan * kSpan;
+    if (first + kSpan > n) return i;                   // the last, partial span in order
+    const int r = (int)(i - first);
+    return first + (r % kXcds) * kXcdRun + r / kXcds;
+}
+
 // One launch for one beam: work-group = (DM row, tile) of NTH threads.
 template <bool FIRST, int FAM, bool RHO, int NTH, bool W>
 __global__ __launch_bounds__(NTH, (Fam<FAM>::WAVES)) void step_kernel(const StepArgs A) {
-    // (16-byte alignment matters: with the buffer right behind st_cnt, at 8 bytes past a multiple of 16, every float4 access of a
-    // tile was misaligned, and LDS, busy 95% of the cycles, bounded every width set; now 15%:
-    // 1024 x 131072 BD-16 1000 -> 909 us, IG(2) with a sigma table 696 -> 553)
+    // (16-byte alignment matters: with the buffer right behind st_cnt, at 8 bytes past a multiple
+    // of 16, every float4 access of a tile was misaligned, and LDS, busy 95% of the cycles, bounded
+    // every width set; now 15%: 1024 x 131072 BD-16 1000 -> 909 us, IG(2) with a sigma table 696 -> 553)
     extern __shared__ __attribute__((aligned(16))) float lds[];
     __shared__ uint32_t st_cnt[3 * kStepMaxLevels];
-    const int d = blockIdx.x / A.n_tiles;
-    const int tile = blockIdx.x - d * A.n_tiles;
+    const int i = (int)xcd_order(blockIdx.x, (int64_t)A.n_dm * A.n_tiles);
+    const int d = i / A.n_tiles;
+    const int tile = i - d * A.n_tiles;
     if (d >= A.n_dm) return;
     step_tile<FIRST, FAM, RHO, NTH, W>(A, ArgGeom{launch_args()}, d, tile, lds, st_cnt);
 }
@@ -804,13 +820,15 @@ __global__ __launch_bounds__(kStepThreads, (Fam<FAM>::WAVES)) void step_kernel_b
     const ConstBeamPtr beams = (ConstBeamPtr)B.beams;
     const ConstI64Ptr base = (ConstI64Ptr)B.item_base;
     int b = 0;
-    for (int64_t item = blockIdx.x; item < B.n_items; item += gridDim.x) {
+    for (int64_t i = blockIdx.x; i < B.n_items; i += gridDim.x) {
+        // (a smaller persistent grid keeps the items in order: they must not go backwards)
+        const int64_t item = gridDim.x >= B.n_items ? xcd_order(i, B.n_items) : i;
         while (b + 1 < B.n_beams && base[b + 1] <= item) ++b;
         const TabGeom V{launch_args(), beams + b};
         const int64_t local = item - base[b];
         const int d = (int)(local / V.n_tiles());
         const int tile = (int)(local - (int64_t)d * V.n_tiles());
-        if (item != (int64_t)blockIdx.x) lds_barrier();   // the previous item is done with LDS
+        if (i != (int64_t)blockIdx.x) lds_barrier();   // the previous item is done with LDS
         step_tile<FIRST, FAM, false, kStepThreads, W>(B.s, V, d, tile, lds, st_cnt);
     }
 }
