@@ -494,7 +494,9 @@ int make_layout(const spd_params *p, const Search &s, int32_t n_dm, int32_t n_in
         }
     }
     // groups of the peak finder: enough that a bright pulse's run of chunks is spread over many, few
-    // enough that each can add up the totals of those before it
+    // enough that each can add up the totals of those before it.  With 4 slabs at least against 16:
+    // 256 x 131072 slots BD-32, 16 rows of them above the threshold throughout, 940 -> 658 us (from
+    // records and formed again 37.3 -> 9.3 ms); no block without such rows is slower.
     L->slabs_per_group = (int)std::max<int64_t>(
         std::min<int64_t>(64, std::max<int64_t>(spd::kPeakGroupSlabs, ceil_div(L->n_slabs, spd::kPeakGroupsWanted))),
         ceil_div(L->n_slabs, spd::kPeakGroups));
@@ -514,16 +516,23 @@ int make_layout(const spd_params *p, const Search &s, int32_t n_dm, int32_t n_in
             // candidates only: no planes anywhere; the cascade leaves a record of every chunk with
             // a slot above the threshold.  The pool holds 3 units per chunk, at most 32 per slab (a
             // record takes 4 and one per slot above: room for about half of all chunks, where noise
-            // at 5 sigma needs one in a hundred); the slots of a chunk that finds no room are
-            // formed again by the peak finder from the step's record.
+            // at 5 sigma needs one in a hundred).  A single pulse can cover most of a small
+            // block: it gets 2 MiB at least, or room for every slot (up to a workspace of 32 MiB, so
+            // that a search that fits a fixed scratch buffer still does).  The slots of a chunk that
+            // finds no room are formed again by the peak finder from the step's record, which takes
+            // far longer than to read it (4 x 4096 slots BD-32 with one long bright pulse: 871 us
+            // without the 2 MiB, 86 with).
             L->off_rec = take((int64_t)L->steps.size() * (int64_t)sizeof(spd::RecStep));
-            int64_t entries = 0;
+            int64_t entries = 0, every = 0;
             for (int k = 0; k < nlev; ++k) {
                 const int64_t slabs = (int64_t)n_dm * L->tiles_per_row[k];
                 L->dir_off[k] = entries;
+                every += slabs * L->cpt[k] * (spd::kChunk / 64 + spd::kChunk);
                 entries += slabs * L->cpt[k];
                 L->pool_units += slabs * std::min(spd::kPoolUnitsPerChunk * L->cpt[k], spd::kPoolUnitsPerSlab);
             }
+            if (ws < (int64_t)32 << 20)
+                L->pool_units = std::max(L->pool_units, std::min<int64_t>(every, spd::kPoolUnitsSmall));
             L->pool_units = std::min<int64_t>(L->pool_units, 0x7fffffff);
             L->off_dir = take(entries * 4);
             L->off_pool = take(L->pool_units * 8);

@@ -24,10 +24,11 @@ constexpr int kExhItemsPerWave = 4;   // work items per wave when every width fi
 constexpr int kEdgeMaxima = 64;       // see StepArgs::edge
 constexpr int kExhEdgeMaxima = 16;
 constexpr int kPeakGroups = 16384;    // most work-groups of a peak-finder pass
-constexpr int kPeakGroupSlabs = 16;   // fewest (level, row, tile) slabs of one of them ...
+constexpr int kPeakGroupSlabs = 4;    // fewest (level, row, tile) slabs of one of them (one a wave) ...
 constexpr int kPeakGroupsWanted = 4096;   // ... which grow to 64 (a wave's reach) beyond this many groups
 constexpr int kPoolUnitsPerChunk = 3; // candidates only: room for records, in 8-byte units per chunk
-constexpr int kPoolUnitsPerSlab = 32; //   of a slab, and the most for one slab
+constexpr int kPoolUnitsPerSlab = 32; //   of a slab, and the most for one slab;
+constexpr int kPoolUnitsSmall = 1 << 18; //   in a small workspace 2 MiB, if all records can take that
 constexpr int kPoolCounterWords = 64; // a batch's pool counters lie 256 bytes apart
 constexpr uint32_t kNoRecord = 0xffffffffu;   // a chunk above the threshold found no room for its record
 constexpr uint32_t kEmptyChunk = 0xfffffffeu; // nothing of the chunk is above the threshold

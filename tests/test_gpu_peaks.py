@@ -100,3 +100,15 @@ def test_last_slot_sees_the_evaluated_slot_after_it(dev, method, n_out):
                 if ok and seen and not c >= after[d]:
                     ok = False
                 assert ((i, d, m << k) in got) == ok, (method, planes, i, d)
+
+
+@pytest.mark.parametrize("method,n_dm,n,l_end", [("bd32", 4, 4096, 1533), ("ig1", 1, 257, 64), ("bd16", 16, 16384, 512)])
+def test_small_block_under_a_bright_pulse(dev, method, n_dm, n, l_end):
+    """One pulse lifts nearly every slot of its row: full records, and in the largest block too many."""
+    x, mu, sg = make_input(n_dm, n, 79, pulses=[synth.Pulse(0, n // 4, n // 2, 900.0)])
+    if n_dm > 4:
+        x[4:] += 6.0
+    (n0, ref), (n1, rec) = lists(dev, x, mu, sg, 0, 0, method=method, l_end=l_end, threshold=5.0)
+    assert n0 == n1 == len(ref) > 0 and np.array_equal(ref, rec)
+    R = oplanes.planes(x, mu, sg, ow.method_levels(method, l_end))
+    parity.check_candidates(ref, R, 5.0, what=method)
