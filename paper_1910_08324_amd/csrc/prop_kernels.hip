@@ -16,6 +16,8 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "spd.h"
 #include "spd_proposal.h"
 
@@ -33,7 +35,7 @@ constexpr int CH = SPD_PROP_CH;
 constexpr int TAPS = SPD_PROP_TAPS;
 constexpr int KW1 = 48;                 // padded k of layer 1 (5 taps x 8 channels = 40)
 constexpr int KW = TAPS * CH;           // 160
-constexpr int MAX_PART_WAVES = 1024;    // waves of the weight-gradient passes
+constexpr int MAX_PARTS = 256;          // work-groups of the backward pass (one per CU)
 
 // bfloat16: the upper half of an IEEE binary32, rounded to nearest even
 __device__ __forceinline__ uint16_t to_bf16(float f) {
@@ -42,6 +44,28 @@ __device__ __forceinline__ uint16_t to_bf16(float f) {
     return (uint16_t)(u >> 16);
 }
 __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
+
+// Work-group barrier that orders LDS only: global loads stay in flight across it (__syncthreads()
+// waits for them too, which put the latency of every row's prefetch into the row).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// two values rounded to nearest even, the first in the lower half (v_cvt_pk_bf16_f32)
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
+}
+__device__ __forceinline__ float low_bf16(uint32_t v) { return __uint_as_float(v << 16); }
+__device__ __forceinline__ float high_bf16(uint32_t v) { return __uint_as_float(v & 0xFFFF0000u); }
+// v where the half of m (an activation, never negative) is not zero, else zero
+__device__ __forceinline__ uint32_t where_bf16(uint32_t v, uint32_t m) {
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    const u16x2 on = __builtin_elementwise_min(__builtin_bit_cast(u16x2, m), u16x2{1, 1});
+    return v & __builtin_bit_cast(uint32_t, (u16x2)(u16x2{0, 0} - on));
+}
 
 __device__ __forceinline__ bf16x8 load8(const uint16_t *p) {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(p));
@@ -211,104 +235,19 @@ __global__ void prep_weights_kernel(const float *params, WB o) {
     }
 }
 
-// ---------------------------------------------------------------------------------------
-// Convolution as an MFMA GEMM.  MODE 0: out = relu(conv + bias).  MODE 1 (input gradient):
-// out = conv(dz, Wt) where prev > 0, else 0.  Work-group = half a row (128 positions), one
-// 32 x 32 output tile per wave.
-// ---------------------------------------------------------------------------------------
-struct ConvArgs {
-    const uint16_t *in;        // [rows][RP][CI]
-    const uint16_t *w;         // [32][KS 16]
-    const float *bias;         // MODE 0
-    const uint16_t *prev;      // MODE 1: activations whose ReLU masks the gradient
-    uint16_t *out;             // [rows][RP][32]
-    int32_t rows;
-};
-
-template <int CI, int MODE>
-__global__ __launch_bounds__(256) void conv_kernel(const ConvArgs A) {
-    constexpr int KS = (TAPS * CI + 15) / 16;
-    constexpr int KWC = KS * 16;
-    const int wave = threadIdx.x >> 6;
-    const int l = threadIdx.x & 63;
-    const int r = blockIdx.x >> 1;
-    const int half = blockIdx.x & 1;
-    if (r >= A.rows) return;
-    const int p0 = half * 128 + wave * 32;
-    const int h = l >> 5;
-    const int n = l & 31;
-    const uint16_t *inr = A.in + (int64_t)r * RP * CI;
-    bf16x8 wa[KS];
-#pragma unroll
-    for (int s = 0; s < KS; ++s) wa[s] = load8(A.w + n * KWC + 16 * s + 8 * h);
-    f32x16 acc;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        const bf16x8 b = load8(inr + (p0 + n) * CI + 16 * s + 8 * h);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[s], b, acc, 0, 0, 0);
-    }
-    // D[co][pos]: lane l, register i -> co = 8 (i / 4) + 4 h + i % 4, pos = p0 + n
-    const int64_t ro = ((int64_t)r * RP + p0 + n + 2) * CH;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        uint16_t hv[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int co = 8 * g + 4 * h + j;
-            float v = acc[4 * g + j];
-            if (MODE == 0) {
-                v = fmaxf(v + A.bias[co], 0.0f);
-            } else {
-                v = from_bf16(A.prev[ro + co]) > 0.0f ? v : 0.0f;
-            }
-            hv[j] = to_bf16(v);
-        }
-        *reinterpret_cast<uint2 *>(A.out + ro + 8 * g + 4 * h) =
-            make_uint2((uint32_t)hv[0] | ((uint32_t)hv[1] << 16),
-                       (uint32_t)hv[2] | ((uint32_t)hv[3] << 16));
-    }
-    // zero pads of the output row: positions 0, 1 (first half) and 258 .. 261 (second half)
-    if (half == 0 && wave == 0 && l < 16) {
-        *reinterpret_cast<uint2 *>(A.out + (int64_t)r * RP * CH + 4 * l) = make_uint2(0u, 0u);
-    }
-    if (half == 1 && wave == 3 && l < 32) {
-        *reinterpret_cast<uint2 *>(A.out + ((int64_t)r * RP + POS + 2) * CH + 4 * l) =
-            make_uint2(0u, 0u);
-    }
-}
-
-// ---------------------------------------------------------------------------------------
-// Read-out, tile logit (log-mean-exp over the tile's positions) and, when training, the loss
-// and the gradient of the read-out: one work-group per tile, thread p takes position p of
-// all 64 rows.
-// ---------------------------------------------------------------------------------------
-struct HeadArgs {
-    const uint16_t *a3;
-    const float *params;
-    const float *labels;       // null: inference
-    float *s;                  // [rows][POS] scores
-    float *logits;             // may be null
-    float *loss_t;             // [n_tiles]
-    float *hpart;              // [n_tiles][33]: d wh, d bh
-    uint16_t *dz3;             // [rows][RP][32]
-    int32_t n_tiles;
-};
-
 __device__ __forceinline__ float block_max(float v, float *sh) {
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    __syncthreads();
+    lds_barrier();
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
+    lds_barrier();
     return fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
 }
 
 __device__ __forceinline__ float block_sum(float v, float *sh) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    __syncthreads();
+    lds_barrier();
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
+    lds_barrier();
     return (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
@@ -325,151 +264,6 @@ __device__ __forceinline__ void load_act(const uint16_t *p, float a[CH]) {
     }
 }
 
-__global__ __launch_bounds__(256) void head_kernel(const HeadArgs A) {
-    __shared__ float sh[4];
-    const int t = blockIdx.x;
-    const int p = threadIdx.x;
-    if (t >= A.n_tiles) return;
-    const float *wh = A.params + SPD_PROP_OFF_WH;
-    const float bh = A.params[SPD_PROP_OFF_BH];
-    float w[CH];
-#pragma unroll
-    for (int c = 0; c < CH; ++c) w[c] = wh[c];
-    float mx = -__builtin_huge_valf();
-    for (int j = 0; j < ROWS; ++j) {
-        const int64_t row = (int64_t)t * ROWS + j;
-        float a[CH];
-        load_act(A.a3 + (row * RP + p + 2) * CH, a);
-        float s = 0.0f;
-#pragma unroll
-        for (int c = 0; c < CH; ++c) s += w[c] * a[c];
-        s += bh;
-        A.s[row * POS + p] = s;
-        mx = fmaxf(mx, s);
-    }
-    mx = block_max(mx, sh);
-    float se = 0.0f;
-    for (int j = 0; j < ROWS; ++j) se += expf(A.s[((int64_t)t * ROWS + j) * POS + p] - mx);
-    se = block_sum(se, sh);
-    const float lse = mx + logf(se);
-    const float logit = lse - 9.70406052783923f;               // log(64 * 256)
-    if (p == 0 && A.logits) A.logits[t] = logit;
-    if (!A.labels) return;
-    const float y = A.labels[t];
-    const float sig = 1.0f / (1.0f + expf(-logit));
-    const float dlogit = (sig - y) / (float)A.n_tiles;
-    if (p == 0) A.loss_t[t] = fmaxf(logit, 0.0f) + log1pf(expf(-fabsf(logit))) - y * logit;
-    float gw[CH];
-#pragma unroll
-    for (int c = 0; c < CH; ++c) gw[c] = 0.0f;
-    float gb = 0.0f;
-    for (int j = 0; j < ROWS; ++j) {
-        const int64_t row = (int64_t)t * ROWS + j;
-        const float ds = expf(A.s[row * POS + p] - lse) * dlogit;
-        float a[CH];
-        load_act(A.a3 + (row * RP + p + 2) * CH, a);
-        uint32_t packed[CH / 2];
-#pragma unroll
-        for (int c = 0; c < CH; c += 2) {
-            const float d0 = a[c] > 0.0f ? ds * w[c] : 0.0f;
-            const float d1 = a[c + 1] > 0.0f ? ds * w[c + 1] : 0.0f;
-            packed[c / 2] = (uint32_t)to_bf16(d0) | ((uint32_t)to_bf16(d1) << 16);
-            gw[c] += ds * a[c];
-            gw[c + 1] += ds * a[c + 1];
-        }
-        gb += ds;
-        uint16_t *dzp = A.dz3 + (row * RP + p + 2) * CH;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            *reinterpret_cast<uint4 *>(dzp + 8 * q) =
-                make_uint4(packed[4 * q], packed[4 * q + 1], packed[4 * q + 2], packed[4 * q + 3]);
-        if (p < RP - POS) {
-            const int pad = p < 2 ? p : POS + p;
-            uint16_t *zp = A.dz3 + (row * RP + pad) * CH;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) *reinterpret_cast<uint4 *>(zp + 8 * q) = make_uint4(0u, 0u, 0u, 0u);
-        }
-    }
-    float *hp = A.hpart + (int64_t)t * (CH + 1);
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const float v = block_sum(gw[c], sh);
-        if (p == 0) hp[c] = v;
-    }
-    const float vb = block_sum(gb, sh);
-    if (p == 0) hp[CH] = vb;
-}
-
-// ---------------------------------------------------------------------------------------
-// Weight gradient: dW[co][k] = sum over rows and positions of dz[row][p][co] in[row][p C_in + k]
-// (and the bias gradient sum of dz), as MFMA products with positions as the reduction index.
-// Each wave accumulates a fixed set of rows and writes one partial; the partials are reduced in
-// a fixed order afterwards.
-// ---------------------------------------------------------------------------------------
-struct WgArgs {
-    const uint16_t *dz;        // [rows][RP][32]
-    const uint16_t *in;        // [rows][RP][CI]
-    float *part;               // [n_waves][32 KR + 32]
-    int32_t rows;
-    int32_t n_waves;
-};
-
-template <int CI>
-__global__ __launch_bounds__(256) void wgrad_kernel(const WgArgs A) {
-    constexpr int KR = TAPS * CI;
-    constexpr int NT = (KR + 31) / 32;
-    const int wv = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int l = threadIdx.x & 63;
-    if (wv >= A.n_waves) return;
-    const int h = l >> 5;
-    const int n = l & 31;
-    f32x16 acc[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[nt][i] = 0.0f;
-    float bsum = 0.0f;
-    for (int r = wv; r < A.rows; r += A.n_waves) {
-        const uint16_t *dzr = A.dz + (int64_t)r * RP * CH;
-        const uint16_t *inr = A.in + (int64_t)r * RP * CI;
-        for (int ps = 0; ps < POS / 16; ++ps) {
-            const int pb = 16 * ps + 8 * h;
-            bf16x8 a;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const uint16_t v = dzr[(pb + j + 2) * CH + n];
-                a[j] = __builtin_bit_cast(__bf16, v);
-                bsum += from_bf16(v);
-            }
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const int k = nt * 32 + n;
-                bf16x8 b;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const uint16_t v = k < KR ? inr[(pb + j) * CI + k] : (uint16_t)0;
-                    b[j] = __builtin_bit_cast(__bf16, v);
-                }
-                acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[nt], 0, 0, 0);
-            }
-        }
-    }
-    float *pw = A.part + (int64_t)wv * (CH * KR + CH);
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const int k = nt * 32 + n;
-        if (k < KR) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int co = 8 * (i / 4) + 4 * h + (i % 4);
-                pw[co * KR + k] = acc[nt][i];
-            }
-        }
-    }
-    const float other = __shfl_down(bsum, 32);
-    if (l < 32) pw[CH * KR + l] = bsum + other;
-}
-
 // ---------------------------------------------------------------------------------------
 // Fixed-order reduction of the partials into the gradient vector, and the mean loss.
 // ---------------------------------------------------------------------------------------
@@ -477,7 +271,7 @@ struct RedArgs {
     const float *part1, *part2, *part3, *hpart, *loss_t;
     float *grads;
     float *loss;
-    int32_t n_waves, n_tiles;
+    int32_t n_parts, n_tiles;
 };
 
 // Sum of src[w * stride] over w in [w0, w1), in increasing w, with 8 loads in flight.
@@ -507,7 +301,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(const RedArgs A) {
     const int c = threadIdx.x / RED_PARAMS;
     const int i = blockIdx.x * RED_PARAMS + j;
     const float *src = nullptr;
-    int stride = 0, idx = 0, count = A.n_waves;
+    int stride = 0, idx = 0;
     if (i < SPD_PROP_OFF_B1) {
         src = A.part1; stride = CH * 40 + CH; idx = i;
     } else if (i < SPD_PROP_OFF_W2) {
@@ -521,10 +315,10 @@ __global__ __launch_bounds__(256) void reduce_kernel(const RedArgs A) {
     } else if (i < SPD_PROP_OFF_WH) {
         src = A.part3; stride = CH * KW + CH; idx = CH * KW + (i - SPD_PROP_OFF_B3);
     } else if (i <= SPD_PROP_OFF_BH) {
-        src = A.hpart; stride = CH + 1; idx = i - SPD_PROP_OFF_WH; count = A.n_tiles;
+        src = A.hpart; stride = CH + 1; idx = i - SPD_PROP_OFF_WH;
     }
-    const int w0 = (int)((int64_t)c * count / RED_CHUNKS);
-    const int w1 = (int)((int64_t)(c + 1) * count / RED_CHUNKS);
+    const int w0 = (int)((int64_t)c * A.n_parts / RED_CHUNKS);
+    const int w1 = (int)((int64_t)(c + 1) * A.n_parts / RED_CHUNKS);
     part[c][j] = src ? ordered_sum(src + idx, stride, w0, w1) : 0.0f;
     __syncthreads();
     if (c == 0 && i < SPD_PROP_NPARAMS) {
@@ -700,12 +494,11 @@ __device__ __forceinline__ void conv_lds(const uint16_t *in, const LayerW<CI> &W
         for (int g = 0; g < 4; ++g) {
             const float4 bv = *reinterpret_cast<const float4 *>(bias + 8 * g + 4 * h);
             const float bb[4] = {bv.x, bv.y, bv.z, bv.w};
-            uint16_t hv[4];
+            float v[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) hv[j] = to_bf16(fmaxf(acc[t][4 * g + j] + bb[j], 0.0f));
+            for (int j = 0; j < 4; ++j) v[j] = fmaxf(acc[t][4 * g + j] + bb[j], 0.0f);
             *reinterpret_cast<uint2 *>(out + act_at(po, g) + 4 * h) =
-                make_uint2((uint32_t)hv[0] | ((uint32_t)hv[1] << 16),
-                           (uint32_t)hv[2] | ((uint32_t)hv[3] << 16));
+                make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
         }
     }
 }
@@ -754,14 +547,14 @@ __global__ __launch_bounds__(256) void infer_kernel(const InferArgs A) {
     for (int r = blockIdx.x; r < A.rows; r += gridDim.x) {
         reinterpret_cast<uint4 *>(f)[tid] = fp0;
         if (tid + 256 < NF) reinterpret_cast<uint4 *>(f)[tid + 256] = fp1;
-        __syncthreads();
+        lds_barrier();
         if (r + (int)gridDim.x < A.rows) fetch(r + gridDim.x);
         conv_lds<FCH>(f, W1, bias, a, wave, l);
-        __syncthreads();
+        lds_barrier();
         conv_lds<CH>(a, W2, bias + CH, b, wave, l);
-        __syncthreads();
+        lds_barrier();
         conv_lds<CH>(b, W3, bias + 2 * CH, a, wave, l);
-        __syncthreads();
+        lds_barrier();
         // read-out of position tid, then the row's max and sum of exp(s - max)
         float act[CH];
 #pragma unroll
@@ -784,27 +577,404 @@ __global__ __launch_bounds__(256) void infer_kernel(const InferArgs A) {
             A.row_max[r] = mx;
             A.row_sum[r] = se;
         }
-        __syncthreads();                    // f and a are rewritten for the next row
+        lds_barrier();                    // f and a are rewritten for the next row
     }
 }
 
-__global__ void infer_combine_kernel(const float *row_max, const float *row_sum, int32_t n_tiles,
-                                     float *logits) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n_tiles) return;
-    float M = -__builtin_huge_valf();
-    for (int j = 0; j < ROWS; ++j) M = fmaxf(M, row_max[t * ROWS + j]);
-    float Z = 0.0f;
-    for (int j = 0; j < ROWS; ++j) Z += row_sum[t * ROWS + j] * expf(row_max[t * ROWS + j] - M);
-    logits[t] = M + logf(Z) - 9.70406052783923f;
+// A tile's logit from its rows' maxima and sums and, training (labels not null), its loss and what
+// the backward pass needs of it.  One wave per tile, a lane per row.
+struct CombineArgs {
+    const float *row_max, *row_sum;
+    const float *labels;
+    float *logits;             // may be null when training
+    float *loss_t, *lse, *dlogit;
+    int32_t n_tiles;
+};
+
+__global__ __launch_bounds__(256) void combine_kernel(const CombineArgs A) {
+    static_assert(ROWS == 64, "a lane per row");
+    const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (t >= A.n_tiles) return;
+    const float m = A.row_max[(int64_t)t * ROWS + lane];
+    float M = m;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
+    float Z = A.row_sum[(int64_t)t * ROWS + lane] * expf(m - M);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) Z += __shfl_xor(Z, o);
+    if (lane) return;
+    const float lse = M + logf(Z);
+    const float logit = lse - 9.70406052783923f;               // log(64 * 256)
+    if (A.logits) A.logits[t] = logit;
+    if (!A.labels) return;
+    const float y = A.labels[t];
+    const float sig = 1.0f / (1.0f + expf(-logit));
+    A.lse[t] = lse;
+    A.dlogit[t] = (sig - y) / (float)A.n_tiles;
+    A.loss_t[t] = fmaxf(logit, 0.0f) + log1pf(expf(-fabsf(logit))) - y * logit;
+}
+
+// ---------------------------------------------------------------------------------------
+// Training: forward and backward of a row in one work-group, with every activation and gradient in
+// LDS.  The forward launch (infer_kernel) gives each tile's logit; this one forms the row's
+// activations again (bitwise the same) and runs the backward pass on them, so that neither
+// activations nor gradients go through HBM.
+//
+// An MFMA tile of a convolution is formed twice from the same operands, once with the weights and
+// once with the positions as rows: a lane then holds four consecutive channels of one position
+// (stored channel-last, the layout the next convolution reads 16 bytes at a time) and four
+// consecutive positions of one channel (stored channel by channel, the layout in which the weight
+// gradient, whose reduction index is the position, reads 16 bytes at a time).  The five taps of a
+// channel are five shifts of 12 consecutive positions, so two 16-byte loads and eight register
+// funnel shifts feed five MFMAs.
+//
+// One work-group of 8 waves per CU (144 KB of LDS), persistent over rows.  A wave convolves its 32
+// positions; the weight gradients of a row, 12 MFMA tiles summed over 256 positions, are 24
+// half-tiles, three per wave, so that their accumulators stay in registers
+// with two waves per SIMD.  The weights of layer 3 and of the input gradients come from the cache
+// for each row.  At the end the halves are added in order and the work-group writes one partial.
+// Measured, 16,384 rows (256 tiles): 0.91 ms, and 0.14 ms for the forward launch, where separate
+// launches per convolution, weight gradient and read-out, bound by 3.3 GB of activations and by
+// 2-byte gathers, took 2.35 ms together.  Bound by latency: a row's MFMAs need 6.4k of its 30k cycles.
+// ---------------------------------------------------------------------------------------
+struct BwdArgs {
+    const uint16_t *feat;
+    WB wb;
+    const float *params;
+    const float *lse;          // [n_tiles] log of the sum of exp(s) over the tile
+    const float *dlogit;       // [n_tiles] gradient of the loss at the tile's logit
+    float *part1, *part2, *part3, *hpart;   // [gridDim.x] partial gradients
+    int32_t rows;
+};
+
+constexpr int T_LD = 264;                      // positions per channel row: 16-byte rows, 4 banks apart
+constexpr int T_ELEMS = CH * T_LD;
+constexpr int ACT_ELEMS = RP * ACT_LD;
+constexpr int BWD_ELEMS = RP * FCH + 3 * ACT_ELEMS + 4 * T_ELEMS + FCH * T_LD;
+constexpr int P1 = CH * TAPS * FCH + CH, P2 = CH * KW + CH;   // floats of a partial of layer 1; 2, 3
+static_assert((P1 + 2 * P2) * 4 <= BWD_ELEMS * 2, "the waves' sums fit where the activations were");
+
+// both forms of one 32-position tile at p0: n (weights as rows), t (positions as rows)
+template <int CI, bool N>
+__device__ __forceinline__ void conv_both(const uint16_t *in, const LayerW<CI> &W, int p0, int l,
+                                          f32x16 &an, f32x16 &at) {
+    const int h = l >> 5, n = l & 31;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        if (N) an[i] = 0.0f;
+        at[i] = 0.0f;
+    }
+#pragma unroll
+    for (int s = 0; s < LayerW<CI>::KS; ++s) {
+        const bf16x8 b = load8(CI == CH ? in + act_at(p0 + n + (s >> 1), 2 * (s & 1) + h)
+                                        : in + (p0 + n) * CI + 16 * s + 8 * h);
+        if (N) an = __builtin_amdgcn_mfma_f32_32x32x16_bf16(W.w[s], b, an, 0, 0, 0);
+        at = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, W.w[s], at, 0, 0, 0);
+    }
+}
+
+constexpr int kBwdThreads = 512;
+
+// acc[co][column] += sum over 128 positions from p of dz[pos][co] in[pos + T][channel], the channel
+// (lane n's column) chosen by the row `in` points to.  T < 0 (layer 1, columns 8 t + ci): lane n takes
+// tap n / 8 of channel n % 8.
+template <int T>
+__device__ __forceinline__ void wgrad_half(const uint16_t *dz, const uint16_t *in, f32x16 &acc, int n) {
+    const bool second = (n >> 4) & 1;
+    const uint32_t odd = ((n >> 3) & 1) * 16;
+#pragma unroll
+    for (int ps = 0; ps < 8; ++ps) {
+        const bf16x8 a = load8(dz + 16 * ps);
+        const uint4 lo = *reinterpret_cast<const uint4 *>(in + 16 * ps);
+        uint4 w = lo;
+        if constexpr (T != 0) {
+            const uint4 hi = *reinterpret_cast<const uint4 *>(in + 16 * ps + 8);
+            const uint32_t d[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+            if constexpr (T < 0) {
+                uint32_t e[5];
+#pragma unroll
+                for (int i = 0; i < 5; ++i) {
+                    const uint32_t x = d[i + 1], y = d[i];   // (values: a choice of elements would put d in memory)
+                    e[i] = second ? x : y;
+                }
+                w = make_uint4(__builtin_amdgcn_alignbit(e[1], e[0], odd), __builtin_amdgcn_alignbit(e[2], e[1], odd),
+                               __builtin_amdgcn_alignbit(e[3], e[2], odd), __builtin_amdgcn_alignbit(e[4], e[3], odd));
+            } else {
+                constexpr int o = T >> 1;
+                w = (T & 1) ? make_uint4(__builtin_amdgcn_alignbit(d[o + 1], d[o], 16),
+                                         __builtin_amdgcn_alignbit(d[o + 2], d[o + 1], 16),
+                                         __builtin_amdgcn_alignbit(d[o + 3], d[o + 2], 16),
+                                         __builtin_amdgcn_alignbit(d[o + 4], d[o + 3], 16))
+                            : make_uint4(d[o], d[o + 1], d[o + 2], d[o + 3]);
+            }
+        }
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, w), acc, 0, 0, 0);
+    }
+}
+
+__global__ __launch_bounds__(kBwdThreads, 2) void backward_kernel(const BwdArgs A) {
+    constexpr int NF = RP * FCH / 8;
+    static_assert(NF <= kBwdThreads, "a row's features take one piece per thread");
+    __shared__ __attribute__((aligned(16))) uint16_t smem[BWD_ELEMS];
+    __shared__ __attribute__((aligned(16))) float bias[4 * CH];   // the layers' biases, the read-out's weights
+    __shared__ __attribute__((aligned(16))) float dsv[POS];
+    __shared__ float red[8 + CH];
+    uint16_t *f = smem;
+    uint16_t *c1 = f + RP * FCH, *c2 = c1 + ACT_ELEMS, *c3 = c2 + ACT_ELEMS;      // channel-last
+    uint16_t *t1 = c3 + ACT_ELEMS, *t2 = t1 + T_ELEMS, *z1 = t2 + T_ELEMS, *z2 = z1 + T_ELEMS;
+    uint16_t *ft = z2 + T_ELEMS;                                                  // channel by channel
+    uint16_t *z3 = c1;                          // (layer 1's activations are not read after layer 2)
+    static_assert(T_ELEMS <= ACT_ELEMS, "z3 fits in c1");
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l = tid & 63;
+    const int h = l >> 5, n = l & 31;
+    const int p0 = wave * 32;                   // this wave's positions
+    LayerW<FCH> W1;
+    LayerW<CH> W2;
+    W1.load(A.wb.w1, l);
+    W2.load(A.wb.w2, l);
+    if (tid < 4 * CH) {
+        const int j = tid / CH, c = tid - j * CH;
+        const int off = j == 0 ? SPD_PROP_OFF_B1 : j == 1 ? SPD_PROP_OFF_B2 : j == 2 ? SPD_PROP_OFF_B3 : SPD_PROP_OFF_WH;
+        bias[tid] = A.params[off + c];
+    }
+    // the pads (positions 0, 1, 258 ..) are zero and, but for c1's, never written
+    for (int i = tid; i < BWD_ELEMS / 8; i += kBwdThreads)
+        reinterpret_cast<uint4 *>(smem)[i] = make_uint4(0u, 0u, 0u, 0u);
+    static_assert(BWD_ELEMS % 8 == 0, "cleared in 16-byte pieces");
+    const float *wh = bias + 3 * CH;
+    const float bh = A.params[SPD_PROP_OFF_BH];
+    const float whn = A.params[SPD_PROP_OFF_WH + n];
+    f32x16 acc[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[q][i] = 0.0f;
+    float b1 = 0.0f, b2 = 0.0f, b3 = 0.0f, gw = 0.0f, gb = 0.0f;
+    uint4 fp = make_uint4(0u, 0u, 0u, 0u);
+    auto fetch = [&](int r) {
+        if (tid < NF) fp = reinterpret_cast<const uint4 *>(A.feat + (int64_t)r * RP * FCH)[tid];
+    };
+    // the layer's activations of the wave's tile in both layouts; packed: the second one's values
+    auto relu_both = [&](auto store_t, const f32x16 &an, const f32x16 &at, const float *bs, uint16_t *c,
+                         uint16_t *t, uint32_t packed[8]) {
+        const float bn = bs[n];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 bv = *reinterpret_cast<const float4 *>(bs + 8 * g + 4 * h);
+            const float bb[4] = {bv.x, bv.y, bv.z, bv.w};
+            float u[4], w[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                u[j] = fmaxf(an[4 * g + j] + bb[j], 0.0f);
+                w[j] = fmaxf(at[4 * g + j] + bn, 0.0f);
+            }
+            *reinterpret_cast<uint2 *>(c + act_at(p0 + n + 2, g) + 4 * h) =
+                make_uint2(pack_bf16(u[0], u[1]), pack_bf16(u[2], u[3]));
+            packed[2 * g] = pack_bf16(w[0], w[1]);
+            packed[2 * g + 1] = pack_bf16(w[2], w[3]);
+            if constexpr (decltype(store_t)::value) {
+                uint32_t *q = reinterpret_cast<uint32_t *>(t + n * T_LD + p0 + 8 * g + 4 * h + 2);
+                q[0] = packed[2 * g];
+                q[1] = packed[2 * g + 1];
+            }
+        }
+    };
+    // the input gradient of the wave's tile, masked by the layer's activations prev (same layout),
+    // to z; returns the lane's sum of the rounded values
+    auto grad_t = [&](const f32x16 &at, const uint16_t *prev, uint16_t *z) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const uint32_t *q = reinterpret_cast<const uint32_t *>(prev + n * T_LD + p0 + 8 * g + 4 * h + 2);
+            const uint32_t u0 = where_bf16(pack_bf16(at[4 * g], at[4 * g + 1]), q[0]);
+            const uint32_t u1 = where_bf16(pack_bf16(at[4 * g + 2], at[4 * g + 3]), q[1]);
+            sum += low_bf16(u0);
+            sum += high_bf16(u0);
+            sum += low_bf16(u1);
+            sum += high_bf16(u1);
+            *reinterpret_cast<uint2 *>(z + n * T_LD + p0 + 8 * g + 4 * h) = make_uint2(u0, u1);
+        }
+        return sum;
+    };
+    fetch(blockIdx.x);
+    lds_barrier();
+    for (int r = blockIdx.x; r < A.rows; r += gridDim.x) {
+        const float lse = A.lse[r / ROWS], dlogit = A.dlogit[r / ROWS];
+        if (tid < NF) {
+            reinterpret_cast<uint4 *>(f)[tid] = fp;
+            const uint32_t w[3] = {fp.x, fp.y, fp.z};
+#pragma unroll
+            for (int c = 0; c < 5; ++c) ft[c * T_LD + tid] = (uint16_t)(w[c / 2] >> (16 * (c & 1)));
+        } else if (tid < NF + 6 * (ACT_LD / 8)) {
+            // c1's pads, where z3 was
+            const int i = tid - NF, p = i / (ACT_LD / 8), q = i - p * (ACT_LD / 8);
+            *reinterpret_cast<uint4 *>(c1 + (p < 2 ? p : POS + p) * ACT_LD + 8 * q) = make_uint4(0u, 0u, 0u, 0u);
+        }
+        lds_barrier();
+        if (r + (int)gridDim.x < A.rows) fetch(r + gridDim.x);
+        uint32_t a3[8];
+        f32x16 an, at;
+        LayerW<CH> V;                           // weights loaded for each row, ahead of their use
+        auto load_w = [&](const uint16_t *p) {
+            asm volatile("" : "+s"(p));         // (here, not once for all rows)
+            V.load(p, l);
+        };
+        load_w(A.wb.w3);
+        // ---- forward
+        conv_both<FCH, true>(f, W1, p0, l, an, at);
+        relu_both(std::true_type{}, an, at, bias, c1, t1, a3);
+        lds_barrier();
+        conv_both<CH, true>(c1, W2, p0, l, an, at);
+        relu_both(std::true_type{}, an, at, bias + CH, c2, t2, a3);
+        lds_barrier();
+        conv_both<CH, true>(c2, V, p0, l, an, at);
+        relu_both(std::false_type{}, an, at, bias + 2 * CH, c3, t1, a3);
+        load_w(A.wb.w3t);
+        lds_barrier();
+        // ---- read-out of position tid % 256 and half of the gradient at layer 3's output, in place
+        {
+            const int pos = tid & (POS - 1);
+            const bool upper = tid >= POS;      // (uniform over the wave)
+            float a[CH];
+            uint16_t *p = c3 + act_at(pos + 2, 0);
+            load_act(p, a);
+            float s = 0.0f;
+#pragma unroll
+            for (int c = 0; c < CH; c += 4) {
+                const float4 w = *reinterpret_cast<const float4 *>(wh + c);
+                s += w.x * a[c];
+                s += w.y * a[c + 1];
+                s += w.z * a[c + 2];
+                s += w.w * a[c + 3];
+            }
+            s += bh;
+            const float ds = expf(s - lse) * dlogit;
+            if (!upper) {
+                gb += ds;
+                dsv[pos] = ds;
+            }
+            lds_barrier();                    // both halves have read the position's activations
+            // channels 16 upper .. + 15
+            const float *w0 = wh + (upper ? CH / 2 : 0);
+            uint4 *out = reinterpret_cast<uint4 *>(p + (upper ? CH / 2 : 0));
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                uint32_t v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float2 w = *reinterpret_cast<const float2 *>(w0 + 8 * q + 2 * i);
+                    const float x = a[8 * q + 2 * i], x1 = a[8 * q + 2 * i + 1];
+                    const float y = a[CH / 2 + 8 * q + 2 * i], y1 = a[CH / 2 + 8 * q + 2 * i + 1];
+                    const float dx = ds * w.x, dy = ds * w.y;
+                    v[i] = pack_bf16((upper ? y : x) > 0.0f ? dx : 0.0f, (upper ? y1 : x1) > 0.0f ? dy : 0.0f);
+                }
+                out[q] = make_uint4(v[0], v[1], v[2], v[3]);
+            }
+        }
+        // (dsv is complete since the barrier above)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 d4 = *reinterpret_cast<const float4 *>(dsv + p0 + 8 * g + 4 * h);
+            const float ds[4] = {d4.x, d4.y, d4.z, d4.w};
+            uint32_t u[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const float x = low_bf16(a3[2 * g + i]), y = high_bf16(a3[2 * g + i]);
+                gw += ds[2 * i] * x;
+                gw += ds[2 * i + 1] * y;
+                u[i] = pack_bf16(x > 0.0f ? ds[2 * i] * whn : 0.0f, y > 0.0f ? ds[2 * i + 1] * whn : 0.0f);
+                b3 += low_bf16(u[i]);
+                b3 += high_bf16(u[i]);
+            }
+            *reinterpret_cast<uint2 *>(z3 + n * T_LD + p0 + 8 * g + 4 * h) = make_uint2(u[0], u[1]);
+        }
+        lds_barrier();
+        // ---- the gradient at layer 2's output, over its activations c2
+        conv_both<CH, true>(c3, V, p0, l, an, at);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            uint2 *q = reinterpret_cast<uint2 *>(c2 + act_at(p0 + n + 2, g) + 4 * h);
+            const uint2 m = *q;
+            *q = make_uint2(where_bf16(pack_bf16(an[4 * g], an[4 * g + 1]), m.x),
+                            where_bf16(pack_bf16(an[4 * g + 2], an[4 * g + 3]), m.y));
+        }
+        b2 += grad_t(at, t2, z2);
+        load_w(A.wb.w2t);
+        lds_barrier();
+        // ---- the gradient at layer 1's output (none at the features)
+        conv_both<CH, false>(c2, V, p0, l, an, at);
+        b1 += grad_t(at, t1, z1);
+        lds_barrier();
+        // ---- weights: half-tile 3 wave + q: tiles 0..4 layer 3, 5..9 layer 2, 10, 11 layer 1
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const int job = (3 * wave + q) >> 1, p = ((3 * wave + q) & 1) * 128 + 8 * h;
+            const uint16_t *dz = (job < 5 ? z3 : job < 10 ? z2 : z1) + n * T_LD + p;
+            const uint16_t *in = (job < 5 ? t2 : job < 10 ? t1 : ft) + (job < 10 ? n : (n & 7)) * T_LD + p;
+            switch (job < 10 ? (job < 5 ? job : job - 5) : job - 5) {
+                case 0: wgrad_half<0>(dz, in, acc[q], n); break;
+                case 1: wgrad_half<1>(dz, in, acc[q], n); break;
+                case 2: wgrad_half<2>(dz, in, acc[q], n); break;
+                case 3: wgrad_half<3>(dz, in, acc[q], n); break;
+                case 5: wgrad_half<-1>(dz, in, acc[q], n); break;
+                default: wgrad_half<4>(dz, in, acc[q], n); break;
+            }
+        }
+        lds_barrier();                        // everything is rewritten for the next row
+    }
+    // ---- the two halves of each tile and the waves' sums in order, then one partial per work-group
+    float *sum1 = reinterpret_cast<float *>(smem), *sum2 = sum1 + P1, *sum3 = sum2 + P2;
+    for (int half = 0; half < 2; ++half) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            if (((3 * wave + q) & 1) != half) continue;
+            const int job = (3 * wave + q) >> 1;
+            const int k = job < 5 ? job * CH + n : job < 10 ? (job - 5) * CH + n : (job - 10) * CH + n;
+            const int ld = job < 10 ? KW : TAPS * FCH;
+            float *p = (job < 5 ? sum3 : job < 10 ? sum2 : sum1) + k;
+            if (job == 11 && n >= 8) continue;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                float *at = p + (8 * (i / 4) + 4 * h + (i % 4)) * ld;
+                *at = half == 0 ? acc[q][i] : *at + acc[q][i];
+            }
+        }
+        __syncthreads();
+    }
+    const float o1 = b1 + __shfl_down(b1, 32), o2 = b2 + __shfl_down(b2, 32);
+    const float o3 = b3 + __shfl_down(b3, 32), ow = gw + __shfl_down(gw, 32);
+    for (int w = 0; w < kBwdThreads / 64; ++w) {
+        if (wave == w && l < CH) {
+            auto add = [&](float *p, float v) { *p = w == 0 ? v : *p + v; };
+            add(sum1 + CH * TAPS * FCH + l, o1);
+            add(sum2 + CH * KW + l, o2);
+            add(sum3 + CH * KW + l, o3);
+            add(red + 8 + l, ow);
+        }
+        __syncthreads();
+    }
+    for (int o = 32; o > 0; o >>= 1) gb += __shfl_xor(gb, o);
+    if (l == 0) red[wave] = gb;
+    __syncthreads();
+    const int64_t b = blockIdx.x;
+    for (int i = tid; i < P1; i += kBwdThreads) A.part1[b * P1 + i] = sum1[i];
+    for (int i = tid; i < P2; i += kBwdThreads) {
+        A.part2[b * P2 + i] = sum2[i];
+        A.part3[b * P2 + i] = sum3[i];
+    }
+    if (tid < CH) A.hpart[b * (CH + 1) + tid] = red[8 + tid];
+    if (tid == 0) A.hpart[b * (CH + 1) + CH] = (red[0] + red[1]) + (red[2] + red[3]);   // (positions: waves 0..3)
 }
 
 // ---------------------------------------------------------------------------------------
 // Workspace layout for n_tiles tiles.
 // ---------------------------------------------------------------------------------------
 struct Layout {
-    int64_t wb, a1, a2, a3, dz3, dz2, dz1, s, loss_t, hpart, part1, part2, part3, total;
-    int n_waves;
+    int64_t wb, row_max, row_sum, lse, dlogit, loss_t, hpart, part1, part2, part3, total;
+    int n_parts;
 };
 
 inline int64_t up256(int64_t v) { return (v + 255) & ~(int64_t)255; }
@@ -812,31 +982,26 @@ inline int64_t up256(int64_t v) { return (v + 255) & ~(int64_t)255; }
 Layout layout(int32_t n_tiles) {
     Layout L;
     const int64_t rows = (int64_t)n_tiles * ROWS;
-    const int64_t act = rows * RP * CH * 2;
-    L.n_waves = (int)(rows < MAX_PART_WAVES ? rows : MAX_PART_WAVES);
+    L.n_parts = (int)(rows < MAX_PARTS ? rows : MAX_PARTS);
     int64_t o = 0;
     auto take = [&](int64_t b) { const int64_t at = o; o += up256(b); return at; };
     L.wb = take((int64_t)(CH * KW1 + 4 * CH * KW) * 2);
-    L.a1 = take(act);
-    L.a2 = take(act);
-    L.a3 = take(act);
-    L.dz3 = take(act);
-    L.dz2 = take(act);
-    L.dz1 = take(act);
-    L.s = take(rows * POS * 4);
+    L.row_max = take(rows * 4);
+    L.row_sum = take(rows * 4);
+    L.lse = take((int64_t)n_tiles * 4);
+    L.dlogit = take((int64_t)n_tiles * 4);
     L.loss_t = take((int64_t)n_tiles * 4);
-    L.hpart = take((int64_t)n_tiles * (CH + 1) * 4);
-    L.part1 = take((int64_t)L.n_waves * (CH * 40 + CH) * 4);
-    L.part2 = take((int64_t)L.n_waves * (CH * KW + CH) * 4);
-    L.part3 = take((int64_t)L.n_waves * (CH * KW + CH) * 4);
+    L.hpart = take((int64_t)L.n_parts * (CH + 1) * 4);
+    L.part1 = take((int64_t)L.n_parts * P1 * 4);
+    L.part2 = take((int64_t)L.n_parts * P2 * 4);
+    L.part3 = take((int64_t)L.n_parts * P2 * 4);
     L.total = o;
     return L;
 }
 
 struct Bufs {
     WB wb;
-    uint16_t *a1, *a2, *a3, *dz3, *dz2, *dz1;
-    float *s, *loss_t, *hpart, *part1, *part2, *part3;
+    float *row_max, *row_sum, *lse, *dlogit, *loss_t, *hpart, *part1, *part2, *part3;
 };
 
 Bufs bufs(const Layout &L, void *ws) {
@@ -848,18 +1013,16 @@ Bufs bufs(const Layout &L, void *ws) {
     B.wb.w3 = B.wb.w2 + CH * KW;
     B.wb.w2t = B.wb.w3 + CH * KW;
     B.wb.w3t = B.wb.w2t + CH * KW;
-    B.a1 = reinterpret_cast<uint16_t *>(b + L.a1);
-    B.a2 = reinterpret_cast<uint16_t *>(b + L.a2);
-    B.a3 = reinterpret_cast<uint16_t *>(b + L.a3);
-    B.dz3 = reinterpret_cast<uint16_t *>(b + L.dz3);
-    B.dz2 = reinterpret_cast<uint16_t *>(b + L.dz2);
-    B.dz1 = reinterpret_cast<uint16_t *>(b + L.dz1);
-    B.s = reinterpret_cast<float *>(b + L.s);
-    B.loss_t = reinterpret_cast<float *>(b + L.loss_t);
-    B.hpart = reinterpret_cast<float *>(b + L.hpart);
-    B.part1 = reinterpret_cast<float *>(b + L.part1);
-    B.part2 = reinterpret_cast<float *>(b + L.part2);
-    B.part3 = reinterpret_cast<float *>(b + L.part3);
+    auto at = [&](int64_t o) { return reinterpret_cast<float *>(b + o); };
+    B.row_max = at(L.row_max);
+    B.row_sum = at(L.row_sum);
+    B.lse = at(L.lse);
+    B.dlogit = at(L.dlogit);
+    B.loss_t = at(L.loss_t);
+    B.hpart = at(L.hpart);
+    B.part1 = at(L.part1);
+    B.part2 = at(L.part2);
+    B.part3 = at(L.part3);
     return B;
 }
 
@@ -885,41 +1048,28 @@ int check_ws(int32_t n_tiles, const void *ws, int64_t ws_bytes, Layout *L) {
     return SPD_OK;
 }
 
-// forward through the three layers and the read-out (labels: training mode)
+// Tile logits (labels not null: and losses and what the backward pass needs).
 int run_forward(const float *params, const uint16_t *feat, int32_t n_tiles, const float *labels,
-                float *logits, const Layout &L, const Bufs &B, hipStream_t st) {
+                float *logits, const Bufs &B, hipStream_t st) {
     const int rows = n_tiles * ROWS;
     SPDP_LAUNCH(prep_weights_kernel, dim3((CH * KW + 255) / 256), dim3(256), 0, st, params, B.wb);
-    ConvArgs c;
-    memset(&c, 0, sizeof(c));
-    c.rows = rows;
-    c.in = feat;
-    c.w = B.wb.w1;
-    c.bias = params + SPD_PROP_OFF_B1;
-    c.out = B.a1;
-    SPDP_LAUNCH((conv_kernel<FCH, 0>), dim3(2 * rows), dim3(256), 0, st, c);
-    c.in = B.a1;
-    c.w = B.wb.w2;
-    c.bias = params + SPD_PROP_OFF_B2;
-    c.out = B.a2;
-    SPDP_LAUNCH((conv_kernel<CH, 0>), dim3(2 * rows), dim3(256), 0, st, c);
-    c.in = B.a2;
-    c.w = B.wb.w3;
-    c.bias = params + SPD_PROP_OFF_B3;
-    c.out = B.a3;
-    SPDP_LAUNCH((conv_kernel<CH, 0>), dim3(2 * rows), dim3(256), 0, st, c);
-    HeadArgs h;
-    h.a3 = B.a3;
-    h.params = params;
-    h.labels = labels;
-    h.s = B.s;
-    h.logits = logits;
-    h.loss_t = B.loss_t;
-    h.hpart = B.hpart;
-    h.dz3 = B.dz3;
-    h.n_tiles = n_tiles;
-    SPDP_LAUNCH(head_kernel, dim3(n_tiles), dim3(256), 0, st, h);
-    (void)L;
+    InferArgs a;
+    a.feat = feat;
+    a.wb = B.wb;
+    a.params = params;
+    a.row_max = B.row_max;
+    a.row_sum = B.row_sum;
+    a.rows = rows;
+    // persistent grid: as many work-groups as the device keeps resident at once, at most one per row
+    int dev = 0, cus = 0, per_cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, infer_kernel, 256, 0) != hipSuccess)
+        return fail(hipGetLastError());
+    const int grid = std::max(1, std::min(rows, cus * std::max(1, per_cu)));
+    SPDP_LAUNCH(infer_kernel, dim3(grid), dim3(256), 0, st, a);
+    const CombineArgs c{B.row_max, B.row_sum, labels, logits, B.loss_t, B.lse, B.dlogit, n_tiles};
+    SPDP_LAUNCH(combine_kernel, dim3((n_tiles + 3) / 4), dim3(256), 0, st, c);
     return SPD_OK;
 }
 
@@ -960,28 +1110,8 @@ int spd_prop_forward(const float *params, const uint16_t *feat, int32_t n_tiles,
     if (st != SPD_OK) return st;
     if (!params || !feat || !logits) return SPD_EINVAL;
     if ((uintptr_t)feat & 15) return SPD_EALIGN;
-    const Bufs B = bufs(L, workspace);
-    hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    const int rows = n_tiles * ROWS;
-    SPDP_LAUNCH(prep_weights_kernel, dim3((CH * KW + 255) / 256), dim3(256), 0, s, params, B.wb);
-    InferArgs a;
-    a.feat = feat;
-    a.wb = B.wb;
-    a.params = params;
-    a.row_max = B.s;
-    a.row_sum = B.s + rows;
-    a.rows = rows;
-    // persistent grid: as many work-groups as the device keeps resident at once, at most one per row
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, infer_kernel, 256, 0) != hipSuccess)
-        return fail(hipGetLastError());
-    const int grid = std::max(1, std::min(rows, cus * std::max(1, per_cu)));
-    SPDP_LAUNCH(infer_kernel, dim3(grid), dim3(256), 0, s, a);
-    SPDP_LAUNCH(infer_combine_kernel, dim3((n_tiles + 255) / 256), dim3(256), 0, s, a.row_max,
-                a.row_sum, n_tiles, logits);
-    return SPD_OK;
+    return run_forward(params, feat, n_tiles, nullptr, logits, bufs(L, workspace),
+                       static_cast<hipStream_t>(hip_stream));
 }
 
 int spd_prop_backward(const float *params, const uint16_t *feat, const float *labels,
@@ -993,42 +1123,11 @@ int spd_prop_backward(const float *params, const uint16_t *feat, const float *la
     if (!params || !feat || !labels || !grads || !loss) return SPD_EINVAL;
     const Bufs B = bufs(L, workspace);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    st = run_forward(params, feat, n_tiles, labels, logits, L, B, s);
+    st = run_forward(params, feat, n_tiles, labels, logits, B, s);
     if (st != SPD_OK) return st;
-    const int rows = n_tiles * ROWS;
-    const int wg_blocks = (L.n_waves + 3) / 4;
-    WgArgs w;
-    w.rows = rows;
-    w.n_waves = L.n_waves;
-    // layer 3: weights, then the gradient at layer 2's output
-    w.dz = B.dz3;
-    w.in = B.a2;
-    w.part = B.part3;
-    SPDP_LAUNCH(wgrad_kernel<CH>, dim3(wg_blocks), dim3(256), 0, s, w);
-    ConvArgs c;
-    memset(&c, 0, sizeof(c));
-    c.rows = rows;
-    c.in = B.dz3;
-    c.w = B.wb.w3t;
-    c.prev = B.a2;
-    c.out = B.dz2;
-    SPDP_LAUNCH((conv_kernel<CH, 1>), dim3(2 * rows), dim3(256), 0, s, c);
-    // layer 2
-    w.dz = B.dz2;
-    w.in = B.a1;
-    w.part = B.part2;
-    SPDP_LAUNCH(wgrad_kernel<CH>, dim3(wg_blocks), dim3(256), 0, s, w);
-    c.in = B.dz2;
-    c.w = B.wb.w2t;
-    c.prev = B.a1;
-    c.out = B.dz1;
-    SPDP_LAUNCH((conv_kernel<CH, 1>), dim3(2 * rows), dim3(256), 0, s, c);
-    // layer 1 (no gradient at the features)
-    w.dz = B.dz1;
-    w.in = feat;
-    w.part = B.part1;
-    SPDP_LAUNCH(wgrad_kernel<FCH>, dim3(wg_blocks), dim3(256), 0, s, w);
-    RedArgs r{B.part1, B.part2, B.part3, B.hpart, B.loss_t, grads, loss, L.n_waves, n_tiles};
+    const BwdArgs w{feat, B.wb, params, B.lse, B.dlogit, B.part1, B.part2, B.part3, B.hpart, n_tiles * ROWS};
+    SPDP_LAUNCH(backward_kernel, dim3(L.n_parts), dim3(kBwdThreads), 0, s, w);
+    const RedArgs r{B.part1, B.part2, B.part3, B.hpart, B.loss_t, grads, loss, L.n_parts, n_tiles};
     SPDP_LAUNCH(reduce_kernel, dim3((SPD_PROP_NPARAMS + RED_PARAMS - 1) / RED_PARAMS), dim3(256), 0, s, r);
     return SPD_OK;
 }

@@ -257,3 +257,26 @@ def test_gated_search_pipeline(P):
                            64, 4096)
     torch.cuda.synchronize()
     assert np.array_equal(gs.out.candidates_host(), ref.candidates_host())
+
+
+@pytest.mark.parametrize("tiles", [1, 3, 5])
+def test_backward_row_counts(P, tiles):
+    """Fewer rows than work-groups, a few more (some take one row, some two), and several each, in a
+    network with room for more tiles; a second call gives the same bits."""
+    _, feat = make_batch(P, tiles, seed=31)
+    net = oracle_net(31)
+    y = np.arange(tiles) % 2.0
+    N = P.Network(packed(P, net), max_tiles=tiles + 3)
+    lab = torch.tensor(y, dtype=torch.float32, device="cuda")
+    N.backward(feat, lab, tiles)
+    g, loss = N.grads.cpu().numpy().copy(), float(N.loss.item())
+    N.backward(feat, lab, tiles)
+    assert np.array_equal(g.view(np.uint32), N.grads.cpu().numpy().view(np.uint32)) and loss == float(N.loss.item())
+    F = bf16_host(feat)[:, 2:258, :5]
+    exact_loss, exact = op.backward(F, y, net)
+    B = op.error_budget(F, y, net)
+    assert abs(loss - exact_loss) <= B["loss"]
+    got = P.unpack(g)
+    for n in op.Net.NAMES:
+        err = np.abs(np.asarray(got[n], np.float64) - np.asarray(getattr(exact, n), np.float64))
+        assert np.all(err <= B[n]), n
