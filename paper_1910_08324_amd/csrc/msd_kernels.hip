@@ -4,8 +4,7 @@
 //
 // A read of the row serves every level at once.  The row streams through in tiles of 1024
 // samples, one float4 per thread; inside a tile the decimated values of levels 1..8 are formed
-// in registers (levels 1, 2 within a thread, 3..8 by pairwise sums across lanes, moved by DPP
-// row shifts and readlane rather than through LDS).  Levels 0..5 are accumulated as they stream
+// in registers (levels 1, 2 within a thread, 3..8 by a butterfly across lanes, DPP and row swaps).  Levels 0..5 are accumulated as they stream
 // by: per level, each thread keeps a count and the sums of (value - shift) and of its square,
 // the shift being the level's current mean estimate; levels 0..2, which every lane serves, count
 // their kept values per wave and total their lanes' sums directly, levels 3..5 merge per-lane
@@ -25,6 +24,12 @@
 // pass counts and stopping decisions, are those of full reads; only the order of the FP64 sums
 // differs (and is fixed).  When the band is no longer covered, or a list overflowed its room, the
 // pass reads the row again and lists anew around its own estimate (0.8 of its limit).
+//
+// What bounds it is the issue of the first read's FP64 and list instructions and the latency of
+// its stores.  One loop per kind of read (one loop for all moved 250 scalar registers per tile at
+// its joins), the first without the tests that always hold, two tiles' loads in flight, no barrier
+// in a tile (levels 9.. are formed after the read) and no pass through LDS: 4096 x 262144 samples,
+// 14 levels, 3.56 -> 2.15 ms (2.0 TB/s of samples), the results bit for bit the same.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -228,9 +233,9 @@ __device__ __forceinline__ void take(Acc &a, const Level &L, bool first, bool va
     a.s2 = fma(e, e, a.s2);
 }
 
-// v of lane l + 2^(K-3), for the lanes that are multiples of 2^(K-2) (other lanes get values
-// that are never used).  Within a row of 16 lanes a DPP row shift moves the value in registers;
-// across rows the two (or one) values needed are read out with readlane.
+// Level K from level K-1: a butterfly, after which every lane of a run of 2^(K-2) holds the sum of the
+// run's two halves (a + b == b + a, so the lanes agree).  Within a row of 16 lanes DPP moves the
+// other half's value: it is the same in every lane of that half, so mirrors serve as exchanges.
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
     const long long b = __double_as_longlong(v);
@@ -239,35 +244,30 @@ __device__ __forceinline__ double dpp_f64(double v) {
     return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
-__device__ __forceinline__ double readlane_f64(double v, int l) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)b, l);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-
 template <int K>
-__device__ __forceinline__ double from_lane_above(double v, int lane) {
-    constexpr int span = 1 << (K - 3);
-    if constexpr (span <= 8) {
-        return dpp_f64<0x100 + span>(v);                // row_shl:span (lane l reads l + span)
-    } else if constexpr (span == 16) {
-        const double a = readlane_f64(v, 16), b = readlane_f64(v, 48);
-        return lane < 32 ? a : b;
-    } else {
-        return readlane_f64(v, 32);
+__device__ __forceinline__ double level_step(double v) {
+    if constexpr (K == 3) return v + dpp_f64<0xb1>(v);       // quad_perm 1 0 3 2
+    else if constexpr (K == 4) return v + dpp_f64<0x4e>(v);  // quad_perm 2 3 0 1
+    else if constexpr (K == 5) return v + dpp_f64<0x141>(v); // row_half_mirror
+    else if constexpr (K == 6) return v + dpp_f64<0x140>(v); // row_mirror
+    else {
+        // rows 0 | 1 and 2 | 3 (level 7), lanes 0..31 | 32..63 (level 8)
+        const long long b = __double_as_longlong(v);
+        const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+        double x[2];
+        if constexpr (K == 7) {
+            const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+            const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) x[i] = __longlong_as_double(((long long)h[i] << 32) | l[i]);
+        } else {
+            const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+            const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) x[i] = __longlong_as_double(((long long)h[i] << 32) | l[i]);
+        }
+        return x[0] + x[1];
     }
-}
-
-// one step of the cross-lane cascade: level K from pairs of level K-1 values; each holder lane
-// (a multiple of 2^(K-2)) parks its value in the wave's slot of level K (NaN past the data;
-// in a FULL tile every value of levels 3..8 lies inside it)
-template <int K, bool FULL>
-__device__ __forceinline__ void level_step(double &v, double *slots, int lane, int s, int n) {
-    constexpr int kSlotK = K == 3 ? 0 : K == 4 ? 32 : K == 5 ? 48 : K == 6 ? 56 : K == 7 ? 60 : 62;
-    v = v + from_lane_above<K>(v, lane);
-    if ((lane & ((2 << (K - 3)) - 1)) == 0)
-        slots[kSlotK + (lane >> (K - 2))] = (FULL || s + (1 << K) <= n) ? v : __builtin_nan("");
 }
 
 // how many of the lanes below this one have their bit set in b (mbcnt)
@@ -276,13 +276,18 @@ __device__ __forceinline__ int count_below(uint64_t b) {
                                           __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
 }
 
+// entry i of a list (fewer than n / 64 + 16 values, so its byte offset fits 32 bits)
+__device__ __forceinline__ void list_put(double *list, int i, double v) {
+    *reinterpret_cast<double *>(reinterpret_cast<char *>(list) + (uint32_t)i * 8u) = v;
+}
+
 // append the values of the lanes whose `far` is set to the wave's list, in lane order after the
 // values appended before (a full list still counts them, which marks the overflow)
 __device__ __forceinline__ void list_append(bool far, double v, double *list, int &cnt, int room) {
     const uint64_t b = __ballot(far);
     if (b) {
         const int i = cnt + count_below(b);
-        if (far && i < room) list[i] = v;
+        if (far && i < room) list_put(list, i, v);
         cnt += __popcll(b);
     }
 }
@@ -290,16 +295,17 @@ __device__ __forceinline__ void list_append(bool far, double v, double *list, in
 // take for a level every lane of the wave serves: the count of kept values is kept per wave
 // (a ballot's population count, on the scalar unit) instead of per lane.  LIST: values beyond
 // the list threshold also go to the wave's list of the level.
-template <bool LIST>
-__device__ __forceinline__ void take_w(Acc &a, uint32_t &nw, const Level &L, bool first,
-                                       bool valid, double v, double *list, int &cnt, int room) {
+// FIRST: every valid value is kept.  FULL: every value is valid.
+template <bool FULL, bool FIRST, bool LIST>
+__device__ __forceinline__ void take_w(Acc &a, uint32_t &nw, const Level &L, bool valid, double v,
+                                       double *list, int &cnt, int room) {
     const double d = v - L.shift;
-    const bool ok = valid && (first || fabs(d) <= L.lim);
+    const bool ok = (FULL || valid) && (FIRST || fabs(d) <= L.lim);
     const double e = ok ? d : 0.0;           // (d may be NaN for a value past the data)
-    nw += (uint32_t)__popcll(__ballot(ok));
+    nw += FULL && FIRST ? 64u : (uint32_t)__popcll(__ballot(ok));
     a.s1 += e;
     a.s2 = fma(e, e, a.s2);
-    if (LIST) list_append(valid && !(fabs(d) <= L.lt), v, list, cnt, room);   // lc == shift
+    if (LIST) list_append((FULL || valid) && !(fabs(d) <= L.lt), v, list, cnt, room);   // lc == shift
 }
 
 // statistics of a level all of whose values share one shift: the work-group's totals of the
@@ -322,8 +328,6 @@ __device__ __forceinline__ Part wave_counted_part(const Acc &a, uint32_t nw, dou
 __global__ __launch_bounds__(kThreads, 4) void msd_kernel(const MsdArgs A) {
     __shared__ Part sh[4];
     __shared__ Level lv[SPD_MAX_LEVELS];
-    __shared__ double t8[4];                   // level-8 value of each wave in the current tile
-    __shared__ double slot_buf[4][64];         // per wave: this tile's level 3..8 values
     __shared__ int list_cnt[kWaves][kListLevels];  // values each wave listed in the last full read
     __shared__ int any_active, pass_mode;
     const int d = blockIdx.x;
@@ -337,13 +341,10 @@ __global__ __launch_bounds__(kThreads, 4) void msd_kernel(const MsdArgs A) {
     const float *xr = A.x + (int64_t)d * A.ld;
     double *wr = A.ws + (int64_t)d * A.ws_row;
     const int n_tiles = (n + kTile - 1) / kTile;
-    const bool vec = (((uintptr_t)xr) & 15) == 0;
-    // a tile gives each wave 32 + 16 + 8 + 4 + 2 + 1 values of levels 3..8: lanes 0..31 take
-    // level 3, 32..47 level 4, 48..55 level 5, 56..59 level 6, 60..61 level 7, 62 level 8
-    const int my_k = lane < 32 ? 3 : lane < 48 ? 4 : lane < 56 ? 5 : lane < 60 ? 6 : lane < 62 ? 7
-                                                                                   : lane < 63 ? 8 : kRegLevels;
-    double *slots = slot_buf[wave];
-    slots[63] = __builtin_nan("");               // lane 63 has no value
+    // a tile gives each wave 32 + 16 + 8 + 4 + 2 + 1 values of levels 3..8.  After step k a run of
+    // 2^(k-2) lanes holds one value of level k; the run's middle lane takes it: the odd lanes level 3,
+    // lanes 2, 6, 10.. level 4, ..., lane 32 level 8 (lane 0 none)
+    const int my_k = lane ? 3 + __builtin_ctz(lane) : kRegLevels;
     // this wave's list of level k
     auto list_of = [&](int k) { return wr + list_offset(n, k) + (int64_t)wave * list_room(n, k); };
 
@@ -418,133 +419,139 @@ __global__ __launch_bounds__(kThreads, 4) void msd_kernel(const MsdArgs A) {
         const bool onm = my_k < klist && (first || Lm.active);   // lanes of levels 3..5
         const bool arr = pass == 0 && my_k >= kArrFirst && my_k < K;   // lanes of 6..8
 
-        auto fetch = [&](int tile, float4 &f) {
-            const int s = tile * kTile + 4 * tid;
-            if (vec && s + 3 < n) {
-                // streamed once per full read: keep the cache for the lists being written
-                typedef float v4f __attribute__((ext_vector_type(4)));
-                const v4f t = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(xr + s));
-                f = make_float4(t.x, t.y, t.z, t.w);
-            } else {
-                f.x = s + 0 < n ? xr[s + 0] : 0.0f;
-                f.y = s + 1 < n ? xr[s + 1] : 0.0f;
-                f.z = s + 2 < n ? xr[s + 2] : 0.0f;
-                f.w = s + 3 < n ? xr[s + 3] : 0.0f;
-            }
+        auto fetch = [&](int tile) {                   // a tile all inside the data
+            // streamed once per full read: keep the cache for the lists being written
+            typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
+            return __builtin_nontemporal_load(reinterpret_cast<const v4f *>(xr + tile * kTile + 4 * tid));
         };
-        // the pre-estimate reads tiles (i n_tiles) / n_probe, a full read every tile
-        auto tile_at = [&](int i) { return probe ? (int)(((int64_t)i * n_tiles) / n_probe) : i; };
-        const int n_read = probe ? n_probe : n_tiles;
-        float4 nxt = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (read_row) fetch(tile_at(0), nxt);
+        // where this lane's value of levels 6..8 of the next tile goes (first pass)
+        double *arr_at = wr;
+        if (arr) arr_at += arr_offset(n, my_k) + wave * (256 >> my_k) + (lane >> (my_k - 2));
         // one tile; FULL: every sample of the tile is inside the data (all tiles but the last),
-        // so the per-value validity tests fold away; LIST: the values beyond the band are listed
-        auto tile_body = [&](auto full_tag, auto list_tag, int tile, float4 cur) {
+        // so the per-value validity tests fold away; FIRST: every valid value is kept; LIST: the
+        // values beyond the band are listed
+        auto tile_body = [&](auto full_tag, auto first_tag, auto list_tag, int tile, float c0, float c1,
+                             float c2, float c3) {
             constexpr bool FULL = decltype(full_tag)::value;
+            constexpr bool FIRST = decltype(first_tag)::value;
             constexpr bool LIST = decltype(list_tag)::value;
-            const int s = tile * kTile + 4 * tid;                // first sample of this thread
-            const double v0[4] = {(double)cur.x, (double)cur.y, (double)cur.z, (double)cur.w};
-            if (on0)
+            const int s = FULL ? 0 : tile * kTile + 4 * tid;     // first sample of this thread
+            const double v0[4] = {(double)c0, (double)c1, (double)c2, (double)c3};
+            if (FIRST || on0)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    take_w<LIST>(a0, n0w, L0, first, FULL || s + q < n, v0[q], list_of(0), lc_[0],
-                                 list_room(n, 0));
+                    take_w<FULL, FIRST, LIST>(a0, n0w, L0, FULL || s + q < n, v0[q], list_of(0), lc_[0],
+                                              list_room(n, 0));
             // levels 1, 2 within the thread
             const double v1a = v0[0] + v0[1], v1b = v0[2] + v0[3];
             if (on1) {
-                take_w<LIST>(a1, n1w, L1, first, FULL || s + 2 <= n, v1a, list_of(1), lc_[1],
-                             list_room(n, 1));
-                take_w<LIST>(a1, n1w, L1, first, FULL || s + 4 <= n, v1b, list_of(1), lc_[1],
-                             list_room(n, 1));
+                take_w<FULL, FIRST, LIST>(a1, n1w, L1, FULL || s + 2 <= n, v1a, list_of(1), lc_[1],
+                                          list_room(n, 1));
+                take_w<FULL, FIRST, LIST>(a1, n1w, L1, FULL || s + 4 <= n, v1b, list_of(1), lc_[1],
+                                          list_room(n, 1));
             }
             double v = v1a + v1b;
             if (on2)
-                take_w<LIST>(a2, n2w, L2, first, FULL || s + 4 <= n, v, list_of(2), lc_[2],
-                             list_room(n, 2));
-            // levels 3..8 across lanes: after step k, lane l holds the value of level k that starts
-            // at its own samples when l is a multiple of 2^(k-2); holders park their values in the
-            // wave's 64 slots (level k from slot 64 - 2^(9-k), one per holder, NaN past the data), and
-            // every lane then takes the one value of its own level in its slot
-            level_step<3, FULL>(v, slots, lane, s, n);
-            level_step<4, FULL>(v, slots, lane, s, n);
-            level_step<5, FULL>(v, slots, lane, s, n);
-            level_step<6, FULL>(v, slots, lane, s, n);
-            level_step<7, FULL>(v, slots, lane, s, n);
-            level_step<8, FULL>(v, slots, lane, s, n);
-            bool far = false;
-            double mv = 0.0;
-            if (onm) {
-                mv = slots[lane];                                // written by this wave above
-                const bool valid = FULL || !__builtin_isnan(mv);
-                take(am, Lm, first, valid, mv);
-                if (LIST) far = valid && !(fabs(mv - Lm.shift) <= Lm.lt);   // lc == shift
+                take_w<FULL, FIRST, LIST>(a2, n2w, L2, FULL || s + 4 <= n, v, list_of(2), lc_[2],
+                                          list_room(n, 2));
+            // levels 3..8 across lanes; every lane keeps the one value of its own level
+            double mv = v = level_step<3>(v);
+            v = level_step<4>(v);
+            mv = my_k == 4 ? v : mv;
+            v = level_step<5>(v);
+            mv = my_k == 5 ? v : mv;
+            if (FIRST && LIST) {                               // levels 6.. are stored once
+                v = level_step<6>(v);
+                mv = my_k == 6 ? v : mv;
+                v = level_step<7>(v);
+                mv = my_k == 7 ? v : mv;
+                v = level_step<8>(v);
+                mv = my_k == 8 ? v : mv;
             }
-            if (arr) {
+            bool far = false;
+            if (onm) {
+                bool valid = true;
+                if (!FULL) {
+                    const int run = 1 << (my_k - 2);           // lanes that share the value
+                    const int s0 = tile * kTile + 4 * (tid & -run);
+                    valid = s0 + (1 << my_k) <= n && !__builtin_isnan(mv);
+                }
+                const double dm = mv - Lm.shift;
+                const bool ok = valid && (FIRST || fabs(dm) <= Lm.lim);
+                const double e = ok ? dm : 0.0;
+                am.n += ok ? 1 : 0;
+                am.s1 += e;
+                am.s2 = fma(e, e, am.s2);
+                if (LIST) far = valid && !(fabs(dm) <= Lm.lt);   // lc == shift
+            }
+            if (FIRST && LIST && arr) {
                 // the first pass stores levels 6..8 whole: level k's values of a tile in wave,
-                // then lane order (lanes 56.., 60.., 62 hold levels 6, 7, 8)
-                const int k = my_k;
-                const int lane0 = k == 6 ? 56 : k == 7 ? 60 : 62;
-                const int64_t i = (int64_t)tile * (kTile >> k) + wave * (256 >> k) + (lane - lane0);
-                if (i < (n >> k)) wr[arr_offset(n, k) + i] = slots[lane];
+                // then lane order
+                bool in = true;
+                if (!FULL) {
+                    const int64_t i = (int64_t)tile * (kTile >> my_k) + wave * (256 >> my_k) + (lane >> (my_k - 2));
+                    in = i < (n >> my_k);
+                }
+                if (in) *arr_at = mv;
+                arr_at += kTile >> my_k;
             }
             if (LIST) {
-                // each level's lanes form one run of the wave: append level by level (the
-                // ballot and the counts stay in uniform control flow)
+                // append level by level (the ballot and the counts stay in uniform control flow)
                 const uint64_t b = __ballot(far);
                 if (b) {
 #pragma unroll
                     for (int k = 3; k < kListLevels; ++k) {
-                        const uint64_t run = k == 3 ? 0xffffffffull : k == 4 ? 0xffffull << 32
-                                                                    : 0xffull << 48;
-                        const uint64_t bk = b & run;
+                        const uint64_t lanes = k == 3 ? 0xaaaaaaaaaaaaaaaaull : k == 4 ? 0x4444444444444444ull
+                                                                              : 0x1010101010101010ull;
+                        const uint64_t bk = b & lanes;
                         if (bk) {
                             const int i = lc_[k] + count_below(bk);
-                            if (far && my_k == k && i < list_room(n, k)) list_of(k)[i] = mv;
+                            if (far && my_k == k && i < list_room(n, k)) list_put(list_of(k), i, mv);
                             lc_[k] += __popcll(bk);
                         }
                     }
                 }
             }
-            // levels 9 and 10 (and the level-10 values the higher levels are built from): the
-            // first pass writes them to the workspace
-            if (pass == 0 && K > 9) {
-                if (lane == 0) t8[wave] = v;
-                __syncthreads();
-                if (tid == 0) {
-                    const int64_t i9 = (int64_t)tile * 2;
-                    const double a9 = t8[0] + t8[1], b9 = t8[2] + t8[3];
-                    double *w9 = wr + arr_offset(n, 9);
-                    const int64_t n9 = n >> 9;
-                    if (i9 < n9) w9[i9] = a9;
-                    if (i9 + 1 < n9) w9[i9 + 1] = b9;
-                    if (K > 10 && tile < (n >> 10)) w9[n9 + tile] = a9 + b9;
+        };
+        // the pre-estimate reads tiles (i n_tiles) / n_probe, a full read every tile.  The loads of
+        // two tiles are in flight while one is taken.
+        auto read_tiles = [&](auto first_tag, auto list_tag) {
+            constexpr bool kAll = decltype(list_tag)::value;
+            const int n_read = kAll ? n_tiles : n_probe;
+            auto tile_at = [&](int i) { return kAll ? i : (int)(((int64_t)i * n_tiles) / n_probe); };
+            const int n_full = n_read - (tile_at(n_read - 1) * kTile + kTile > n ? 1 : 0);
+            if (n_full > 0) {
+                auto f0 = fetch(tile_at(0));
+                auto f1 = fetch(tile_at(min(1, n_full - 1)));
+                for (int i = 0; i < n_full; i += 2) {
+                    const auto c0 = f0;
+                    f0 = fetch(tile_at(min(i + 2, n_full - 1)));
+                    tile_body(std::true_type{}, first_tag, list_tag, tile_at(i), c0.x, c0.y, c0.z, c0.w);
+                    if (i + 1 >= n_full) break;
+                    const auto c1 = f1;
+                    f1 = fetch(tile_at(min(i + 3, n_full - 1)));
+                    tile_body(std::true_type{}, first_tag, list_tag, tile_at(i + 1), c1.x, c1.y, c1.z, c1.w);
                 }
-                __syncthreads();
+            }
+            if (n_full < n_read) {
+                const int tile = tile_at(n_full), s = tile * kTile + 4 * tid;
+                tile_body(std::false_type{}, first_tag, list_tag, tile, s + 0 < n ? xr[s + 0] : 0.0f,
+                          s + 1 < n ? xr[s + 1] : 0.0f, s + 2 < n ? xr[s + 2] : 0.0f,
+                          s + 3 < n ? xr[s + 3] : 0.0f);
             }
         };
-        for (int i = 0; read_row && i < n_read; ++i) {
-            const int tile = tile_at(i);
-            const float4 cur = nxt;
-            if (i + 1 < n_read) fetch(tile_at(i + 1), nxt);      // in flight while this tile computes
-            const bool full = (tile + 1) * kTile <= n;            // uniform over the work-group
-            if (build) {
-                if (full)
-                    tile_body(std::true_type{}, std::true_type{}, tile, cur);
-                else
-                    tile_body(std::false_type{}, std::true_type{}, tile, cur);
-            } else {
-                if (full)
-                    tile_body(std::true_type{}, std::false_type{}, tile, cur);
-                else
-                    tile_body(std::false_type{}, std::false_type{}, tile, cur);
-            }
+        if (read_row) {
+            if (probe) read_tiles(std::true_type{}, std::false_type{});
+            else if (first) read_tiles(std::true_type{}, std::true_type{});
+            else read_tiles(std::false_type{}, std::true_type{});
         }
         if (build && lane == 0)
             for (int k = 0; k < klist; ++k) list_cnt[wave][k] = lc_[k];
-        if (pass == 0 && K > 11) {
-            // levels 11.. from pairs of the level below, all in the workspace
-            int64_t off_prev = arr_offset(n, 10), off = arr_offset(n, 11);
-            for (int k = 11; k < K; ++k) {
+        if (pass == 0 && K > 9) {
+            // levels 9.. from pairs of the level below, all in the workspace
+            __syncthreads();
+            int64_t off_prev = arr_offset(n, 8), off = arr_offset(n, 9);
+            for (int k = 9; k < K; ++k) {
                 const int64_t cnt = (int64_t)(n >> k);
                 for (int64_t i = tid; i < cnt; i += kThreads) wr[off + i] = wr[off_prev + 2 * i] + wr[off_prev + 2 * i + 1];
                 off_prev = off;
@@ -742,7 +749,7 @@ int spd_msd_workspace(int32_t n_dm, int32_t n_in, int32_t levels, int64_t *bytes
     if (!bytes || n_dm < 1 || n_in < 2 || n_in > INT32_MAX - 4096 || levels < 1 ||
         levels > SPD_MAX_LEVELS || ((int64_t)n_in >> (levels - 1)) < 2)
         return SPD_EINVAL;
-    // levels 9.. of every row (fewer than n_in / 256 values) and the lists of levels 0..8
+    // levels 6.. of every row (fewer than n_in / 32 values) and the lists of levels 0..5
     *bytes = (int64_t)n_dm * spdm::ws_row_doubles(n_in) * 8 + 256;
     return SPD_OK;
 }

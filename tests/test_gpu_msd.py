@@ -146,3 +146,21 @@ def test_sigma_table_of_white_noise_is_neutral(M):
         torch.cuda.synchronize()
         for la, lb in zip(a.planes_host(), b.planes_host()):
             assert np.allclose(la["Y"], lb["Y"], rtol=1e-6, atol=1e-6)
+
+
+@pytest.mark.parametrize("n", [2, 5, 1023, 1024, 1025, 2048, 3071, 3072, 8192, 9 * 1024 + 2, 10 * 1024 + 515])
+def test_msd_tile_counts(M, n):
+    """One tile or less, odd and even numbers of whole tiles, a last tile of any length, every level the
+    row has, and rows that start at any 4-byte address (the row's view starts at sample 3 of a longer one)."""
+    levels = min(int(np.log2(n)), 13)
+    x = rows_for_lists(max(n, 8), 11)[:, :n]
+    wide = np.zeros((x.shape[0], n + 9), np.float32)
+    wide[:, 3:3 + n] = x
+    for t in (torch.from_numpy(np.ascontiguousarray(x)).cuda(), torch.from_numpy(wide).cuda()[:, 3:3 + n]):
+        mean, sigma, rho, lsd, passes = (a.cpu().numpy() for a in M.msd(t, levels, tau=3.0, max_iter=10,
+                                                                          with_passes=True))
+        for d in range(x.shape[0]):
+            r = om.msd_row(x[d], levels, tau=3.0, max_iter=10)
+            assert passes[d] == max(r["passes"]), d
+            assert mean[d] == pytest.approx(r["mean"][0], rel=1e-6, abs=1e-7), d
+            assert np.allclose(lsd[d], r["sd"], rtol=1e-6, atol=1e-12), d
