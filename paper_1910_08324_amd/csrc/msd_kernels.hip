@@ -25,11 +25,12 @@
 // differs (and is fixed).  When the band is no longer covered, or a list overflowed its room, the
 // pass reads the row again and lists anew around its own estimate (0.8 of its limit).
 //
-// What bounds it is the issue of the first read's FP64 and list instructions and the latency of
-// its stores.  One loop per kind of read (one loop for all moved 250 scalar registers per tile at
-// its joins), the first without the tests that always hold, two tiles' loads in flight, no barrier
-// in a tile (levels 9.. are formed after the read) and no pass through LDS: 4096 x 262144 samples,
-// 14 levels, 3.56 -> 2.15 ms (2.0 TB/s of samples), the results bit for bit the same.
+// What bounds it is the issue of the first read's FP64 and list instructions, then the reductions
+// and list passes of a row, one after another.  One loop per kind of read (one loop for all moved
+// 250 scalar registers per tile at its joins), the first without the tests that always hold, two
+// tiles' loads in flight, no barrier in a tile (levels 9.. are formed after the read), no pass
+// through LDS for the levels, and the listed values gathered there: 4096 x 262144 samples,
+// 14 levels, 3.49 -> 1.89 ms (2.3 TB/s of samples), the results bit for bit the same.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -276,19 +277,30 @@ __device__ __forceinline__ int count_below(uint64_t b) {
                                           __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
 }
 
-// entry i of a list (fewer than n / 64 + 16 values, so its byte offset fits 32 bits)
-__device__ __forceinline__ void list_put(double *list, int i, double v) {
-    *reinterpret_cast<double *>(reinterpret_cast<char *>(list) + (uint32_t)i * 8u) = v;
+// A wave's list of one level being built: entry i waits in LDS at stage[i & 127], and each run of 64
+// goes to memory in one store.  (A store per append kept the tile loop waiting: the compiler has to
+// assume that a conditional store was not made when it counts what may be outstanding before a
+// load, so a wait for the load became a wait for the store: 4096 x 262144 samples 2.15 ms, so 1.89.)
+constexpr int kStage = 128;
+
+__device__ __forceinline__ void list_flush(const double *stage, double *list, int first, int end, int lane) {
+    __builtin_amdgcn_wave_barrier();         // the wave's LDS accesses are performed in order
+    const int i = first + lane;
+    const double v = stage[i & (kStage - 1)];
+    if (i < end) list[i] = v;
+    __builtin_amdgcn_wave_barrier();
 }
 
 // append the values of the lanes whose `far` is set to the wave's list, in lane order after the
 // values appended before (a full list still counts them, which marks the overflow)
-__device__ __forceinline__ void list_append(bool far, double v, double *list, int &cnt, int room) {
-    const uint64_t b = __ballot(far);
+__device__ __forceinline__ void list_append(bool far, uint64_t b, double v, double *stage, double *list,
+                                            int &cnt, int room, int lane) {
     if (b) {
         const int i = cnt + count_below(b);
-        if (far && i < room) list_put(list, i, v);
+        if (far) stage[i & (kStage - 1)] = v;
+        const int was = cnt;
         cnt += __popcll(b);
+        if ((cnt ^ was) & 64) list_flush(stage, list, was & ~63, min(room, (was & ~63) + 64), lane);
     }
 }
 
@@ -298,14 +310,17 @@ __device__ __forceinline__ void list_append(bool far, double v, double *list, in
 // FIRST: every valid value is kept.  FULL: every value is valid.
 template <bool FULL, bool FIRST, bool LIST>
 __device__ __forceinline__ void take_w(Acc &a, uint32_t &nw, const Level &L, bool valid, double v,
-                                       double *list, int &cnt, int room) {
+                                       double *stage, double *list, int &cnt, int room, int lane) {
     const double d = v - L.shift;
     const bool ok = (FULL || valid) && (FIRST || fabs(d) <= L.lim);
     const double e = ok ? d : 0.0;           // (d may be NaN for a value past the data)
     nw += FULL && FIRST ? 64u : (uint32_t)__popcll(__ballot(ok));
     a.s1 += e;
     a.s2 = fma(e, e, a.s2);
-    if (LIST) list_append((FULL || valid) && !(fabs(d) <= L.lt), v, list, cnt, room);   // lc == shift
+    if (LIST) {
+        const bool far = (FULL || valid) && !(fabs(d) <= L.lt);   // lc == shift
+        list_append(far, __ballot(far), v, stage, list, cnt, room, lane);
+    }
 }
 
 // statistics of a level all of whose values share one shift: the work-group's totals of the
@@ -328,6 +343,7 @@ __device__ __forceinline__ Part wave_counted_part(const Acc &a, uint32_t nw, dou
 __global__ __launch_bounds__(kThreads, 4) void msd_kernel(const MsdArgs A) {
     __shared__ Part sh[4];
     __shared__ Level lv[SPD_MAX_LEVELS];
+    __shared__ double stages[kWaves][kListLevels][kStage];
     __shared__ int list_cnt[kWaves][kListLevels];  // values each wave listed in the last full read
     __shared__ int any_active, pass_mode;
     const int d = blockIdx.x;
@@ -345,6 +361,7 @@ __global__ __launch_bounds__(kThreads, 4) void msd_kernel(const MsdArgs A) {
     // 2^(k-2) lanes holds one value of level k; the run's middle lane takes it: the odd lanes level 3,
     // lanes 2, 6, 10.. level 4, ..., lane 32 level 8 (lane 0 none)
     const int my_k = lane ? 3 + __builtin_ctz(lane) : kRegLevels;
+    double (*stage)[kStage] = stages[wave];
     // this wave's list of level k
     auto list_of = [&](int k) { return wr + list_offset(n, k) + (int64_t)wave * list_room(n, k); };
 
@@ -424,14 +441,20 @@ __global__ __launch_bounds__(kThreads, 4) void msd_kernel(const MsdArgs A) {
             typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
             return __builtin_nontemporal_load(reinterpret_cast<const v4f *>(xr + tile * kTile + 4 * tid));
         };
-        // where this lane's value of levels 6..8 of the next tile goes (first pass)
-        double *arr_at = wr;
-        if (arr) arr_at += arr_offset(n, my_k) + wave * (256 >> my_k) + (lane >> (my_k - 2));
+        // where this lane's value of levels 6..8 of the next tile goes (first pass): a byte offset in
+        // the row's values, past their end for the lanes that have none, whose stores are dropped
+        // (every lane stores, so that the loads' waits can count the store)
+        const auto arr_buf = __builtin_amdgcn_make_buffer_rsrc(wr, 0, (int)(((n >> 5) + 8) * 8), 0x00027000);
+        uint32_t arr_at = 0x80000000u, arr_step = 0;
+        if (arr) {
+            arr_at = (uint32_t)(arr_offset(n, my_k) + wave * (256 >> my_k) + (lane >> (my_k - 2))) * 8u;
+            arr_step = (uint32_t)(kTile >> my_k) * 8u;
+        }
         // one tile; FULL: every sample of the tile is inside the data (all tiles but the last),
         // so the per-value validity tests fold away; FIRST: every valid value is kept; LIST: the
         // values beyond the band are listed
         auto tile_body = [&](auto full_tag, auto first_tag, auto list_tag, int tile, float c0, float c1,
-                             float c2, float c3) {
+                             float c2, float c3) __attribute__((always_inline)) {
             constexpr bool FULL = decltype(full_tag)::value;
             constexpr bool FIRST = decltype(first_tag)::value;
             constexpr bool LIST = decltype(list_tag)::value;
@@ -440,20 +463,20 @@ __global__ __launch_bounds__(kThreads, 4) void msd_kernel(const MsdArgs A) {
             if (FIRST || on0)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    take_w<FULL, FIRST, LIST>(a0, n0w, L0, FULL || s + q < n, v0[q], list_of(0), lc_[0],
-                                              list_room(n, 0));
+                    take_w<FULL, FIRST, LIST>(a0, n0w, L0, FULL || s + q < n, v0[q], stage[0], list_of(0), lc_[0],
+                                              list_room(n, 0), lane);
             // levels 1, 2 within the thread
             const double v1a = v0[0] + v0[1], v1b = v0[2] + v0[3];
             if (on1) {
-                take_w<FULL, FIRST, LIST>(a1, n1w, L1, FULL || s + 2 <= n, v1a, list_of(1), lc_[1],
-                                          list_room(n, 1));
-                take_w<FULL, FIRST, LIST>(a1, n1w, L1, FULL || s + 4 <= n, v1b, list_of(1), lc_[1],
-                                          list_room(n, 1));
+                take_w<FULL, FIRST, LIST>(a1, n1w, L1, FULL || s + 2 <= n, v1a, stage[1], list_of(1), lc_[1],
+                                          list_room(n, 1), lane);
+                take_w<FULL, FIRST, LIST>(a1, n1w, L1, FULL || s + 4 <= n, v1b, stage[1], list_of(1), lc_[1],
+                                          list_room(n, 1), lane);
             }
             double v = v1a + v1b;
             if (on2)
-                take_w<FULL, FIRST, LIST>(a2, n2w, L2, FULL || s + 4 <= n, v, list_of(2), lc_[2],
-                                          list_room(n, 2));
+                take_w<FULL, FIRST, LIST>(a2, n2w, L2, FULL || s + 4 <= n, v, stage[2], list_of(2), lc_[2],
+                                          list_room(n, 2), lane);
             // levels 3..8 across lanes; every lane keeps the one value of its own level
             double mv = v = level_step<3>(v);
             v = level_step<4>(v);
@@ -484,16 +507,18 @@ __global__ __launch_bounds__(kThreads, 4) void msd_kernel(const MsdArgs A) {
                 am.s2 = fma(e, e, am.s2);
                 if (LIST) far = valid && !(fabs(dm) <= Lm.lt);   // lc == shift
             }
-            if (FIRST && LIST && arr) {
+            if (FIRST && LIST) {
                 // the first pass stores levels 6..8 whole: level k's values of a tile in wave,
                 // then lane order
-                bool in = true;
-                if (!FULL) {
+                uint32_t at = arr_at;
+                if (!FULL && arr) {
                     const int64_t i = (int64_t)tile * (kTile >> my_k) + wave * (256 >> my_k) + (lane >> (my_k - 2));
-                    in = i < (n >> my_k);
+                    if (i >= (n >> my_k)) at = 0x80000000u;
                 }
-                if (in) *arr_at = mv;
-                arr_at += kTile >> my_k;
+                typedef unsigned v2u __attribute__((ext_vector_type(2)));
+                const long long w = __double_as_longlong(mv);
+                __builtin_amdgcn_raw_buffer_store_b64(v2u{(unsigned)w, (unsigned)(w >> 32)}, arr_buf, (int)at, 0, 0);
+                arr_at += arr_step;
             }
             if (LIST) {
                 // append level by level (the ballot and the counts stay in uniform control flow)
@@ -503,19 +528,15 @@ __global__ __launch_bounds__(kThreads, 4) void msd_kernel(const MsdArgs A) {
                     for (int k = 3; k < kListLevels; ++k) {
                         const uint64_t lanes = k == 3 ? 0xaaaaaaaaaaaaaaaaull : k == 4 ? 0x4444444444444444ull
                                                                               : 0x1010101010101010ull;
-                        const uint64_t bk = b & lanes;
-                        if (bk) {
-                            const int i = lc_[k] + count_below(bk);
-                            if (far && my_k == k && i < list_room(n, k)) list_put(list_of(k), i, mv);
-                            lc_[k] += __popcll(bk);
-                        }
+                        list_append(far && my_k == k, b & lanes, mv, stage[k], list_of(k), lc_[k],
+                                    list_room(n, k), lane);
                     }
                 }
             }
         };
         // the pre-estimate reads tiles (i n_tiles) / n_probe, a full read every tile.  The loads of
         // two tiles are in flight while one is taken.
-        auto read_tiles = [&](auto first_tag, auto list_tag) {
+        auto read_tiles = [&](auto first_tag, auto list_tag) __attribute__((always_inline)) {
             constexpr bool kAll = decltype(list_tag)::value;
             const int n_read = kAll ? n_tiles : n_probe;
             auto tile_at = [&](int i) { return kAll ? i : (int)(((int64_t)i * n_tiles) / n_probe); };
@@ -545,8 +566,15 @@ __global__ __launch_bounds__(kThreads, 4) void msd_kernel(const MsdArgs A) {
             else if (first) read_tiles(std::true_type{}, std::true_type{});
             else read_tiles(std::false_type{}, std::true_type{});
         }
-        if (build && lane == 0)
-            for (int k = 0; k < klist; ++k) list_cnt[wave][k] = lc_[k];
+        if (build) {
+#pragma unroll
+            for (int k = 0; k < kListLevels; ++k) {
+                if (k >= klist) break;
+                if (lc_[k] & 63)
+                    list_flush(stage[k], list_of(k), lc_[k] & ~63, min(list_room(n, k), lc_[k]), lane);
+                if (lane == 0) list_cnt[wave][k] = lc_[k];
+            }
+        }
         if (pass == 0 && K > 9) {
             // levels 9.. from pairs of the level below, all in the workspace
             __syncthreads();
