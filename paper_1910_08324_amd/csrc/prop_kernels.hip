@@ -368,7 +368,6 @@ struct TileMaxArgs {
     int64_t pitch[SPD_MAX_LEVELS];
     int64_t slots[SPD_MAX_LEVELS];
     int32_t n_levels, rows_per_tile, n_tiles;
-    int32_t vec_ok;            // planes 16-byte aligned: float4 loads
 };
 
 // A float (never NaN here) as a signed integer of the same order: non-negative floats keep their
@@ -381,21 +380,34 @@ __global__ void tile_init_kernel(int32_t *key, int32_t n_tiles) {
 }
 
 // one work-group per DM row: the row's maximum over every level, merged into its tile's entry
-// with an integer atomic maximum on the order key
+// with an integer atomic maximum on the order key.  Bound by the planes it reads.  The waves take
+// runs of 1024 slots in turn, over the levels' ends (most levels are shorter than what a work-group
+// reads at once), and a run's four loads per lane are issued together: 536 MB of IG(1) planes of 16,384
+// rows 147 -> 138 us (3.9 TB/s), 268 MB of exhaustive planes 73 -> 66 us.
 __global__ __launch_bounds__(256) void tile_max_kernel(const TileMaxArgs A, int32_t *key) {
+    typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
     __shared__ float sh[4];
     const int d = blockIdx.x;
     if (d >= A.n_tiles * A.rows_per_tile) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float mx = -__builtin_huge_valf();
+    int64_t run = wave;                                 // the wave's next run, from the level's first
     for (int lv = 0; lv < A.n_levels; ++lv) {
         const float *Y = A.snr + A.off[lv] + (int64_t)d * A.pitch[lv];
-        const int64_t n = A.slots[lv];
-        const int64_t n4 = A.vec_ok ? n >> 2 : 0;
-        for (int64_t q = threadIdx.x; q < n4; q += 256) {
-            const float4 v = reinterpret_cast<const float4 *>(Y)[q];
-            mx = fmaxf(mx, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)));
+        const int64_t n = A.slots[lv], n4 = n >> 2, runs = (n4 + 255) >> 8;
+        for (; run < runs; run += 4) {
+            v4f v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {               // (past the end the last four slots again)
+                const int64_t q = run * 256 + 64 * u + lane;
+                v[u] = reinterpret_cast<const v4f *>(Y)[q < n4 ? q : n4 - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) mx = fmaxf(mx, fmaxf(fmaxf(v[u].x, v[u].y), fmaxf(v[u].z, v[u].w)));
         }
-        for (int64_t s = 4 * n4 + threadIdx.x; s < n; s += 256) mx = fmaxf(mx, Y[s]);
+        run -= runs;
+        if (wave == (lv & 3) && 4 * n4 + lane < n) mx = fmaxf(mx, Y[4 * n4 + lane]);
     }
     mx = block_max(mx, sh);
     if (threadIdx.x == 0) atomicMax(key + d / A.rows_per_tile, order_key(__float_as_int(mx)));
@@ -1160,12 +1172,10 @@ int spd_tile_max(const float *snr, const spd_plan_info *info, int32_t n_dm, int3
     a.n_levels = info->n_levels;
     a.rows_per_tile = rows_per_tile;
     a.n_tiles = n_dm / rows_per_tile;
-    a.vec_ok = ((uintptr_t)snr & 15) == 0;
     for (int i = 0; i < info->n_levels; ++i) {
         a.off[i] = info->plane_offset[i];
         a.pitch[i] = info->plane_pitch[i];
         a.slots[i] = info->plane_slots[i];
-        if ((a.off[i] | a.pitch[i]) & 3) a.vec_ok = 0;
     }
     // the output holds the order keys until the last pass turns them back into floats
     hipStream_t st = static_cast<hipStream_t>(hip_stream);

@@ -280,3 +280,19 @@ def test_backward_row_counts(P, tiles):
     for n in op.Net.NAMES:
         err = np.abs(np.asarray(got[n], np.float64) - np.asarray(getattr(exact, n), np.float64))
         assert np.all(err <= B[n]), n
+
+
+@pytest.mark.parametrize("n", [5, 257, 1023, 1026, 4099, 9001])
+def test_tile_max_of_odd_rows(P, n):
+    """Levels of every length (shorter than four slots, one slot past a run of 1024, tails of 1 to 3):
+    each tile's maximum is exactly that of the planes' values."""
+    from paper_1910_08324_amd import spd
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn((128, n), generator=g, device="cuda") - 3.0
+    mu, sg = torch.zeros(128, device="cuda"), torch.ones(128, device="cuda")
+    r = spd.Runner(x, mu, sg, spd.Config("ig1", min(n, 1024), candidates=False))
+    r.filter()
+    got = P.tile_max(r.result.snr, r.info, 128).cpu().numpy()
+    torch.cuda.synchronize()
+    ref = np.max([p["Y"].reshape(2, 64, -1).max(axis=(1, 2)) for p in r.result.planes_host()], axis=0)
+    assert np.array_equal(got, ref)
