@@ -191,7 +191,7 @@ class StreamServer:
     def window_ws_max(self, n_dm: int) -> int:
         """The most workspace one window of n_dm rows can need, alone in a batch or beside the
         longest window (whose tile lengths the batch then takes).  The workspace is not monotone
-        in the window length (tile counts, hence pre-candidate slabs, step with the tile length),
+        in the window length (tile counts, hence chunk bits and records, step with the tile length),
         so every window length the server forms is planned."""
         g, best = self.grain, 0
         ref, _ = self._batch_plan([(n_dm, self.cap, self.cap)])
