@@ -77,6 +77,14 @@ int spd_tiles_generate(uint64_t seed, int64_t first_tile, int32_t n_tiles, float
 int spd_prop_features(const float *x, int64_t ld, int32_t n_rows, const float *mean,
                       const float *sigma, uint16_t *feat, void *hip_stream);
 
+/*
+ * spd_prop_features_block: the features of a block x [n_dm][ld] cut into n_col columns of 4096 samples
+ * (ld >= 4096 n_col), one column of rows after another: feat [n_col][n_dm][SPD_PROP_ROW_POS][8], the same
+ * values as spd_prop_features on x + 4096 c for each column c, in one launch.
+ */
+int spd_prop_features_block(const float *x, int64_t ld, int32_t n_dm, int32_t n_col, const float *mean,
+                            const float *sigma, uint16_t *feat, void *hip_stream);
+
 /* Workspace bytes (HOST *bytes) that spd_prop_forward / spd_prop_backward need for n_tiles. */
 int spd_prop_workspace(int32_t n_tiles, int64_t *bytes);
 

@@ -162,7 +162,10 @@ __global__ __launch_bounds__(256) void tiles_kernel(const TileArgs A) {
 
 // ---------------------------------------------------------------------------------------
 // Features: thread p of a row's work-group sums level-4 unit p (16 samples); coarser levels
-// are pairwise sums across lanes (butterflies of 2, 4, 8, 16 lanes, inside one wave).
+// are pairwise sums across lanes (butterflies of 2, 4, 8, 16 lanes, inside one wave).  Bound by
+// reading the samples; a block's columns of 4096 samples go in one launch, as a column of a small
+// block is done in less time than a launch takes (16 columns of 1,024 rows: 16 launches of 5 us
+// each, 40 us as one; the gated search 492 -> 469 us).
 // ---------------------------------------------------------------------------------------
 struct FeatArgs {
     const float *x;
@@ -170,16 +173,17 @@ struct FeatArgs {
     const float *mean;
     const float *sigma;
     uint16_t *feat;
-    int32_t n_rows;
+    int32_t n_dm, n_rows;      // rows of a column, and of all columns
 };
 
 __global__ __launch_bounds__(256) void features_kernel(const FeatArgs A) {
     const int r = blockIdx.x;
     const int p = threadIdx.x;
     if (r >= A.n_rows) return;
-    const float *xr = A.x + (int64_t)r * A.ld + 16 * p;
-    const float mu = A.mean[r];
-    const float inv = 1.0f / A.sigma[r];
+    const int c = r / A.n_dm, d = r - c * A.n_dm;
+    const float *xr = A.x + (int64_t)d * A.ld + (int64_t)c * LEN + 16 * p;
+    const float mu = A.mean[d];
+    const float inv = 1.0f / A.sigma[d];
     float y4 = 0.0f;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -1104,8 +1108,19 @@ int spd_prop_features(const float *x, int64_t ld, int32_t n_rows, const float *m
                       const float *sigma, uint16_t *feat, void *hip_stream) {
     if (!x || !mean || !sigma || !feat || n_rows < 1 || ld < LEN || (ld & 3)) return SPD_EINVAL;
     if (((uintptr_t)x & 15) || ((uintptr_t)feat & 15)) return SPD_EALIGN;
-    FeatArgs a{x, ld, mean, sigma, feat, n_rows};
+    FeatArgs a{x, ld, mean, sigma, feat, n_rows, n_rows};
     SPDP_LAUNCH(features_kernel, dim3(n_rows), dim3(256), 0, static_cast<hipStream_t>(hip_stream), a);
+    return SPD_OK;
+}
+
+int spd_prop_features_block(const float *x, int64_t ld, int32_t n_dm, int32_t n_col, const float *mean,
+                            const float *sigma, uint16_t *feat, void *hip_stream) {
+    if (!x || !mean || !sigma || !feat || n_dm < 1 || n_col < 1 || ld < (int64_t)n_col * LEN || (ld & 3) ||
+        (int64_t)n_dm * n_col > INT32_MAX)
+        return SPD_EINVAL;
+    if (((uintptr_t)x & 15) || ((uintptr_t)feat & 15)) return SPD_EALIGN;
+    FeatArgs a{x, ld, mean, sigma, feat, n_dm, n_dm * n_col};
+    SPDP_LAUNCH(features_kernel, dim3(n_dm * n_col), dim3(256), 0, static_cast<hipStream_t>(hip_stream), a);
     return SPD_OK;
 }
 

@@ -33,6 +33,7 @@ def lib():
         P, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
         L.spd_tiles_generate.argtypes = [ctypes.c_uint64, i64, i32, P, P]
         L.spd_prop_features.argtypes = [P, i64, i32, P, P, P, P]
+        L.spd_prop_features_block.argtypes = [P, i64, i32, i32, P, P, P, P]
         L.spd_prop_workspace.argtypes = [i32, ctypes.POINTER(i64)]
         L.spd_prop_forward.argtypes = [P, P, i32, P, P, i64, P]
         L.spd_prop_backward.argtypes = [P, P, P, i32, P, P, P, P, i64, P]
@@ -40,7 +41,7 @@ def lib():
         L.spd_tile_max.argtypes = [P, ctypes.POINTER(spd.PlanInfo), i32, i32, P, P]
         L.spd_prop_labels.argtypes = [P, P, i32, ctypes.c_float, ctypes.c_float, P, P]
         L.spd_prop_flags.argtypes = [P, i32, i32, ctypes.c_float, P, P]
-        for n in ("spd_tiles_generate", "spd_prop_features", "spd_prop_workspace",
+        for n in ("spd_tiles_generate", "spd_prop_features", "spd_prop_features_block", "spd_prop_workspace",
                   "spd_prop_forward", "spd_prop_backward", "spd_prop_adam", "spd_tile_max",
                   "spd_prop_labels", "spd_prop_flags"):
             getattr(L, n).restype = ctypes.c_int
@@ -110,6 +111,15 @@ def features(x, mean, sigma, out=None):
         out = torch.empty((rows, ROW_POS, FEAT_CH), dtype=torch.int16, device=x.device)
     spd._check(lib().spd_prop_features(_p(x), x.stride(0), rows, _p(mean), _p(sigma), _p(out),
                                        _stream(x.device)), "spd_prop_features")
+    return out
+
+
+def features_block(x, mean, sigma, out):
+    """features() of every column of 4096 samples of a block x [n_dm][n], one column of rows after
+    another, in one launch."""
+    n_dm, n = x.shape
+    spd._check(lib().spd_prop_features_block(_p(x), x.stride(0), n_dm, n // TILE_LEN, _p(mean), _p(sigma),
+                                             _p(out), _stream(x.device)), "spd_prop_features_block")
     return out
 
 
@@ -321,10 +331,7 @@ class GatedSearch:
                                     TILE_ROWS, TILE_LEN, cand_cap=cand_cap)
 
     def propose(self):
-        n_dm = self.x.shape[0]
-        for c in range(self.n_ct):
-            features(self.x[:, c * TILE_LEN:(c + 1) * TILE_LEN], self.mean, self.sigma,
-                     out=self.feat[c * n_dm:(c + 1) * n_dm])
+        features_block(self.x, self.mean, self.sigma, self.feat)
         self.net.forward(self.feat, self.n_ct * self.n_rt, self.logits)
         flags(self.logits, self.n_rt, self.n_ct, self.logit_threshold, out=self.flag)
 

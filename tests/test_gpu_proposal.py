@@ -296,3 +296,18 @@ def test_tile_max_of_odd_rows(P, n):
     torch.cuda.synchronize()
     ref = np.max([p["Y"].reshape(2, 64, -1).max(axis=(1, 2)) for p in r.result.planes_host()], axis=0)
     assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("n_dm,n_col,pad", [(1, 1, 0), (3, 1, 4), (5, 2, 0), (64, 3, 12), (2, 17, 4096)])
+def test_features_of_a_block(P, n_dm, n_col, pad):
+    """A block's columns in one launch are bit for bit the columns one by one; nothing past them is written."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn((n_dm, n_col * P.TILE_LEN + pad), generator=g, device="cuda")[:, :n_col * P.TILE_LEN]
+    mu = torch.randn(n_dm, generator=g, device="cuda")
+    sg = torch.rand(n_dm, generator=g, device="cuda") + 0.5
+    out = torch.full((n_col * n_dm + 1, P.ROW_POS, P.FEAT_CH), 77, dtype=torch.int16, device="cuda")
+    P.features_block(x, mu, sg, out[:-1])
+    for c in range(n_col):
+        one = P.features(x[:, c * P.TILE_LEN:(c + 1) * P.TILE_LEN], mu, sg)
+        assert torch.equal(out[c * n_dm:(c + 1) * n_dm], one), c
+    assert bool((out[-1] == 77).all())
