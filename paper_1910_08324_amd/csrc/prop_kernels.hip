@@ -164,7 +164,7 @@ __global__ __launch_bounds__(256) void tiles_kernel(const TileArgs A) {
 // Features: thread p of a row's work-group sums level-4 unit p (16 samples); coarser levels
 // are pairwise sums across lanes (butterflies of 2, 4, 8, 16 lanes, inside one wave).  Bound by
 // reading the samples; a block's columns of 4096 samples go in one launch, as a column of a small
-// block is done in less time than a launch takes (16 columns of 1,024 rows: 16 launches of 5 us
+// block is done in less time than a launch takes (16 columns of 512 rows: 16 launches of 5 us
 // each, 40 us as one; the gated search 492 -> 469 us).
 // ---------------------------------------------------------------------------------------
 struct FeatArgs {
