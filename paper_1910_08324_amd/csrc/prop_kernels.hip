@@ -444,8 +444,8 @@ __global__ void flags_kernel(const float *logits, int32_t n_row, int32_t n_col, 
 // Fused inference: one work-group per row runs the three convolutions with the activations in
 // LDS (features 4.2 KB, two activation buffers of 21 KB), then the read-out; only the
 // features come from HBM.  Each row leaves its read-out maximum and sum of exp(s - max); a
-// second kernel combines a tile's 64 rows into the logit.  The MFMA sequence is the unfused
-// kernels' one, so the activations are bitwise the same.
+// second kernel combines a tile's 64 rows into the logit.  Training runs this
+// launch too, and the backward launch forms the same activations again by the same MFMA sequence.
 // ---------------------------------------------------------------------------------------
 struct InferArgs {
     const uint16_t *feat;
