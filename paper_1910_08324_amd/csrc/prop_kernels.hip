@@ -821,9 +821,10 @@ __global__ __launch_bounds__(kBwdThreads, 2) void backward_kernel(const BwdArgs 
         const float lse = A.lse[r / ROWS], dlogit = A.dlogit[r / ROWS];
         if (tid < NF) {
             reinterpret_cast<uint4 *>(f)[tid] = fp;
-            const uint32_t w[3] = {fp.x, fp.y, fp.z};
+            // (all eight channels: the caller's features may fill those spd_prop_features leaves zero)
+            const uint32_t w[4] = {fp.x, fp.y, fp.z, fp.w};
 #pragma unroll
-            for (int c = 0; c < 5; ++c) ft[c * T_LD + tid] = (uint16_t)(w[c / 2] >> (16 * (c & 1)));
+            for (int c = 0; c < FCH; ++c) ft[c * T_LD + tid] = (uint16_t)(w[c / 2] >> (16 * (c & 1)));
         } else if (tid < NF + 6 * (ACT_LD / 8)) {
             // c1's pads, where z3 was
             const int i = tid - NF, p = i / (ACT_LD / 8), q = i - p * (ACT_LD / 8);

@@ -311,3 +311,24 @@ def test_features_of_a_block(P, n_dm, n_col, pad):
         one = P.features(x[:, c * P.TILE_LEN:(c + 1) * P.TILE_LEN], mu, sg)
         assert torch.equal(out[c * n_dm:(c + 1) * n_dm], one), c
     assert bool((out[-1] == 77).all())
+
+
+def test_gradient_of_every_feature_channel(P):
+    """Channels 5 .. 7 of the features, zero as spd_prop_features writes them, count in the gradient when a
+    caller fills them: as copies of channels 2, 0 and 4 (their weights stay zero, so the forward pass is the
+    same) they get those channels' gradients bit for bit, and the others' do not change."""
+    tiles = 5
+    _, feat = make_batch(P, tiles, seed=51)
+    net = oracle_net(51)
+    N = P.Network(packed(P, net), max_tiles=tiles)
+    lab = (torch.arange(tiles, device="cuda") % 2).float()
+    N.backward(feat, lab, tiles)
+    ref = N.grads.cpu().numpy().copy()
+    assert np.all(ref[:1280].reshape(32, 5, 8)[:, :, 5:] == 0)
+    feat[:, :, 5:] = feat[:, :, [2, 0, 4]]
+    N.backward(feat, lab, tiles)
+    got = N.grads.cpu().numpy()
+    W1, R1 = got[:1280].reshape(32, 5, 8), ref[:1280].reshape(32, 5, 8)
+    assert np.abs(R1[:, :, :5]).min() > 0
+    assert np.array_equal(W1[:, :, :5], R1[:, :, :5]) and np.array_equal(got[1280:], ref[1280:])
+    assert np.array_equal(W1[:, :, 5:], R1[:, :, [2, 0, 4]])
