@@ -192,6 +192,7 @@ struct StepPlan {
     int64_t out_len = 0;       // units handed to the next step per row
     int64_t ld_out = 0;        // row pitch of the handed-on series in the workspace
     int64_t off_out = -1, off_cout = -1;
+    int32_t carry_end = -1;    // see StepArgs::carry_end
     spd::StepLevel lv[spd::kStepMaxLevels + 1];
     float rtab[spd::kStepMaxLevels][spd::kMaxLevelWidths] = {{0}};
 };
@@ -420,6 +421,8 @@ int make_layout(const spd_params *p, const Search &s, int32_t n_dm, int32_t n_in
             }
             if (tiles * n_dm > INT32_MAX) return SPD_EINVAL;
             st.tiles = (int)tiles;
+            if (s.method == SPD_BOXDIT && n_out < n_in)
+                st.carry_end = (int32_t)(I.plane_slots[K] << (K - k0));
             for (int j = 0; j < st.J; ++j) {
                 L->tiles_per_row[k0 + j] = st.tiles;
                 L->tile_slots[k0 + j] = st.T >> j;
@@ -723,6 +726,7 @@ int run_filter(const spd_params *params, const Prepared &P, const float *x, int6
             a.n_in = n_in;
             a.in_len = (int32_t)st.in_len;
             a.n_tiles = st.tiles;
+            a.carry_end = st.carry_end;
             if (L.off_rec >= 0) a.rec = reinterpret_cast<spd::RecStep *>(P.ws + L.off_rec) + si;
             if (L.off_dir >= 0) {
                 a.dir = reinterpret_cast<uint32_t *>(P.ws + L.off_dir);
@@ -968,6 +972,7 @@ spd::BeamView beam_view(const spd_params *params, const BatchPlan &B, const spd_
     v.n_dm = bm.n_dm;
     v.n_in = bm.n_in;
     v.in_len = (int32_t)st.in_len;
+    v.carry_end = st.carry_end;
     v.n_tiles = st.tiles;
     for (int j = 0; j < st.J; ++j) {
         v.plane_off[j] = st.lv[j].plane_off;

@@ -122,7 +122,10 @@ struct StepArgs {
     uint64_t *pool;
     unsigned long long *pool_used;   // units asked for (may exceed pool_units: the rest has no record)
     uint32_t pool_units;
-    uint32_t pad1;
+    // BoxDIT with look-ahead samples (else -1): the last slot of the step's first level whose carry
+    // is formed.  The slot after a level's last one (see edge) needs the carries of the slots that
+    // lead to it, which lie past the planes' ends: slot s of level k from s 2^i of level k - i.
+    int32_t carry_end;
     StepLevel lv[kStepMaxLevels + 1];
     float rtab[kStepMaxLevels][kMaxLevelWidths];   // 1/sqrt(base + U 2^k) at [j][U-1]
 };
@@ -152,7 +155,8 @@ struct BeamView {
     int64_t plane_off[kStepMaxLevels];
     int64_t pitch[kStepMaxLevels];
     int32_t slots[kStepMaxLevels];
-    int32_t pad0[2];
+    int32_t carry_end;          // as StepArgs::carry_end
+    int32_t pad0;
 };
 
 struct StepBatchArgs {

@@ -292,6 +292,7 @@ struct ArgGeom {
     __device__ uint64_t *pool() const { return P->pool; }
     __device__ unsigned long long *pool_used() const { return P->pool_used; }
     __device__ uint32_t pool_units() const { return P->pool_units; }
+    __device__ int carry_end() const { return P->carry_end; }
     __device__ int64_t plane_off(int j) const { return P->lv[j].plane_off; }
     __device__ int64_t pitch(int j) const { return P->lv[j].pitch; }
     __device__ int slots(int j) const { return P->lv[j].slots; }
@@ -331,6 +332,7 @@ struct TabGeom {
     __device__ uint64_t *pool() const { return V->pool; }
     __device__ unsigned long long *pool_used() const { return V->pool_used; }
     __device__ uint32_t pool_units() const { return V->pool_units; }
+    __device__ int carry_end() const { return V->carry_end; }
     __device__ int64_t plane_off(int j) const { return V->plane_off[j]; }
     __device__ int64_t pitch(int j) const { return V->pitch[j]; }
     __device__ int slots(int j) const { return V->slots[j]; }
@@ -518,7 +520,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
     if (tid < 3 * kStepMaxLevels) st_cnt[tid] = 0;
     if (d == 0 && tile == 0 && V.rec()) write_rec<NTH>(A, V, V.rec());
     if (FIRST && carry && A.J > 1 && V.edge() && tid < kGroup) {
-        // level 1's slots after the plane's last one may have no carried prefix: taken as zero
+        // level 1's slots after the last one with a carried prefix: taken as zero
         const int i = V.slots(1) - tile * (T >> 1) + tid;
         if (i >= 0 && i < (T >> 1)) lds[A.lv[0].lds_c + i] = 0.0f;
     }
@@ -592,9 +594,10 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
         if (!FIRST && carry && V.cin()) {
             const float *cr = V.cin() + (int64_t)d * V.ld_cin();
             float *c0 = lds + A.lv[0].lds_c;
+            const int64_t cend = max((int64_t)V.slots(0), min((int64_t)V.carry_end() + 1, len));
             for (int i = tid; i < T; i += NTH) {
                 const int64_t m = u0 + i;
-                c0[i] = (m < V.slots(0)) ? cr[m] : 0.0f;
+                c0[i] = (m < cend) ? cr[m] : 0.0f;
             }
         }
     }
@@ -629,6 +632,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
         const int ms0 = tile * Sj;                         // absolute slot of tile slot 0
         const int ngroups = Sj / kGroup;
         const int slots = V.slots(j);
+        const int formed = carry ? max(slots, (V.carry_end() >> j) + 1) : slots;   // slots with a carry
         const bool has_carry = carry && (j > 0 || V.cin() != nullptr);
         const bool to_lds = carry && (j + 1 < A.J);
         const bool to_glb = carry && (j + 1 == A.J) && A.has_out;
@@ -706,7 +710,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
                     nu0 = w0.x + w0.y;
                     nu1 = w0.z + w0.w;
                     const bool act = g < ngroups && ma < slots;
-                    if (act) {
+                    if (g < ngroups && ma < formed) {       // (past the plane for the carry alone)
                         if (has_carry) {
 #pragma unroll
                             for (int q = 0; q < kGroup; ++q) X[q] = cbuf[m0 + q];
@@ -745,7 +749,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
                         if (n0 >= 0 && n0 < n_next) ybuf[n0] = nu0;
                         if (n0 + 1 >= 0 && n0 + 1 < n_next) ybuf[n0 + 1] = nu1;
                         // this level's longest boxcar is the next level's carried prefix
-                        if (to_lds && ms0 + g * kGroup < slots)
+                        if (to_lds && ms0 + g * kGroup < formed)
                             *reinterpret_cast<float2 *>(cbuf + 2 * g) = make_float2(xc0, xc1);
                     }
                 }

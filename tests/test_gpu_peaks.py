@@ -112,3 +112,42 @@ def test_small_block_under_a_bright_pulse(dev, method, n_dm, n, l_end):
     assert n0 == n1 == len(ref) > 0 and np.array_equal(ref, rec)
     R = oplanes.planes(x, mu, sg, ow.method_levels(method, l_end))
     parity.check_candidates(ref, R, 5.0, what=method)
+
+
+@pytest.mark.parametrize("planes", [True, False])
+@pytest.mark.parametrize("method,l_end,segment,step_levels", [
+    ("bd8", 500, 0, 0), ("bd16", 400, 512, 2), ("bd32", 700, 0, 0), ("bd32", 700, 0, 1), ("bd", 300, 256, 3)])
+@pytest.mark.parametrize("n_out", [2290, 2301, 2306])
+def test_last_slot_of_boxdit_levels(dev, planes, method, l_end, segment, step_levels, n_out):
+    """BoxDIT: the slot after a level's last one is evaluated with the carried prefix that the search of a
+    longer plane gives it, at every level (its prefix comes from slots past the lower levels' ends), for
+    every remainder of the levels' slots and with steps that hand the prefixes on."""
+    from paper_1910_08324_amd import spd
+    n_dm, n, thr = 96, 4200, 6.0
+    rng = np.random.default_rng(n_out)
+    # pulses of any width that end near the planes' ends, so that the two slots are close
+    pulses = [synth.Pulse(d, n_out - int(w * rng.uniform(0.0, 1.0)), int(w), 45.0)
+              for d in range(n_dm) for w in (np.exp(rng.uniform(0, np.log(l_end))),)]
+    x, mu, sg = make_input(n_dm, n, 80, pulses=pulses)
+    t = [torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to(dev) for a in (x, mu, sg)]
+    kw = dict(boxdit_lmax=[6, 10]) if method == "bd" else {}
+    wide = spd.search(*t, spd.Config(method, l_end, threshold=thr, **kw), n_out=n_out + 1024)
+    r = spd.search(*t, spd.Config(method, l_end, threshold=thr, planes=planes, segment=segment,
+                                  step_levels=step_levels, **kw), n_out=n_out)
+    torch.cuda.synchronize()
+    got = {(int(c["level"]), int(c["dm"]), int(c["start"])) for c in r.candidates_host()}
+    barred = 0
+    for i in range(r.info.n_levels):
+        k, slots = int(r.info.level_shift[i]), int(r.info.plane_slots[i])
+        Y = np.full((n_dm + 2, slots + 2), -np.inf, np.float32)
+        Y[1:-1, 1:-1] = wide.level(i)[0][:, :slots].cpu().numpy()
+        after = wide.level(i)[0][:, slots].cpu().numpy()
+        for d in range(n_dm):
+            c, m = Y[d + 1, slots], slots - 1
+            ok = c > thr and all(c > v for v in (*Y[d, slots - 1:slots + 2], Y[d + 1, slots - 1])) and \
+                all(c >= v for v in (Y[d + 1, slots + 1], *Y[d + 2, slots - 1:slots + 2]))
+            if ok and slots % 4 != 0 and not c >= after[d]:
+                barred += 1
+                ok = False
+            assert ((i, d, m << k) in got) == ok, (i, k, slots, d, c, after[d])
+    assert barred > 3
