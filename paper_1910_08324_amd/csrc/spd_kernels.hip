@@ -519,11 +519,6 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
     const int64_t u0 = (int64_t)tile * T;
     if (tid < 3 * kStepMaxLevels) st_cnt[tid] = 0;
     if (d == 0 && tile == 0 && V.rec()) write_rec<NTH>(A, V, V.rec());
-    if (FIRST && carry && A.J > 1 && V.edge() && tid < kGroup) {
-        // level 1's slots after the last one with a carried prefix: taken as zero
-        const int i = V.slots(1) - tile * (T >> 1) + tid;
-        if (i >= 0 && i < (T >> 1)) lds[A.lv[0].lds_c + i] = 0.0f;
-    }
 
     // ---- 1. window of the input series (normalised in the first step) and carried prefixes
     {
@@ -632,7 +627,6 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
         const int ms0 = tile * Sj;                         // absolute slot of tile slot 0
         const int ngroups = Sj / kGroup;
         const int slots = V.slots(j);
-        const int formed = carry ? max(slots, (V.carry_end() >> j) + 1) : slots;   // slots with a carry
         const bool has_carry = carry && (j > 0 || V.cin() != nullptr);
         const bool to_lds = carry && (j + 1 < A.J);
         const bool to_glb = carry && (j + 1 == A.J) && A.has_out;
@@ -710,7 +704,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
                     nu0 = w0.x + w0.y;
                     nu1 = w0.z + w0.w;
                     const bool act = g < ngroups && ma < slots;
-                    if (g < ngroups && ma < formed) {       // (past the plane for the carry alone)
+                    if (act || (carry && g < ngroups && ma <= V.carry_end() >> j)) {   // (for the carry alone)
                         if (has_carry) {
 #pragma unroll
                             for (int q = 0; q < kGroup; ++q) X[q] = cbuf[m0 + q];
@@ -748,8 +742,9 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
                         const int n0 = form_next ? (g * kGroup - A.lv[j + 1].cshift) >> 1 : -2;
                         if (n0 >= 0 && n0 < n_next) ybuf[n0] = nu0;
                         if (n0 + 1 >= 0 && n0 + 1 < n_next) ybuf[n0 + 1] = nu1;
-                        // this level's longest boxcar is the next level's carried prefix
-                        if (to_lds && ms0 + g * kGroup < formed)
+                        // this level's longest boxcar is the next level's carried prefix (zero where
+                        // it is not formed)
+                        if (to_lds)
                             *reinterpret_cast<float2 *>(cbuf + 2 * g) = make_float2(xc0, xc1);
                     }
                 }
