@@ -645,11 +645,16 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineArgs A) {
 // channel are five shifts of 12 consecutive positions, so two 16-byte loads and eight register
 // funnel shifts feed five MFMAs.
 //
-// One work-group of 8 waves per CU (144 KB of LDS), persistent over rows.  A wave convolves its 32
+// One work-group of 8 waves per CU (150,688 bytes of LDS), persistent over rows.  A wave convolves its 32
 // positions; the weight gradients of a row, 12 MFMA tiles summed over 256 positions, are 24
-// half-tiles, three per wave, so that their accumulators stay in registers
-// with two waves per SIMD.  The weights of layer 3 and of the input gradients come from the cache
-// for each row.  At the end the halves are added in order and the work-group writes one partial.
+// half-tiles, three per wave, whose accumulators are kept over the rows.  The weights of layer 3 and of
+// the input gradients come from the cache for each row.  All of it needs more than the 256 registers of
+// a lane with two waves per SIMD: the compiler keeps 44 values in scratch (180 bytes a lane).
+// FP32 chains stay short whatever the number of tiles: every kBwdFlush rows the accumulators are added
+// to the work-group's partial (the halves of a tile in turn) and the lanes' sums to their totals in
+// LDS.  An accumulator then takes 256 MFMAs in a row, a bias gradient 512 additions and the
+// read-out's 16 a row and 32 rows.  One chain over all rows of a work-group lost accuracy with the
+// tiles of a call: 1024 tiles alike, read-out gradient 4e-5 off.
 // Measured, 16,384 rows (256 tiles): 0.91 ms, and 0.14 ms for the forward launch, where separate
 // launches per convolution, weight gradient and read-out, bound by 3.3 GB of activations and by
 // 2-byte gathers, took 2.35 ms together.  Bound by latency: a row's MFMAs need 6.4k of its 30k cycles.
@@ -669,7 +674,6 @@ constexpr int T_ELEMS = CH * T_LD;
 constexpr int ACT_ELEMS = RP * ACT_LD;
 constexpr int BWD_ELEMS = RP * FCH + 3 * ACT_ELEMS + 4 * T_ELEMS + FCH * T_LD;
 constexpr int P1 = CH * TAPS * FCH + CH, P2 = CH * KW + CH;   // floats of a partial of layer 1; 2, 3
-static_assert((P1 + 2 * P2) * 4 <= BWD_ELEMS * 2, "the waves' sums fit where the activations were");
 
 // both forms of one 32-position tile at p0: n (weights as rows), t (positions as rows)
 template <int CI, bool N>
@@ -691,6 +695,7 @@ __device__ __forceinline__ void conv_both(const uint16_t *in, const LayerW<CI> &
 }
 
 constexpr int kBwdThreads = 512;
+constexpr int kBwdFlush = 32;                  // rows between additions to the partial
 
 // acc[co][column] += sum over 128 positions from p of dz[pos][co] in[pos + T][channel], the channel
 // (lane n's column) chosen by the row `in` points to.  T < 0 (layer 1, columns 8 t + ci): lane n takes
@@ -735,7 +740,8 @@ __global__ __launch_bounds__(kBwdThreads, 2) void backward_kernel(const BwdArgs 
     __shared__ __attribute__((aligned(16))) uint16_t smem[BWD_ELEMS];
     __shared__ __attribute__((aligned(16))) float bias[4 * CH];   // the layers' biases, the read-out's weights
     __shared__ __attribute__((aligned(16))) float dsv[POS];
-    __shared__ float red[8 + CH];
+    __shared__ float red[8];
+    __shared__ float tot[5][kBwdThreads];      // each lane's b1, b2, b3, gw, gb up to the last flush
     uint16_t *f = smem;
     uint16_t *c1 = f + RP * FCH, *c2 = c1 + ACT_ELEMS, *c3 = c2 + ACT_ELEMS;      // channel-last
     uint16_t *t1 = c3 + ACT_ELEMS, *t2 = t1 + T_ELEMS, *z1 = t2 + T_ELEMS, *z2 = z1 + T_ELEMS;
@@ -769,6 +775,9 @@ __global__ __launch_bounds__(kBwdThreads, 2) void backward_kernel(const BwdArgs 
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[q][i] = 0.0f;
     float b1 = 0.0f, b2 = 0.0f, b3 = 0.0f, gw = 0.0f, gb = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 5; ++i) tot[i][tid] = 0.0f;
+    const int64_t b = blockIdx.x;
     uint4 fp = make_uint4(0u, 0u, 0u, 0u);
     auto fetch = [&](int r) {
         if (tid < NF) fp = reinterpret_cast<const uint4 *>(A.feat + (int64_t)r * RP * FCH)[tid];
@@ -817,6 +826,8 @@ __global__ __launch_bounds__(kBwdThreads, 2) void backward_kernel(const BwdArgs 
     };
     fetch(blockIdx.x);
     lds_barrier();
+    int since = 0;                              // rows since the last flush
+    bool flushed = false;
     for (int r = blockIdx.x; r < A.rows; r += gridDim.x) {
         const float lse = A.lse[r / ROWS], dlogit = A.dlogit[r / ROWS];
         if (tid < NF) {
@@ -892,6 +903,7 @@ __global__ __launch_bounds__(kBwdThreads, 2) void backward_kernel(const BwdArgs 
             }
         }
         // (dsv is complete since the barrier above)
+        float gr = 0.0f;                      // the row's
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             const float4 d4 = *reinterpret_cast<const float4 *>(dsv + p0 + 8 * g + 4 * h);
@@ -900,14 +912,15 @@ __global__ __launch_bounds__(kBwdThreads, 2) void backward_kernel(const BwdArgs 
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const float x = low_bf16(a3[2 * g + i]), y = high_bf16(a3[2 * g + i]);
-                gw += ds[2 * i] * x;
-                gw += ds[2 * i + 1] * y;
+                gr += ds[2 * i] * x;
+                gr += ds[2 * i + 1] * y;
                 u[i] = pack_bf16(x > 0.0f ? ds[2 * i] * whn : 0.0f, y > 0.0f ? ds[2 * i + 1] * whn : 0.0f);
                 b3 += low_bf16(u[i]);
                 b3 += high_bf16(u[i]);
             }
             *reinterpret_cast<uint2 *>(z3 + n * T_LD + p0 + 8 * g + 4 * h) = make_uint2(u[0], u[1]);
         }
+        gw += gr;
         lds_barrier();
         // ---- the gradient at layer 2's output, over its activations c2
         conv_both<CH, true>(c3, V, p0, l, an, at);
@@ -940,49 +953,61 @@ __global__ __launch_bounds__(kBwdThreads, 2) void backward_kernel(const BwdArgs 
                 default: wgrad_half<4>(dz, in, acc[q], n); break;
             }
         }
+        if (++since == kBwdFlush || r + (int)gridDim.x >= A.rows) {
+            // ---- to the partial: the two halves of each tile in turn (the lane's place in a tile is
+            // formed here: kept over the rows, its addresses would push the accumulators out)
+            int place = l;
+            asm volatile("" : "+v"(place));
+            const int pn = place & 31, ph = place >> 5;
+            for (int half = 0; half < 2; ++half) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    if (((3 * wave + q) & 1) != half) continue;
+                    const int job = (3 * wave + q) >> 1;
+                    const int k = (job < 5 ? job : job < 10 ? job - 5 : job - 10) * CH + pn;
+                    const int ld = job < 10 ? KW : TAPS * FCH;
+                    float *p = (job < 5 ? A.part3 + b * P2 : job < 10 ? A.part2 + b * P2 : A.part1 + b * P1) + k;
+                    if (job < 11 || pn < 8) {
+                        p += 4 * ph * ld;
+                        float v[16];
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) v[i] = 0.0f;
+                        if (half || flushed) {
+#pragma unroll
+                            for (int i = 0; i < 16; ++i) v[i] = p[(8 * (i / 4) + (i % 4)) * ld];
+                        }
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) p[(8 * (i / 4) + (i % 4)) * ld] = v[i] + acc[q][i];
+                    }
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[q][i] = 0.0f;
+                }
+                __syncthreads();
+            }
+            tot[0][tid] += b1;
+            tot[1][tid] += b2;
+            tot[2][tid] += b3;
+            tot[3][tid] += gw;
+            tot[4][tid] += gb;
+            b1 = b2 = b3 = gw = gb = 0.0f;
+            since = 0;
+            flushed = true;
+        }
         lds_barrier();                        // everything is rewritten for the next row
     }
-    // ---- the two halves of each tile and the waves' sums in order, then one partial per work-group
-    float *sum1 = reinterpret_cast<float *>(smem), *sum2 = sum1 + P1, *sum3 = sum2 + P2;
-    for (int half = 0; half < 2; ++half) {
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            if (((3 * wave + q) & 1) != half) continue;
-            const int job = (3 * wave + q) >> 1;
-            const int k = job < 5 ? job * CH + n : job < 10 ? (job - 5) * CH + n : (job - 10) * CH + n;
-            const int ld = job < 10 ? KW : TAPS * FCH;
-            float *p = (job < 5 ? sum3 : job < 10 ? sum2 : sum1) + k;
-            if (job == 11 && n >= 8) continue;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                float *at = p + (8 * (i / 4) + 4 * h + (i % 4)) * ld;
-                *at = half == 0 ? acc[q][i] : *at + acc[q][i];
-            }
-        }
-        __syncthreads();
+    // ---- the lanes' totals: bias and read-out gradients of channel c over the waves in order
+    if (tid < 4 * CH) {
+        const int i = tid / CH, c = tid - i * CH;
+        float v = 0.0f;
+        for (int w = 0; w < kBwdThreads / 64; ++w) v += tot[i][64 * w + c] + tot[i][64 * w + 32 + c];
+        float *p = i == 0 ? A.part1 + b * P1 + CH * TAPS * FCH : i == 1 ? A.part2 + b * P2 + CH * KW
+                   : i == 2 ? A.part3 + b * P2 + CH * KW : A.hpart + b * (CH + 1);
+        p[c] = v;
     }
-    const float o1 = b1 + __shfl_down(b1, 32), o2 = b2 + __shfl_down(b2, 32);
-    const float o3 = b3 + __shfl_down(b3, 32), ow = gw + __shfl_down(gw, 32);
-    for (int w = 0; w < kBwdThreads / 64; ++w) {
-        if (wave == w && l < CH) {
-            auto add = [&](float *p, float v) { *p = w == 0 ? v : *p + v; };
-            add(sum1 + CH * TAPS * FCH + l, o1);
-            add(sum2 + CH * KW + l, o2);
-            add(sum3 + CH * KW + l, o3);
-            add(red + 8 + l, ow);
-        }
-        __syncthreads();
-    }
+    gb = tot[4][tid];
     for (int o = 32; o > 0; o >>= 1) gb += __shfl_xor(gb, o);
     if (l == 0) red[wave] = gb;
     __syncthreads();
-    const int64_t b = blockIdx.x;
-    for (int i = tid; i < P1; i += kBwdThreads) A.part1[b * P1 + i] = sum1[i];
-    for (int i = tid; i < P2; i += kBwdThreads) {
-        A.part2[b * P2 + i] = sum2[i];
-        A.part3[b * P2 + i] = sum3[i];
-    }
-    if (tid < CH) A.hpart[b * (CH + 1) + tid] = red[8 + tid];
     if (tid == 0) A.hpart[b * (CH + 1) + CH] = (red[0] + red[1]) + (red[2] + red[3]);   // (positions: waves 0..3)
 }
 

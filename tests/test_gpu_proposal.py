@@ -332,3 +332,25 @@ def test_gradient_of_every_feature_channel(P):
     assert np.abs(R1[:, :, :5]).min() > 0
     assert np.array_equal(W1[:, :, :5], R1[:, :, :5]) and np.array_equal(got[1280:], ref[1280:])
     assert np.array_equal(W1[:, :, 5:], R1[:, :, [2, 0, 4]])
+
+
+def test_readout_gradient_of_many_tiles(P):
+    """1024 tiles alike (256 rows a work-group): every position adds the same to the read-out's gradient, so
+    rounding in one long chain of additions would go one way.  The sums go a row (16), 32 rows, the groups of
+    32 rows (8), the waves (17) and the partials (8 and 32) at a time: 113 additions of at most 2^-24 each, and
+    3e-6 for exp(s - lse) and the logit."""
+    tiles = 1024
+    rng = np.random.default_rng(61)
+    z = np.zeros
+    b3 = op.round_bf16(rng.uniform(0.2, 1.5, 32))
+    wh = rng.uniform(0.005, 0.03, 32).astype(np.float32).astype(np.float64)
+    p = P.pack({"W1": z((32, 5, 5)), "b1": z(32), "W2": z((32, 5, 32)), "b2": z(32), "W3": z((32, 5, 32)),
+                "b3": b3, "wh": wh, "bh": 0.125})
+    N = P.Network(p, max_tiles=tiles)
+    feat = torch.zeros((tiles * 64, P.ROW_POS, P.FEAT_CH), dtype=torch.int16, device="cuda")
+    N.backward(feat, torch.zeros(tiles, device="cuda"), tiles)
+    g = P.unpack(N.grads.cpu().numpy())
+    sig = 1.0 / (1.0 + np.exp(-(float(wh @ b3) + 0.125)))      # the mean over the tiles of d loss / d logit
+    tol = 113 * 2.0 ** -24 + 3e-6
+    assert np.abs(np.asarray(g["wh"], np.float64) / (b3 * sig) - 1.0).max() <= tol
+    assert abs(float(g["bh"]) / sig - 1.0) <= tol
