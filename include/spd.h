@@ -77,6 +77,8 @@ extern "C" {
  *   igrid_depth     IGRID only: d in 0..4.
  *   igrid_layers    IGRID only: P, a power of two with 2^d <= P <= 64, or 0 for P = 2^(d+1) (the
  *                   paper's 4/8/16 layers for IG(1)/(2)/(3)).  d = 0, P = 1 is the plain DIT search.
+ *                   A level's widths are at most 64 of its units (2^k samples at level k): P = 64 with
+ *                   d >= 1 is SPD_EINVAL wherever l_end lets a width past that in.
  *   threshold       candidates need SNR strictly above it.
  *   flags           SPD_WRITE_PLANES | SPD_WRITE_CANDIDATES.
  *   segment         samples per work item along time (0 = chosen by the library).  Results do not

@@ -172,8 +172,9 @@ int build_search(const spd_params *p, Search *s) {
     if (s->levels.empty() || s->levels.size() > (size_t)kMaxLevels) return SPD_EINVAL;
     for (const Level &lv : s->levels) {
         if (lv.widths.empty()) return SPD_EINVAL;
+        // (a level's masks and scale tables have an entry for each unit count up to kMaxLevelWidths)
         if (p->method != SPD_EXHAUSTIVE &&
-            (lv.units.size() > (size_t)kMaxLevelWidths || lv.units.back() > 255))
+            (lv.units.size() > (size_t)kMaxLevelWidths || lv.units.back() > kMaxLevelWidths))
             return SPD_EINVAL;
         s->max_width = std::max(s->max_width, lv.widths.back());
     }

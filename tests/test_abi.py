@@ -352,3 +352,25 @@ def test_gated_plan_host_checks(lib):
     pn, kn = spd.Config("exh", 512, candidates=False).params()
     assert lib.spd_gated_plan(ctypes.byref(pl), ctypes.byref(pn), 40, 9000, 9000, 16, 4096,
                               ctypes.byref(b)) == spd.SPD_EINVAL
+
+
+@pytest.mark.parametrize("depth", [1, 2, 3, 4])
+def test_layers_beyond_the_unit_tables_are_refused(lib, depth):
+    """64 layers with a depth have widths of more than 64 units, which the masks and tables of a level do not
+    hold; every other number of layers keeps its widths, and so do 64 where no width is longer than 64 units."""
+    for l_end in (65, 100, 8192):
+        for planes in (True, False):
+            cfg = spd.Config("ig", l_end, igrid_depth=depth, igrid_layers=64, planes=planes)
+            if any(w > 64 << k for k, ws in ow.igrid_levels(depth, l_end, layers=64) for w in ws):
+                with pytest.raises(spd.SpdError) as e:
+                    spd.level_widths(cfg)
+                assert e.value.status == spd.SPD_EINVAL
+                with pytest.raises(spd.SpdError) as e:
+                    spd.plan(cfg, 2, 5000)
+                assert e.value.status == spd.SPD_EINVAL
+            else:
+                assert spd.level_widths(cfg) == [w for _, w in ow.igrid_levels(depth, l_end, layers=64)]
+    for l_end, P, d in ((64, 64, depth), (8192, 64, 0), (8192, 32, depth)):
+        cfg = spd.Config("ig", l_end, igrid_depth=d, igrid_layers=P)
+        assert spd.level_widths(cfg) == [w for _, w in ow.igrid_levels(d, l_end, layers=P)]
+        assert spd.plan(cfg, 2, 5000).n_levels == len(ow.igrid_levels(d, l_end, layers=P))
