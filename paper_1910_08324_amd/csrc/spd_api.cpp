@@ -219,6 +219,7 @@ struct Layout {
     // lossy, candidates only: directory and pool of the chunk records
     int64_t off_dir = -1, off_pool = -1, off_used = -1;
     int64_t pool_units = 0;
+    int form_units = 0;
     int64_t dir_off[kMaxLevels] = {0};
     int64_t scale_ld = 0;
 };
@@ -541,8 +542,16 @@ int make_layout(const spd_params *p, const Search &s, int32_t n_dm, int32_t n_in
             L->off_dir = take(entries * 4);
             L->off_pool = take(L->pool_units * 8);
             L->off_used = take(8);
+            L->form_units = spd::kFormUnits;
             for (StepPlan &st : L->steps)
-                for (int j = 0; j < st.J; ++j) st.lv[j].dir_off = L->dir_off[st.k0 + j];
+                for (int j = 0; j < st.J; ++j) {
+                    st.lv[j].dir_off = L->dir_off[st.k0 + j];
+                    // the window of one slot of the level (at most 4032: 64 units, sixth of a step)
+                    int len = st.lv[j].umax;
+                    for (int i = j - 1; i >= 0; --i)
+                        len = std::max(2 * len + st.lv[i + 1].cshift, st.lv[i].ufull);
+                    L->form_units = std::max(L->form_units, len);
+                }
         } else {
             // the exhaustive search is bound by arithmetic: its planes go to the workspace
             L->off_Y = take(I.plane_elems * 4);
@@ -848,6 +857,7 @@ spd::PeakArgs peak_args(const spd_params *params, const Prepared &P, int32_t n_d
         a.pool = reinterpret_cast<const uint64_t *>(P.ws + L.off_pool);
         for (int i = 0; i < I.n_levels; ++i) a.dir_off[i] = L.dir_off[i];
     }
+    a.form_units = L.form_units;
     if (L.off_rec >= 0) {
         a.rec = reinterpret_cast<const spd::RecStep *>(P.ws + L.off_rec);
         for (size_t si = 0; si < L.steps.size(); ++si)
@@ -1231,6 +1241,7 @@ int spd_batch_search(const spd_params *params, int32_t n_beams, const spd_beam *
     pb.n_groups = B.n_groups;
     pb.n_beams = n_beams;
     pb.records = B.L[0].off_dir >= 0;
+    pb.form_units = B.L[0].form_units;
     const int err = spd::launch_peaks_batch(pb, hip_stream);
     if (err) return hip_fail(err);
     return SPD_OK;

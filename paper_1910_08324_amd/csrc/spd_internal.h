@@ -30,6 +30,9 @@ constexpr int kPoolUnitsPerChunk = 3; // candidates only: room for records, in 8
 constexpr int kPoolUnitsPerSlab = 32; //   of a slab, and the most for one slab;
 constexpr int kPoolUnitsSmall = 1 << 18; //   in a small workspace 2 MiB, if all records can take that
 constexpr int kPoolCounterWords = 64; // a batch's pool counters lie 256 bytes apart
+// floats of a wave's window for forming slots again: 128 slots of a fourth level of IG(1..3) and BD-16
+// in one window (256 take the same time), and more waves a CU than their registers leave
+constexpr int kFormUnits = 1280;
 constexpr uint32_t kNoRecord = 0xffffffffu;   // a chunk above the threshold found no room for its record
 constexpr uint32_t kEmptyChunk = 0xfffffffeu; // nothing of the chunk is above the threshold
 
@@ -248,6 +251,7 @@ struct PeakArgs {
     const uint64_t *pool;
     int64_t dir_off[kMaxLevels];
     const RecStep *rec;
+    int32_t form_units;         // floats a wave has for forming slots again (form_slots)
     int8_t level_step[kMaxLevels];
     int8_t level_j[kMaxLevels];
     // tile gating: flag_mode 0 = every slot; 1 = candidates only in tiles whose flag is clear
@@ -279,6 +283,7 @@ struct PeakBatchArgs {
     int64_t n_groups;
     int32_t n_beams;
     int32_t records;          // slot values from the chunk records, not from planes
+    int32_t form_units;       // as PeakArgs::form_units, the same for every beam
 };
 int launch_peaks_batch(const PeakBatchArgs &a, void *stream);
 const char *hip_error_text(int err);

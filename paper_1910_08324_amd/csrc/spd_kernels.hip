@@ -1248,112 +1248,164 @@ __global__ __launch_bounds__(64, 6) void exh_kernel(const ExhArgs A) {
 constexpr int kPeakThreads = 256;
 constexpr int kPeakGroupWaves = kPeakThreads / 64;
 
-__device__ __forceinline__ float rec_in(const RecStep &R, const float *inr, float mu, float inv,
-                                        int64_t r) {
-    if (r >= R.in_len) return 0.0f;                   // the tile pads past the data with zeros
-    return R.normalise ? (inr[r] - mu) * inv : inr[r];
+// Slots m .. m + n - 1 (n <= 256) of level j of a step, row d, formed again by one wave: buf[i] receives
+// the SNR and buf[256 + i] the width of slot m + i.  As many slots at a time as the row's window of
+// the step's input has room for in buf (`units` floats, enough for one slot of any level): the window
+// is loaded once and goes down the levels in place, as in step_tile, each lane adding the carried
+// prefixes of its slots on the way.  A wave forms a chunk in the time that a lane on its own needs for a
+// slot, whose units it would have to form from 2^j samples each.  Both passes of the peak finder, 256 x
+// 131072 samples of noise with candidates only, where the records' room does not last, against slots
+// formed by the lanes that needed them: IG(1) at a threshold of 3 1821 -> 584 us.
+typedef __attribute__((address_space(4))) const RecStep *ConstRecPtr;
+typedef __attribute__((address_space(3))) float *LdsFloatPtr;
+
+__device__ __forceinline__ void wave_lds_order() {        // (a wave's LDS accesses are performed in order)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
 }
 
-// pairwise sum of the 2^J input units from a, in the cascade's order
-template <int J>
-__device__ __forceinline__ float rec_tree(const RecStep &R, const float *inr, float mu, float inv,
-                                          int64_t a) {
-    float v[1 << J];
-#pragma unroll
-    for (int i = 0; i < (1 << J); ++i) v[i] = rec_in(R, inr, mu, inv, a + i);
-#pragma unroll
-    for (int h = (1 << J); h > 1; h >>= 1) {
-#pragma unroll
-        for (int i = 0; i < h / 2; ++i) v[i] = v[2 * i] + v[2 * i + 1];
-    }
-    return v[0];
-}
-
-// unit n of level j of the step: y_j[n] = y_{j-1}[2n + cshift_j] + y_{j-1}[2n + cshift_j + 1]
-__device__ __noinline__ float rec_unit(const RecStep &R, const float *inr, float mu, float inv,
-                                       int j, int64_t n) {
-    int64_t a = n;
-    for (int i = j; i >= 1; --i) a = 2 * a + R.lv[i].cshift;
-    switch (j) {
-        case 0: return rec_in(R, inr, mu, inv, a);
-        case 1: return rec_tree<1>(R, inr, mu, inv, a);
-        case 2: return rec_tree<2>(R, inr, mu, inv, a);
-        case 3: return rec_tree<3>(R, inr, mu, inv, a);
-        default: break;
-    }
-    // levels 4 and 5 from sums of 8, pairwise as before (fewer registers than a tree of 32)
-    float s[2] = {0.0f, 0.0f};
-    const int halves = j == 4 ? 1 : 2;
-    for (int i = 0; i < halves; ++i)
-        s[i] = rec_tree<3>(R, inr, mu, inv, a + 16 * i) + rec_tree<3>(R, inr, mu, inv, a + 16 * i + 8);
-    return j == 4 ? s[0] : s[0] + s[1];
-}
-
-// Y and W of slot m (absolute) of level j of the step, row d
-__device__ __noinline__ float rec_slot(const RecStep &R, int d, int j, int64_t m, int *w_out) {
-    const float *inr = R.in + (int64_t)d * R.ld_in;
+__device__ __noinline__ void form_slots(const RecStep *rec, int d_, int j_, int m_, int n_, LdsFloatPtr buf_, int units_) {
+    // (the arguments are the same in every lane)
+    const int d = __builtin_amdgcn_readfirstlane(d_), j = __builtin_amdgcn_readfirstlane(j_);
+    const int m = __builtin_amdgcn_readfirstlane(m_), n = __builtin_amdgcn_readfirstlane(n_);
+    const int units = __builtin_amdgcn_readfirstlane(units_);
+    const LdsFloatPtr buf = (LdsFloatPtr)(uintptr_t)__builtin_amdgcn_readfirstlane((int)(uintptr_t)buf_);
+    const uint64_t rp = (uint64_t)rec;
+    const ConstRecPtr R = (ConstRecPtr)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(rp >> 32)) << 32) |
+                                        (uint32_t)__builtin_amdgcn_readfirstlane((int)rp));
+    const int lane = threadIdx.x & 63;
+    const float *inr = R->in + (int64_t)d * R->ld_in;
+    const int64_t in_len = R->in_len;
+    const bool norm = R->normalise != 0;
     float mu = 0.0f, inv = 1.0f;
-    if (R.normalise) {
-        mu = R.mean[d];
-        inv = 1.0f / R.sigma[d];
+    if (norm) {
+        mu = R->mean[d];
+        inv = 1.0f / R->sigma[d];
     }
-    const RecLevel &L = R.lv[j];
-    // carried prefix (BoxDIT): from the previous step's hand-off, then through levels 0..j-1,
-    // each adding its ufull units at the slot that leads to m
-    float X = 0.0f;
-    if (R.carry && (j > 0 || R.cin != nullptr)) {
-        const int64_t p0 = m << j;
-        if (R.cin && p0 < R.lv[0].slots) X = R.cin[(int64_t)d * R.ld_cin + p0];
-        for (int i = 0; i < j; ++i) {
-            const int64_t p = m << (j - i);
-            const int uf = R.lv[i].ufull;
-            for (int u = 0; u < uf; ++u) X += rec_unit(R, inr, mu, inv, i, p + u);
+    const auto *L = R->lv + j;
+    const int umax = L->umax, k = L->k, base = L->base;
+    const uint64_t emask = L->evalmask;
+    const bool carry = R->carry && (j > 0 || R->cin != nullptr);
+    int cs[kStepMaxLevels], uf[kStepMaxLevels], len[kStepMaxLevels];
+#pragma unroll
+    for (int i = 0; i < kStepMaxLevels; ++i) {
+        cs[i] = i > 0 && i <= j ? R->lv[i].cshift : 0;
+        uf[i] = i < j && carry ? R->lv[i].ufull : 0;
+    }
+    // units of level i that F slots of level j take; F: the most slots whose window fits
+    int F = 2 * kChunk;
+    do {
+        F >>= 1;
+        int l = F + umax - 1;
+#pragma unroll
+        for (int i = kStepMaxLevels - 1; i >= 0; --i) {
+            if (i < j) l = max(2 * l + cs[i + 1 < kStepMaxLevels ? i + 1 : i], ((F - 1) << (j - i)) + uf[i]);
+            len[i] = l;
+        }
+    } while (F > 1 && (len[0] > units || F >= 2 * n));
+    // this level's scales, one a lane
+    float rt = 0.0f;
+    if (lane < umax) {
+        rt = L->rt[lane];
+        if (R->rho) {
+            const double W = (double)base + ldexp((double)(lane + 1), k);
+            rt = (float)((double)rt / rho_of_width(R->rho + (int64_t)d * R->ld_rho, R->n_rho, W));
         }
     }
-    const float *rr = R.rho ? R.rho + (int64_t)d * R.ld_rho : nullptr;
-    const int64_t room = (int64_t)R.n_in - (m << L.k);
-    float best = SPD_NEG_INF;
-    int bu = 0;
-    for (int u = 0; u < L.umax; ++u) {
-        X += rec_unit(R, inr, mu, inv, j, m + u);
-        if ((L.evalmask >> u) & 1ull) {
-            float r = L.rt[u];
-            if (rr) {
-                const double Lw = (double)L.base + ldexp((double)(u + 1), L.k);
-                r = (float)((double)L.rt[u] / rho_of_width(rr, R.n_rho, Lw));
+    const int ends = (int)(((int64_t)R->n_in - base) >> k);   // U units from slot m fit: m + U <= ends
+    float best[kGroup];                                       // slots 64 p + lane
+    int bu[kGroup];
+#pragma unroll
+    for (int p = 0; p < kGroup; ++p) {
+        best[p] = SPD_NEG_INF;
+        bu[p] = 0;
+    }
+    for (int f = 0; f < n; f += F) {
+        const int64_t r0 = (int64_t)(m + f) << j;             // the window's first input unit
+        for (int i0 = lane; i0 - lane < len[0]; i0 += 4 * 64) {
+            float v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int64_t r = r0 + i0 + 64 * q;
+                v[q] = 0.0f;
+                if (i0 + 64 * q < len[0] && r < in_len) v[q] = inr[r];
             }
-            float v = X * r;
-            if ((int64_t)L.base + ((int64_t)(u + 1) << L.k) > room) v = SPD_NEG_INF;
-            if (v > best) {
-                best = v;
-                bu = u + 1;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)                       // (zero past the data)
+                if (i0 + 64 * q < len[0])
+                    buf[i0 + 64 * q] = norm && r0 + i0 + 64 * q < in_len ? (v[q] - mu) * inv : v[q];
+        }
+        float X[kGroup];
+        int at[kGroup];                                       // the lane's slots in the window (0: none)
+        bool on[kGroup];
+#pragma unroll
+        for (int p = 0; p < kGroup; ++p) {
+            const int i = 64 * p + lane - f;
+            on[p] = i >= 0 && i < F && f + i < n;
+            at[p] = on[p] ? i : 0;
+            X[p] = 0.0f;
+            const int64_t c = (int64_t)(m + f + at[p]) << j;
+            if (carry && R->cin && on[p] && c < R->lv[0].slots) X[p] = R->cin[(int64_t)d * R->ld_cin + c];
+        }
+        wave_lds_order();
+#pragma unroll
+        for (int i = 0; i + 1 < kStepMaxLevels; ++i) {
+            if (i >= j) continue;
+            for (int u = 0; u < uf[i]; ++u)
+#pragma unroll
+                for (int p = 0; p < kGroup; ++p) X[p] += buf[(at[p] << (j - i)) + u];
+            wave_lds_order();
+            for (int x = lane; x - lane < len[i + 1]; x += 64) {
+                float v = 0.0f;
+                if (x < len[i + 1]) v = buf[2 * x + cs[i + 1]] + buf[2 * x + cs[i + 1] + 1];
+                wave_lds_order();
+                if (x < len[i + 1]) buf[x] = v;
+                wave_lds_order();
             }
         }
+        for (int u = 0; u < umax; ++u) {
+#pragma unroll
+            for (int p = 0; p < kGroup; ++p) X[p] += buf[at[p] + u];
+            if ((emask >> u) & 1ull) {
+                const float r = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rt), u));
+#pragma unroll
+                for (int p = 0; p < kGroup; ++p) {
+                    const float v = X[p] * r;
+                    const bool gt = on[p] && m + f + at[p] + u + 1 <= ends && v > best[p];
+                    best[p] = gt ? v : best[p];
+                    bu[p] = gt ? u + 1 : bu[p];
+                }
+            }
+        }
+        wave_lds_order();
     }
-    *w_out = bu ? L.base + (bu << L.k) : 0;
-    return best;
+#pragma unroll
+    for (int p = 0; p < kGroup; ++p) {
+        buf[64 * p + lane] = best[p];
+        buf[kChunk + 64 * p + lane] = __int_as_float(bu[p] ? base + (bu[p] << k) : 0);
+    }
+    wave_lds_order();
 }
 
+// The helpers take the arguments, of the launch (one beam) or of a beam in a batch's table, in the
+// constant address space.
+typedef __attribute__((address_space(4))) const PeakArgs CPeakArgs;
 
-// The helpers take the arguments either from the launch (one beam) or from a per-beam table in
-// the constant address space (a batch); PA is the (qualified) PeakArgs type.
 // the chunk bits of tile t of level k in row d
-template <class PA>
-__device__ __forceinline__ uint32_t slab_word(PA &A, int k, int d, int t) {
+__device__ __forceinline__ uint32_t slab_word(CPeakArgs &A, int k, int d, int t) {
     return A.above[A.cnt_off[k] + ((int64_t)d * A.tiles_per_row[k] + t) * A.cnt_stride[k]];
 }
 
 // where the record of chunk c of tile t of level k in row d is (or kNoRecord, kEmptyChunk)
-template <class PA>
-__device__ __forceinline__ uint32_t chunk_record(PA &A, int k, int d, int t, int c) {
+__device__ __forceinline__ uint32_t chunk_record(CPeakArgs &A, int k, int d, int t, int c) {
     return A.dir[A.dir_off[k] + ((int64_t)d * A.tiles_per_row[k] + t) * A.cpt[k] + c];
 }
 
 // SNRs (and widths, if w is not null) of slots m0 .. m0 + 3 of level k in row d, slots m0 + 4 lane
 // of chunk c of tile t whose bit is set; slots past m_end are -inf.  From records, so are the
-// slots at or below the threshold.
-template <bool REC, class PA>
-__device__ __forceinline__ void chunk_values(PA &A, int k, int d, int t, int c, int lane, int m0,
+// slots at or below the threshold; true if the chunk has no record (nothing is set then).
+template <bool REC>
+__device__ __forceinline__ bool chunk_values(CPeakArgs &A, int k, int d, int t, int c, int lane, int m0,
                                              int m_end, float y[kGroup], int *w) {
 #pragma unroll
     for (int q = 0; q < kGroup; ++q) y[q] = SPD_NEG_INF;
@@ -1372,18 +1424,9 @@ __device__ __forceinline__ void chunk_values(PA &A, int k, int d, int t, int c, 
         }
         (void)w;                                   // (the scatter pass reads the widths it needs)
     } else {
-        const uint32_t off = chunk_record(A, k, d, t, c);
-        if (off == kEmptyChunk) return;
-        if (off == kNoRecord) {
-            const RecStep &R = A.rec[A.level_step[k]];
-            for (int q = 0; q < kGroup; ++q) {
-                if (m0 + q >= m_end) break;
-                int wq;
-                y[q] = rec_slot(R, d, A.level_j[k], m0 + q, &wq);
-                if (w) w[q] = wq;
-            }
-            return;
-        }
+        const uint32_t off = (uint32_t)__builtin_amdgcn_readfirstlane((int)chunk_record(A, k, d, t, c));
+        if (off == kEmptyChunk) return false;
+        if (off == kNoRecord) return true;
         const uint64_t *r = A.pool + off;
         const int word = lane >> 4, bit = (lane & 15) * kGroup;
         int pos = 0;
@@ -1406,12 +1449,13 @@ __device__ __forceinline__ void chunk_values(PA &A, int k, int d, int t, int c, 
             }
         }
     }
+    return false;
 }
 
 // SNR of slot m of level k in row d, -inf if its chunk's bit is clear (one lane on its own: the
-// slots beside a chunk)
-template <bool REC, class PA>
-__device__ __forceinline__ float slot_value(PA &A, int k, int d, int m) {
+// slots beside a chunk); missing: its chunk has no record
+template <bool REC>
+__device__ __forceinline__ float slot_value(CPeakArgs &A, int k, int d, int m, bool &missing) {
     const int ts = A.tile_slots[k];
     const int t = m / ts;
     const int i = m - t * ts;
@@ -1423,8 +1467,8 @@ __device__ __forceinline__ float slot_value(PA &A, int k, int d, int m) {
         const uint32_t off = chunk_record(A, k, d, t, c);
         if (off == kEmptyChunk) return SPD_NEG_INF;
         if (off == kNoRecord) {
-            int w;
-            return rec_slot(A.rec[A.level_step[k]], d, A.level_j[k], m, &w);
+            missing = true;
+            return SPD_NEG_INF;
         }
         const uint64_t *r = A.pool + off;
         const int b = i - c * kChunk;
@@ -1442,9 +1486,13 @@ __device__ __forceinline__ float slot_value(PA &A, int k, int d, int m) {
     }
 }
 
+// form_slots for slots of level k
+__device__ __forceinline__ void form_chunk(CPeakArgs &A, int k, int d, int m, int n, LdsFloatPtr form) {
+    form_slots(A.rec + A.level_step[k], d, A.level_j[k], m, n, form, A.form_units);
+}
+
 // tile gating of the candidates (flag_mode): may slot m of level k in row d be a candidate?
-template <class PA>
-__device__ __forceinline__ bool slot_kept(PA &A, int k, int d, int m) {
+__device__ __forceinline__ bool slot_kept(CPeakArgs &A, int k, int d, int m) {
     if (A.flag_mode == 0) return true;
     const int64_t s = (int64_t)m << A.level_shift[k];
     const bool f = A.tile_flag[(int64_t)(d / A.tile_rows) * A.n_col_tiles + s / A.tile_len] != 0;
@@ -1452,10 +1500,11 @@ __device__ __forceinline__ bool slot_kept(PA &A, int k, int d, int m) {
 }
 
 // The candidates of chunk c of tile t of level k in row d, whose bit is set: bit q of the result
-// for slot m0 + q of this lane.  y receives the slots' SNRs and, from records, w their widths.
-template <bool REC, class PA>
-__device__ __forceinline__ uint32_t chunk_test(PA &A, int k, int d, int t, int c, int lane, int &m0,
-                                               float y[kGroup], int w[kGroup]) {
+// for slot m0 + q of this lane.  y receives the slots' SNRs and, from records, w their widths.  Chunks
+// without a record, here or beside, are formed again (FORM) or end the test with `missing` set.
+template <bool REC, bool FORM>
+__device__ __forceinline__ uint32_t chunk_test(CPeakArgs &A, int k, int d, int t, int c, int lane, int &m0,
+                                               float y[kGroup], int w[kGroup], LdsFloatPtr form, bool &missing) {
     const int ts = A.tile_slots[k];
     const int slots = A.level_slots[k];
     const int m_end = min((t + 1) * ts, slots);
@@ -1464,17 +1513,39 @@ __device__ __forceinline__ uint32_t chunk_test(PA &A, int k, int d, int t, int c
     const int bit = c >> A.bit_shift[k];
     const bool up = d > 0 && ((slab_word(A, k, d - 1, t) >> bit) & 1u);
     const bool down = d + 1 < A.n_dm && ((slab_word(A, k, d + 1, t) >> bit) & 1u);
-    chunk_values<REC>(A, k, d, t, c, lane, m0, m_end, y, w);
+    int rows = chunk_values<REC>(A, k, d, t, c, lane, m0, m_end, y, w) ? 1 : 0;   // of d, d - 1, d + 1 without a record
     float yn[2][kGroup];
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int q = 0; q < kGroup; ++q) yn[a][q] = SPD_NEG_INF;
-    if (up) chunk_values<REC>(A, k, d - 1, t, c, lane, m0, m_end, yn[0], nullptr);
-    if (down) chunk_values<REC>(A, k, d + 1, t, c, lane, m0, m_end, yn[1], nullptr);
+    if (up && chunk_values<REC>(A, k, d - 1, t, c, lane, m0, m_end, yn[0], nullptr)) rows |= 2;
+    if (down && chunk_values<REC>(A, k, d + 1, t, c, lane, m0, m_end, yn[1], nullptr)) rows |= 4;
+    if constexpr (REC && !FORM) {
+        if (rows) {
+            missing = true;
+            return 0;
+        }
+    }
+    if constexpr (FORM) {
+#pragma unroll 1
+        for (int a = 0; a < 3; ++a) {
+            if (!((rows >> a) & 1)) continue;
+            form_chunk(A, k, a == 0 ? d : a == 1 ? d - 1 : d + 1, mc, min(kChunk, m_end - mc), form);
+#pragma unroll
+            for (int q = 0; q < kGroup; ++q) {                // (-inf past m_end)
+                const float v = form[kGroup * lane + q];
+                y[q] = a == 0 ? v : y[q];
+                yn[0][q] = a == 1 ? v : yn[0][q];
+                yn[1][q] = a == 2 ? v : yn[1][q];
+                if (a == 0) w[q] = __float_as_int(form[kChunk + kGroup * lane + q]);
+            }
+            wave_lds_order();
+        }
+    }
 
     // time neighbours outside this lane's four slots: the adjacent lanes', or the adjacent
-    // chunks' at either end (looked up only by a lane whose slot there is above the threshold)
+    // chunks' at either end (looked up only where the slot there is above the threshold)
     float l[3], r[3];
     l[0] = __shfl_up(yn[0][kGroup - 1], 1);
     l[1] = __shfl_up(y[kGroup - 1], 1);
@@ -1482,21 +1553,38 @@ __device__ __forceinline__ uint32_t chunk_test(PA &A, int k, int d, int t, int c
     r[0] = __shfl_down(yn[0][0], 1);
     r[1] = __shfl_down(y[0], 1);
     r[2] = __shfl_down(yn[1][0], 1);
-    if (lane == 0) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int dn = d + a - 1;
-            l[a] = (y[0] > A.threshold && m0 > 0 && dn >= 0 && dn < A.n_dm) ? slot_value<REC>(A, k, dn, m0 - 1)
-                                                                           : SPD_NEG_INF;
-        }
-    }
     const int last = min(mc + kChunk, (t + 1) * ts) - kGroup;   // first slot of the chunk's last lane
-    if (m0 == last) {
+    const bool at_left = __ballot(lane == 0 && y[0] > A.threshold) != 0 && mc > 0;
+    const bool at_right = __ballot(m0 == last && y[kGroup - 1] > A.threshold) != 0 && last + kGroup < slots;
+    if (lane == 0) l[0] = l[1] = l[2] = SPD_NEG_INF;
+    if (m0 == last) r[0] = r[1] = r[2] = SPD_NEG_INF;
+    if (at_left || at_right) {
+        // lanes 0 .. 2 look up the left ones in rows d - 1 .. d + 1, lanes 3 .. 5 the right ones
+        const int dn = d + (lane < 3 ? lane : lane - 3) - 1;
+        const int mn = lane < 3 ? mc - 1 : last + kGroup;
+        float v = SPD_NEG_INF;
+        bool none = false;
+        if (lane < 6 && (lane < 3 ? at_left : at_right) && dn >= 0 && dn < A.n_dm) v = slot_value<REC>(A, k, dn, mn, none);
+        if constexpr (REC && !FORM) {
+            if (__ballot(none)) {
+                missing = true;
+                return 0;
+            }
+        }
+        if constexpr (FORM) {
+#pragma unroll 1
+            for (uint64_t b = __ballot(none); b; b &= b - 1) {
+                const int i = __ffsll((unsigned long long)b) - 1;
+                form_chunk(A, k, d + (i < 3 ? i : i - 3) - 1, i < 3 ? mc - 1 : last + kGroup, 1, form);
+                if (lane == i) v = form[0];
+                wave_lds_order();
+            }
+        }
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            const int dn = d + a - 1;
-            r[a] = (y[kGroup - 1] > A.threshold && m0 + kGroup < slots && dn >= 0 && dn < A.n_dm)
-                       ? slot_value<REC>(A, k, dn, m0 + kGroup) : SPD_NEG_INF;
+            const float left = __shfl(v, a), right = __shfl(v, 3 + a);
+            if (lane == 0) l[a] = left;
+            if (m0 == last) r[a] = right;
         }
     }
     uint32_t hit = 0;
@@ -1516,43 +1604,21 @@ __device__ __forceinline__ uint32_t chunk_test(PA &A, int k, int d, int t, int c
 }
 
 // level of slab s
-template <class PA>
-__device__ __forceinline__ int slab_level(PA &A, int64_t s) {
+__device__ __forceinline__ int slab_level(CPeakArgs &A, int64_t s) {
     int k = 0;
     while (k + 1 < A.n_levels && s >= A.slab_base[k + 1]) ++k;
     return k;
 }
 
-// One group of slabs of a pass.  SCATTER false: count its candidates; true: write them.
-template <bool REC, bool SCATTER, class PA>
-__device__ __forceinline__ void peak_group(PA &A, int g) {
-    __shared__ int64_t part[kPeakGroupWaves];
-    __shared__ uint32_t cnt[2][kPeakGroupWaves];
+// The slabs [sbeg, send) of a group.  SCATTER false: `total` receives this wave's candidates; true: they
+// are written from entry `run` on.  Without FORM the count ends, returning true, at the first chunk
+// whose record is needed and missing.
+template <bool REC, bool SCATTER, bool FORM>
+__device__ __forceinline__ bool peak_items(CPeakArgs &A, int64_t sbeg, int64_t send, int64_t run, uint32_t &total,
+                                           uint32_t (*cnt)[kPeakGroupWaves], LdsFloatPtr form) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t sbeg = (int64_t)g * A.slabs_per_group;
-    const int64_t send = min(sbeg + A.slabs_per_group, A.n_slabs);
-    int64_t run = 0;                     // SCATTER: where the next candidate goes
-    if constexpr (SCATTER) {
-        const uint32_t mine = A.group_tot[g];
-        const bool last = g + 1 == A.n_groups;
-        if (mine == 0 && !last) return;
-        int64_t sum = 0;
-        for (int i = threadIdx.x; i < g; i += kPeakThreads) sum += A.group_tot[i];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-        if (lane == 0) part[wave] = sum;
-        __syncthreads();
-        run = *A.base_copy;
-#pragma unroll
-        for (int i = 0; i < kPeakGroupWaves; ++i) run += part[i];
-        if (last && threadIdx.x == 0) *A.cand_count = run + mine;
-        if (mine == 0) return;
-    } else {
-        // candidates already in the list (the scatter pass may overwrite the same count)
-        if (g == 0 && threadIdx.x == 0) *A.base_copy = A.base_count ? *A.base_count : 0;
-    }
-    uint32_t total = 0;                  // SCATTER false: this wave's candidates
+    total = 0;
     int turn = 0;
     for (int64_t sb = sbeg; sb < send; sb += 64) {
         const int64_t s = sb + lane;
@@ -1589,7 +1655,9 @@ __device__ __forceinline__ void peak_group(PA &A, int g) {
                 const uint32_t rs = (uint32_t)(sb + l - A.slab_base[k]);   // (rows x tiles fits 31 bits)
                 d = (int)(rs / (uint32_t)A.tiles_per_row[k]);
                 const int t = (int)(rs - (uint32_t)d * (uint32_t)A.tiles_per_row[k]);
-                if (c < A.cpt[k]) hit = chunk_test<REC>(A, k, d, t, c, lane, m0, y, w);
+                bool missing = false;
+                if (c < A.cpt[k]) hit = chunk_test<REC, FORM>(A, k, d, t, c, lane, m0, y, w, form, missing);
+                if (!SCATTER && missing) return true;
             }
             uint32_t n = 0;
             int pos = 0;
@@ -1628,11 +1696,62 @@ __device__ __forceinline__ void peak_group(PA &A, int g) {
             }
         }
     }
+    return false;
+}
+
+// One group of slabs of a pass.  SCATTER false: count its candidates; true: write them.  A group that
+// needs a record that is missing (kGroupForms in its total) runs again in a loop of its own, so that the
+// registers for forming slots again are not taken from the usual one.
+constexpr uint32_t kGroupForms = 1u << 31;
+template <bool REC, bool SCATTER>
+__device__ __forceinline__ void peak_group(CPeakArgs &A, int g) {
+    __shared__ int64_t part[kPeakGroupWaves];
+    __shared__ uint32_t cnt[2][kPeakGroupWaves];
+    extern __shared__ float form_lds[];  // REC: each wave's window of form_slots
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t sbeg = (int64_t)g * A.slabs_per_group;
+    const int64_t send = min(sbeg + A.slabs_per_group, A.n_slabs);
+    int64_t run = 0;                     // SCATTER: where the next candidate goes
+    uint32_t total = 0;                  // SCATTER false: this wave's candidates
+    bool again = false;                  // (the same in the whole work-group)
+    if constexpr (SCATTER) {
+        const uint32_t mine = A.group_tot[g];
+        const bool last = g + 1 == A.n_groups;
+        if ((mine & ~kGroupForms) == 0 && !last) return;
+        int64_t sum = 0;
+        for (int i = threadIdx.x; i < g; i += kPeakThreads) sum += A.group_tot[i] & ~kGroupForms;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+        if (lane == 0) part[wave] = sum;
+        __syncthreads();
+        run = *A.base_copy;
+#pragma unroll
+        for (int i = 0; i < kPeakGroupWaves; ++i) run += part[i];
+        if (last && threadIdx.x == 0) *A.cand_count = run + (mine & ~kGroupForms);
+        if ((mine & ~kGroupForms) == 0) return;
+        again = REC && (mine & kGroupForms) != 0;
+        if (!again) peak_items<REC, true, false>(A, sbeg, send, run, total, cnt, nullptr);
+    } else {
+        // candidates already in the list (the scatter pass may overwrite the same count)
+        if (g == 0 && threadIdx.x == 0) *A.base_copy = A.base_count ? *A.base_count : 0;
+        const bool missing = peak_items<REC, false, false>(A, sbeg, send, 0, total, cnt, nullptr);
+        if constexpr (REC) again = __syncthreads_or(missing) != 0;
+    }
+    if constexpr (REC) {
+        if (again) {
+            // (behind a pointer that hides where the arguments come from: see above)
+            CPeakArgs *P = &A;
+            asm volatile("" : "+s"(P));
+            const LdsFloatPtr form = (LdsFloatPtr)form_lds + wave * P->form_units;
+            peak_items<true, SCATTER, true>(*P, sbeg, send, run, total, cnt, form);
+        }
+    }
     if constexpr (!SCATTER) {
         if (lane == 0) cnt[0][wave] = total;
         __syncthreads();
         if (threadIdx.x == 0) {
-            uint32_t sum = 0;
+            uint32_t sum = again ? kGroupForms : 0u;
 #pragma unroll
             for (int i = 0; i < kPeakGroupWaves; ++i) sum += cnt[0][i];
             A.group_tot[g] = sum;
@@ -1642,14 +1761,13 @@ __device__ __forceinline__ void peak_group(PA &A, int g) {
 
 template <bool REC, bool SCATTER>
 __global__ __launch_bounds__(kPeakThreads) void peak_kernel(const PeakArgs A) {
-    peak_group<REC, SCATTER>(A, blockIdx.x);
+    (void)A;                             // (read from the kernel arguments' address)
+    peak_group<REC, SCATTER>(*(CPeakArgs *)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.x);
 }
 
 // Batched: the peak-finder arguments of every beam in a table in the constant address space
 // (read with scalar loads), the groups of all beams in one index space: group i belongs to beam b
 // with group_base[b] <= i < group_base[b + 1].  One launch per pass for the whole batch.
-typedef __attribute__((address_space(4))) const PeakArgs CPeakArgs;
-
 template <bool REC, bool SCATTER>
 __global__ __launch_bounds__(kPeakThreads) void peak_batch_kernel(const PeakBatchArgs B) {
     const ConstI64Ptr base = (ConstI64Ptr)B.group_base;
@@ -1815,7 +1933,8 @@ template <bool SCATTER>
 static int launch_peak_pass(const PeakArgs &a, hipStream_t st) {
     const dim3 grid((unsigned)a.n_groups);
     if (a.dir)
-        hipLaunchKernelGGL((peak_kernel<true, SCATTER>), grid, dim3(kPeakThreads), 0, st, a);
+        hipLaunchKernelGGL((peak_kernel<true, SCATTER>), grid, dim3(kPeakThreads),
+                           kPeakGroupWaves * a.form_units * 4, st, a);
     else
         hipLaunchKernelGGL((peak_kernel<false, SCATTER>), grid, dim3(kPeakThreads), 0, st, a);
     return (int)hipGetLastError();
@@ -1830,7 +1949,8 @@ template <bool SCATTER>
 static int launch_peak_batch_pass(const PeakBatchArgs &a, hipStream_t st) {
     const dim3 grid((unsigned)a.n_groups);
     if (a.records)
-        hipLaunchKernelGGL((peak_batch_kernel<true, SCATTER>), grid, dim3(kPeakThreads), 0, st, a);
+        hipLaunchKernelGGL((peak_batch_kernel<true, SCATTER>), grid, dim3(kPeakThreads),
+                           kPeakGroupWaves * a.form_units * 4, st, a);
     else
         hipLaunchKernelGGL((peak_batch_kernel<false, SCATTER>), grid, dim3(kPeakThreads), 0, st, a);
     return (int)hipGetLastError();

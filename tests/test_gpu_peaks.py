@@ -151,3 +151,30 @@ def test_last_slot_of_boxdit_levels(dev, planes, method, l_end, segment, step_le
                 ok = False
             assert ((i, d, m << k) in got) == ok, (i, k, slots, d, c, after[d])
     assert barred > 3
+
+
+@pytest.mark.parametrize("method,bound", [("ig1", 14.0), ("bd32", 45.0)])
+def test_slots_formed_again_by_whole_waves(dev, method, bound):
+    """At a threshold of 2 most chunks find no room for a record and their slots are formed again.  A wave
+    that forms a chunk together costs the peak finder a few times what reading planes costs (6 and 16 times
+    as measured); lanes that form their own slots one after another cost 23 and 136 times as much."""
+    from paper_1910_08324_amd import spd
+    g = torch.Generator(device=dev).manual_seed(5)
+    x = torch.randn((128, 65536), generator=g, device=dev)
+    mu, sg = torch.zeros(128, device=dev), torch.ones(128, device=dev)
+    ms, lists = [], []
+    for planes in (True, False):
+        r = spd.Runner(x, mu, sg, spd.Config(method, 4096, threshold=2.0, planes=planes), cand_cap=1 << 21)
+        r.search()
+        best = np.inf
+        for _ in range(5):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            r.peaks()
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]))
+        ms.append(best)
+        lists.append(r.result.candidates_host())
+    assert np.array_equal(*lists) and len(lists[0]) > 100000
+    assert ms[1] <= bound * ms[0], ms
