@@ -218,7 +218,8 @@ struct Layout {
     int64_t off_rec = -1;     // records of the cascade steps (lossy, candidates only)
     // lossy, candidates only: directory and pool of the chunk records
     int64_t off_dir = -1, off_pool = -1, off_used = -1;
-    int64_t pool_units = 0;
+    int64_t pool_units = 0;   // of each part
+    int pool_parts = 1;
     int form_units = 0;
     int64_t dir_off[kMaxLevels] = {0};
     int64_t scale_ld = 0;
@@ -539,9 +540,12 @@ int make_layout(const spd_params *p, const Search &s, int32_t n_dm, int32_t n_in
             if (ws < (int64_t)32 << 20)
                 L->pool_units = std::max(L->pool_units, std::min<int64_t>(every, spd::kPoolUnitsSmall));
             L->pool_units = std::min<int64_t>(L->pool_units, 0x7fffffff);
+            while (L->pool_parts < spd::kPoolPartsMax && L->pool_units >= (int64_t)2 * L->pool_parts * spd::kPoolPartUnits)
+                L->pool_parts *= 2;
+            L->pool_units /= L->pool_parts;
             L->off_dir = take(entries * 4);
-            L->off_pool = take(L->pool_units * 8);
-            L->off_used = take(8);
+            L->off_pool = take(L->pool_units * L->pool_parts * 8);
+            L->off_used = take(L->pool_parts * spd::kPoolCounterWords * 4);
             L->form_units = spd::kFormUnits;
             for (StepPlan &st : L->steps)
                 for (int j = 0; j < st.J; ++j) {
@@ -699,8 +703,8 @@ int run_filter(const spd_params *params, const Prepared &P, const float *x, int6
     if (P.L.off_used >= 0) {
         // candidates only: the pool of chunk records is empty (this clearing is not one of the
         // filter's listed launches)
-        const int err = spd::launch_fill_u32(reinterpret_cast<uint32_t *>(P.ws + P.L.off_used), 2, 0u,
-                                             hip_stream);
+        const int err = spd::launch_fill_u32(reinterpret_cast<uint32_t *>(P.ws + P.L.off_used),
+                                             P.L.pool_parts * spd::kPoolCounterWords, 0u, hip_stream);
         if (err) return hip_fail(err);
     }
     if (const int err = mark()) return hip_fail(err);
@@ -743,6 +747,7 @@ int run_filter(const spd_params *params, const Prepared &P, const float *x, int6
                 a.pool = reinterpret_cast<uint64_t *>(P.ws + L.off_pool);
                 a.pool_used = reinterpret_cast<unsigned long long *>(P.ws + L.off_used);
                 a.pool_units = (uint32_t)L.pool_units;
+                a.pool_mask = (uint32_t)L.pool_parts - 1;
             }
             const int err = spd::launch_step(a, s.fam, st.lds_bytes, hip_stream);
             if (err) return hip_fail(err);
@@ -895,7 +900,8 @@ struct BatchPlan {
     std::vector<Layout> L;
     std::vector<int64_t> ws_off;
     int64_t ws_total = 0;
-    int64_t used_off = 0;       // candidates only: the beams' pool counters, apart
+    int64_t used_off = 0;       // candidates only: the beams' pool counters, together
+    std::vector<int64_t> used;  // beams' first counters there, and how many in all
     int64_t table_bytes = 0;
     int64_t base_off = 0;       // offset of the item_base arrays in the table
     int64_t peak_off = 0;       // offset of the per-beam peak-finder arguments
@@ -929,7 +935,10 @@ int batch_plan(const spd_params *params, int32_t n_beams, const spd_beam *beams,
     }
     B->n_steps = (int)B->L[0].steps.size();
     B->used_off = off;
-    if (B->L[0].off_used >= 0) off += (int64_t)n_beams * spd::kPoolCounterWords * 4;
+    B->used.assign(1, 0);
+    for (int b = 0; b < n_beams; ++b)
+        B->used.push_back(B->used.back() + (B->L[b].off_used >= 0 ? B->L[b].pool_parts : 0));
+    off += B->used.back() * spd::kPoolCounterWords * 4;
     B->ws_total = off;
     B->base_off = round_up((int64_t)B->n_steps * n_beams * (int64_t)sizeof(spd::BeamView), 256);
     B->peak_off = round_up(B->base_off + (int64_t)B->n_steps * (n_beams + 1) * 8, 256);
@@ -971,8 +980,9 @@ spd::BeamView beam_view(const spd_params *params, const BatchPlan &B, const spd_
         v.dir = reinterpret_cast<uint32_t *>(ws + L.off_dir);
         v.pool = reinterpret_cast<uint64_t *>(ws + L.off_pool);
         v.pool_used = reinterpret_cast<unsigned long long *>(ws_base + B.used_off +
-                                                             (int64_t)b * spd::kPoolCounterWords * 4);
+                                                             B.used[b] * spd::kPoolCounterWords * 4);
         v.pool_units = (uint32_t)L.pool_units;
+        v.pool_mask = (uint32_t)L.pool_parts - 1;
     }
     for (int j = 0; j < st.J; ++j) {
         v.dir_off[j] = st.lv[j].dir_off;
@@ -1216,7 +1226,7 @@ int spd_batch_search(const spd_params *params, int32_t n_beams, const spd_beam *
     if (B.L[0].off_used >= 0) {
         const int err = spd::launch_fill_u32(
             reinterpret_cast<uint32_t *>(static_cast<char *>(workspace) + B.used_off),
-            (int64_t)n_beams * spd::kPoolCounterWords, 0u, hip_stream);
+            B.used.back() * spd::kPoolCounterWords, 0u, hip_stream);
         if (err) return hip_fail(err);
     }
     for (int si = 0; si < B.n_steps; ++si) {

@@ -29,7 +29,13 @@ constexpr int kPeakGroupsWanted = 4096;   // ... which grow to 64 (a wave's reac
 constexpr int kPoolUnitsPerChunk = 3; // candidates only: room for records, in 8-byte units per chunk
 constexpr int kPoolUnitsPerSlab = 32; //   of a slab, and the most for one slab;
 constexpr int kPoolUnitsSmall = 1 << 18; //   in a small workspace 2 MiB, if all records can take that
-constexpr int kPoolCounterWords = 64; // a batch's pool counters lie 256 bytes apart
+constexpr int kPoolCounterWords = 64; // pool counters lie 256 bytes apart
+// A beam's pool is cut into parts (a power of two) with a counter each, which the tiles use in turn: at
+// low thresholds nearly every chunk asks, and the atomics on one counter, some 5 ns each, took longer
+// than the cascade (256 x 131072 samples of noise, IG(1) to 512 at a threshold of 2.5: all cascade
+// launches 2712 us with one counter, 218 with 16).
+constexpr int kPoolPartsMax = 64;
+constexpr int kPoolPartUnits = 1 << 15; // a part holds more than a bright pulse takes in the tiles that share it
 // floats of a wave's window for forming slots again: 128 slots of a fourth level of IG(1..3) and BD-16
 // in one window (256 take the same time), and more waves a CU than their registers leave
 constexpr int kFormUnits = 1280;
@@ -123,8 +129,10 @@ struct StepArgs {
     // chunk is above), then {SNR, width} of each set bit in order
     uint32_t *dir;
     uint64_t *pool;
-    unsigned long long *pool_used;   // units asked for (may exceed pool_units: the rest has no record)
-    uint32_t pool_units;
+    // Work-group i takes room from part i & pool_mask: units [pool_units part, pool_units (part + 1)).
+    unsigned long long *pool_used;   // units asked of each part (may exceed pool_units: the rest has no record)
+    uint32_t pool_units;             // of a part
+    uint32_t pool_mask;
     // BoxDIT with look-ahead samples (else -1): the last slot of the step's first level whose carry
     // is formed.  The slot after a level's last one (see edge) needs the carries of the slots that
     // lead to it, which lie past the planes' ends: slot s of level k from s 2^i of level k - i.
@@ -148,7 +156,7 @@ struct BeamView {
     uint8_t *edge;
     int64_t ld_in, ld_cin, ld_out;
     int32_t n_dm, n_in, in_len, n_tiles;
-    uint32_t pool_units;
+    uint32_t pool_units, pool_mask;
     RecStep *rec;               // the beam's record of this step (candidates only), or null
     uint32_t *dir;              // the beam's chunk records (candidates only), or null
     uint64_t *pool;
@@ -159,7 +167,6 @@ struct BeamView {
     int64_t pitch[kStepMaxLevels];
     int32_t slots[kStepMaxLevels];
     int32_t carry_end;          // as StepArgs::carry_end
-    int32_t pad0;
 };
 
 struct StepBatchArgs {

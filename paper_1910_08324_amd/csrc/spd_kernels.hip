@@ -292,6 +292,7 @@ struct ArgGeom {
     __device__ uint64_t *pool() const { return P->pool; }
     __device__ unsigned long long *pool_used() const { return P->pool_used; }
     __device__ uint32_t pool_units() const { return P->pool_units; }
+    __device__ uint32_t pool_mask() const { return P->pool_mask; }
     __device__ int carry_end() const { return P->carry_end; }
     __device__ int64_t plane_off(int j) const { return P->lv[j].plane_off; }
     __device__ int64_t pitch(int j) const { return P->lv[j].pitch; }
@@ -332,6 +333,7 @@ struct TabGeom {
     __device__ uint64_t *pool() const { return V->pool; }
     __device__ unsigned long long *pool_used() const { return V->pool_used; }
     __device__ uint32_t pool_units() const { return V->pool_units; }
+    __device__ uint32_t pool_mask() const { return V->pool_mask; }
     __device__ int carry_end() const { return V->carry_end; }
     __device__ int64_t plane_off(int j) const { return V->plane_off[j]; }
     __device__ int64_t pitch(int j) const { return V->pitch[j]; }
@@ -343,10 +345,10 @@ struct TabGeom {
 // Candidates only: the record of a wave's chunk (its 64 groups of kGroup slots): the chunk's slots
 // above the threshold with their SNRs and widths, so that the peak finder reads values instead of
 // forming them again.  `left`: plane slots from this lane's first one on; `write`: the chunk exists
-// in the tile.  Records take their room from one pool per beam; a chunk that finds none is marked and
-// the peak finder forms its slots again.  Returns whether any slot is above.
-__device__ __forceinline__ bool put_record(uint64_t *pool, unsigned long long *used, uint32_t units, uint32_t *dir,
-                                           bool write, int lane, int left, float threshold,
+// in the tile.  Records take their room from part `part` of the beam's pool, `units` long; a chunk that
+// finds none is marked and the peak finder forms its slots again.  Returns whether any slot is above.
+__device__ __forceinline__ bool put_record(uint64_t *pool, unsigned long long *used, uint32_t part, uint32_t units,
+                                           uint32_t *dir, bool write, int lane, int left, float threshold,
                                            const float best[kGroup], const int bu[kGroup], int k,
                                            int base) {
     uint32_t nib = 0;
@@ -366,8 +368,8 @@ __device__ __forceinline__ bool put_record(uint64_t *pool, unsigned long long *u
         const uint32_t need = kChunk / 64 + total;
         if (lane == 0) {
             // (64 bits: every chunk of a search may ask, also when the pool is full)
-            const unsigned long long at = atomicAdd(used, (unsigned long long)need);
-            off = at + need <= units ? (uint32_t)at : kNoRecord;
+            const unsigned long long at = atomicAdd(used + part * (kPoolCounterWords / 2), (unsigned long long)need);
+            off = at + need <= units ? part * units + (uint32_t)at : kNoRecord;
         }
         off = (uint32_t)__builtin_amdgcn_readfirstlane((int)off);
         if (off != kNoRecord) {
@@ -466,8 +468,9 @@ __device__ __forceinline__ void step_chunk(const G V, int j, int d, int tile, in
     }
     bool set = any;
     if constexpr (!W) {
-        const int64_t di = V.dir_off(j) + ((int64_t)d * V.n_tiles() + tile) * L->cpt + chunk;
-        set = put_record(V.pool(), V.pool_used(), V.pool_units(), V.dir() + di, chunk < L->cpt, lane,
+        const int item = d * V.n_tiles() + tile;
+        const int64_t di = V.dir_off(j) + (int64_t)item * L->cpt + chunk;
+        set = put_record(V.pool(), V.pool_used(), (uint32_t)item & V.pool_mask(), V.pool_units(), V.dir() + di, chunk < L->cpt, lane,
                          slots - ma, A->threshold, best, bu, L->k, L->base);
     }
     if (set && lane == 0) atomicOr(&st_cnt[j], 1u << (chunk >> L->bit_shift));
