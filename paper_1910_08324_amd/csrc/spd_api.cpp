@@ -511,41 +511,44 @@ int make_layout(const spd_params *p, const Search &s, int32_t n_dm, int32_t n_in
     // the exhaustive kernel's masked tail group reads up to kExhGroup entries past the tables;
     // with a sigma table every row has its own
     L->scale_ld = (!lossy && p->rho) ? (int64_t)L->n_scale + spd::kExhGroup : 0;
-    L->off_scale = take(((int64_t)L->n_scale + spd::kExhGroup) * 4 * (L->scale_ld ? n_dm : 1));
-    L->off_mask = take(s.dense ? 4 : (ceil_div(s.l_end, 32) + 4) * 4);
+    if (!lossy) {
+        L->off_scale = take(((int64_t)L->n_scale + spd::kExhGroup) * 4 * (L->scale_ld ? n_dm : 1));
+        L->off_mask = take(s.dense ? 4 : (ceil_div(s.l_end, 32) + 4) * 4);
+    }
     L->off_above = take(L->n_slabs * 4);
-    L->off_tot = take((int64_t)L->n_groups * 4);
-    L->off_base = take(8);
+    L->off_base = take(8 + (int64_t)L->n_groups * 4);
+    L->off_tot = L->off_base + 8;
     if (n_out < n_in) L->off_edge = take((int64_t)nlev * n_dm);
     if (!(p->flags & SPD_WRITE_PLANES)) {
         if (lossy) {
             // candidates only: no planes anywhere; the cascade leaves a record of every chunk with
-            // a slot above the threshold.  The pool holds 3 units per chunk, at most 32 per slab (a
-            // record takes 4 and one per slot above: room for about half of all chunks, where noise
-            // at 5 sigma needs one in a hundred).  A single pulse can cover most of a small
-            // block: it gets 2 MiB at least, or room for every slot (up to a workspace of 32 MiB, so
-            // that a search that fits a fixed scratch buffer still does).  The slots of a chunk that
-            // finds no room are formed again by the peak finder from the step's record, which takes
-            // far longer than to read it (4 x 4096 slots BD-32 with one long bright pulse: 871 us
-            // without the 2 MiB, 86 with).
+            // a slot above the threshold (4 units and one per slot above).  The pool holds 3 units per
+            // chunk, at most 32 per slab, where noise at 5 sigma needs one unit for twenty chunks.  In
+            // a small block, where few slabs share it and forming slots again is what a search waits
+            // for, it holds 32 units per slab and one for two chunks: all that 272 bytes a slab and 4
+            // per 128 slots, which lists of candidates once took, have room for (16 x 16384 samples
+            // of noise at a threshold of 3: IG(1) 106 -> 82 us, BD-32 344 -> 133).  The slots of a chunk
+            // that finds no room, as most do in such a block under one bright pulse, are formed again
+            // by the peak finder from the step's record.
             L->off_rec = take((int64_t)L->steps.size() * (int64_t)sizeof(spd::RecStep));
-            int64_t entries = 0, every = 0;
+            int64_t entries = 0, small = 0;
             for (int k = 0; k < nlev; ++k) {
                 const int64_t slabs = (int64_t)n_dm * L->tiles_per_row[k];
                 L->dir_off[k] = entries;
-                every += slabs * L->cpt[k] * (spd::kChunk / 64 + spd::kChunk);
                 entries += slabs * L->cpt[k];
                 L->pool_units += slabs * std::min(spd::kPoolUnitsPerChunk * L->cpt[k], spd::kPoolUnitsPerSlab);
+                small += slabs * (spd::kPoolUnitsPerSlab + L->cpt[k] / 2);
             }
             if (ws < (int64_t)32 << 20)
-                L->pool_units = std::max(L->pool_units, std::min<int64_t>(every, spd::kPoolUnitsSmall));
+                L->pool_units = std::max(L->pool_units, std::min<int64_t>(small, spd::kPoolUnitsSmall));
             L->pool_units = std::min<int64_t>(L->pool_units, 0x7fffffff);
             while (L->pool_parts < spd::kPoolPartsMax && L->pool_units >= (int64_t)2 * L->pool_parts * spd::kPoolPartUnits)
                 L->pool_parts *= 2;
-            L->pool_units /= L->pool_parts;
+            // (the parts' counters take their room from it)
+            L->pool_units = L->pool_units / L->pool_parts - (L->pool_parts > 1 ? spd::kPoolCounterWords / 2 : 0);
             L->off_dir = take(entries * 4);
             L->off_pool = take(L->pool_units * L->pool_parts * 8);
-            L->off_used = take(L->pool_parts * spd::kPoolCounterWords * 4);
+            L->off_used = take(L->pool_parts * spd::kPoolCounterWords * 4);   // (the last: see batch_plan)
             L->form_units = spd::kFormUnits;
             for (StepPlan &st : L->steps)
                 for (int j = 0; j < st.J; ++j) {
@@ -931,7 +934,8 @@ int batch_plan(const spd_params *params, int32_t n_beams, const spd_beam *beams,
                 S[i].lds_bytes != S0[i].lds_bytes)
                 return SPD_EINVAL;
         B->ws_off[b] = off;
-        off += round_up(B->L[b].info.workspace_bytes, 256);
+        // (the beams' pool counters lie together behind their workspaces: one launch clears them)
+        off += B->L[b].off_used >= 0 ? B->L[b].off_used : round_up(B->L[b].info.workspace_bytes, 256);
     }
     B->n_steps = (int)B->L[0].steps.size();
     B->used_off = off;

@@ -28,7 +28,7 @@ constexpr int kPeakGroupSlabs = 4;    // fewest (level, row, tile) slabs of one 
 constexpr int kPeakGroupsWanted = 4096;   // ... which grow to 64 (a wave's reach) beyond this many groups
 constexpr int kPoolUnitsPerChunk = 3; // candidates only: room for records, in 8-byte units per chunk
 constexpr int kPoolUnitsPerSlab = 32; //   of a slab, and the most for one slab;
-constexpr int kPoolUnitsSmall = 1 << 18; //   in a small workspace 2 MiB, if all records can take that
+constexpr int kPoolUnitsSmall = 1 << 18; //   small blocks up to 2 MiB of 32 units per slab and one for two chunks
 constexpr int kPoolCounterWords = 64; // pool counters lie 256 bytes apart
 // A beam's pool is cut into parts (a power of two) with a counter each, which the tiles use in turn: at
 // low thresholds nearly every chunk asks, and the atomics on one counter, some 5 ns each, took longer

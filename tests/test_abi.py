@@ -374,3 +374,31 @@ def test_layers_beyond_the_unit_tables_are_refused(lib, depth):
         cfg = spd.Config("ig", l_end, igrid_depth=d, igrid_layers=P)
         assert spd.level_widths(cfg) == [w for _, w in ow.igrid_levels(d, l_end, layers=P)]
         assert spd.plan(cfg, 2, 5000).n_levels == len(ow.igrid_levels(d, l_end, layers=P))
+
+
+# (method, n_dm, n_in, n_out, l_end, bytes) and (method, beams, n_dm, n_in, bytes): what candidates-only plans
+# took before their records had a pool
+CANDIDATE_WORKSPACES = [
+    ("ig1", 16, 4096, 4096, 512, 61952), ("ig1", 8, 5003, 5003, 512, 52736), ("ig1", 64, 16384, 16384, 1024, 737536),
+    ("bd32", 8, 5003, 5003, 512, 62976), ("bd16", 64, 65536, 65000, 4096, 3616000), ("ig3", 1, 257, 257, 64, 4864),
+    ("bd8", 4, 4096, 4000, 1533, 23296), ("ig2", 512, 131072, 131072, 8192, 41508864),
+    ("bd32", 512, 131072, 131072, 8192, 56800512), ("ig1", 4096, 262144, 262144, 8192, 659937280),
+    ("dit", 3, 333, 300, 300, 16128)]
+CANDIDATE_BATCHES = [("ig1", 1024, 8, 5003, 54001664), ("bd16", 64, 64, 16384, 57950208), ("bd32", 5, 3, 700, 56320)]
+
+
+def test_candidates_only_workspaces_do_not_grow(lib):
+    """A buffer that held a candidates-only search, single or batched, still does: the records' pool, which takes
+    the place of lists of a fixed room per tile, makes no workspace larger."""
+    for m, n_dm, n, n_out, l_end, before in CANDIDATE_WORKSPACES:
+        info = spd.plan(spd.Config(m, l_end, planes=False), n_dm, n, n_out)
+        assert 0.5 * before < info.workspace_bytes <= before, (m, n_dm, n)
+    lib = spd._bind_batch(lib)
+    for m, beams, n_dm, n, before in CANDIDATE_BATCHES:
+        arr = (spd.Beam * beams)()
+        for b in arr:
+            b.n_dm, b.n_in, b.n_out = n_dm, n, n
+        p, keep = spd.Config(m, 512, planes=False).params()
+        ws, tab = ctypes.c_int64(), ctypes.c_int64()
+        assert lib.spd_batch_plan(ctypes.byref(p), beams, arr, ctypes.byref(ws), ctypes.byref(tab)) == spd.SPD_OK
+        assert 0.5 * before < ws.value <= before, (m, beams, n_dm, n)
