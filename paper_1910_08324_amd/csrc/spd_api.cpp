@@ -311,7 +311,8 @@ int plan_step(const Search &s, int k0, int J, int T, StepPlan *st) {
 int make_layout(const spd_params *p, const Search &s, int32_t n_dm, int32_t n_in, int32_t n_out,
                 Layout *L, int64_t ref_out = 0) {
     if (n_dm < 1 || n_in < 1 || n_out < 1 || n_out > n_in) return SPD_EINVAL;
-    if (ref_out <= 0) ref_out = n_out;
+    const bool batch = ref_out > 0;
+    if (!batch) ref_out = n_out;
     if (p->rho && (p->n_rho < 1 || p->n_rho > SPD_MAX_LEVELS)) return SPD_EINVAL;
     if (!p->rho && p->n_rho != 0) return SPD_EINVAL;
     if ((int64_t)n_in > (int64_t)INT32_MAX - (1 << 20)) return SPD_EINVAL;
@@ -500,12 +501,19 @@ int make_layout(const spd_params *p, const Search &s, int32_t n_dm, int32_t n_in
         }
     }
     // groups of the peak finder: enough that a bright pulse's run of chunks is spread over many, few
-    // enough that each can add up the totals of those before it.  With 4 slabs at least against 16:
-    // 256 x 131072 slots BD-32, 16 rows of them above the threshold throughout, 940 -> 658 us (from
-    // records and formed again 37.3 -> 9.3 ms); no block without such rows is slower.
-    L->slabs_per_group = (int)std::max<int64_t>(
-        std::min<int64_t>(64, std::max<int64_t>(spd::kPeakGroupSlabs, ceil_div(L->n_slabs, spd::kPeakGroupsWanted))),
-        ceil_div(L->n_slabs, spd::kPeakGroups));
+    // enough that each can add up the totals of those before it.  Single slabs while they are few: a
+    // small block's groups leave most of the GPU idle, and its pulse lies in few of them (16 x 16384
+    // samples, IG(1): pulse over half a row 81 us with groups of 4, 55 single; noise at a threshold
+    // of 3 with candidates only 118 and 82).  A batch of small beams fills the GPU with groups of 4: 64
+    // beams of 64 x 16384 306 us, 498 with single slabs.
+    const int few = lossy && !(p->flags & SPD_WRITE_PLANES) ? spd::kPeakGroupsRecords : spd::kPeakGroupsPlanes;
+    auto group_slabs = [&](int64_t least) {
+        return std::max<int64_t>(
+            std::min<int64_t>(64, std::max<int64_t>(least, ceil_div(L->n_slabs, spd::kPeakGroupsWanted))),
+            ceil_div(L->n_slabs, spd::kPeakGroups));
+    };
+    const int64_t alone = group_slabs(std::min<int64_t>(spd::kPeakGroupSlabs, ceil_div(L->n_slabs, few)));
+    L->slabs_per_group = (int)(batch ? group_slabs(spd::kPeakGroupSlabs) : alone);
     L->n_groups = (int)ceil_div(L->n_slabs, L->slabs_per_group);
 
     // the exhaustive kernel's masked tail group reads up to kExhGroup entries past the tables;
@@ -516,7 +524,7 @@ int make_layout(const spd_params *p, const Search &s, int32_t n_dm, int32_t n_in
         L->off_mask = take(s.dense ? 4 : (ceil_div(s.l_end, 32) + 4) * 4);
     }
     L->off_above = take(L->n_slabs * 4);
-    L->off_base = take(8 + (int64_t)L->n_groups * 4);
+    L->off_base = take(8 + ceil_div(L->n_slabs, alone) * 4);   // (a beam's room is that of its search alone)
     L->off_tot = L->off_base + 8;
     if (n_out < n_in) L->off_edge = take((int64_t)nlev * n_dm);
     if (!(p->flags & SPD_WRITE_PLANES)) {

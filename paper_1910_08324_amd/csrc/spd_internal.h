@@ -24,8 +24,10 @@ constexpr int kExhItemsPerWave = 4;   // work items per wave when every width fi
 constexpr int kEdgeMaxima = 64;       // see StepArgs::edge
 constexpr int kExhEdgeMaxima = 16;
 constexpr int kPeakGroups = 16384;    // most work-groups of a peak-finder pass
-constexpr int kPeakGroupSlabs = 4;    // fewest (level, row, tile) slabs of one of them (one a wave) ...
-constexpr int kPeakGroupsWanted = 4096;   // ... which grow to 64 (a wave's reach) beyond this many groups
+constexpr int kPeakGroupsPlanes = 190;    // groups of a small block: single (level, row, tile) slabs up to here
+constexpr int kPeakGroupsRecords = 1024;  //   (candidates only: to here),
+constexpr int kPeakGroupSlabs = 4;    // up to this many slabs a group beyond (one a wave), which a batch always
+constexpr int kPeakGroupsWanted = 4096;   // takes, growing to 64 (a wave's reach) beyond this many groups
 constexpr int kPoolUnitsPerChunk = 3; // candidates only: room for records, in 8-byte units per chunk
 constexpr int kPoolUnitsPerSlab = 32; //   of a slab, and the most for one slab;
 constexpr int kPoolUnitsSmall = 1 << 18; //   small blocks up to 2 MiB of 32 units per slab and one for two chunks

@@ -1548,7 +1548,7 @@ __device__ __forceinline__ uint32_t chunk_test(CPeakArgs &A, int k, int d, int t
     }
 
     // time neighbours outside this lane's four slots: the adjacent lanes', or the adjacent
-    // chunks' at either end (looked up only where the slot there is above the threshold)
+    // chunks' at either end (looked up only where the slot there passes the test without them)
     float l[3], r[3];
     l[0] = __shfl_up(yn[0][kGroup - 1], 1);
     l[1] = __shfl_up(y[kGroup - 1], 1);
@@ -1557,10 +1557,23 @@ __device__ __forceinline__ uint32_t chunk_test(CPeakArgs &A, int k, int d, int t
     r[1] = __shfl_down(y[0], 1);
     r[2] = __shfl_down(yn[1][0], 1);
     const int last = min(mc + kChunk, (t + 1) * ts) - kGroup;   // first slot of the chunk's last lane
-    const bool at_left = __ballot(lane == 0 && y[0] > A.threshold) != 0 && mc > 0;
-    const bool at_right = __ballot(m0 == last && y[kGroup - 1] > A.threshold) != 0 && last + kGroup < slots;
     if (lane == 0) l[0] = l[1] = l[2] = SPD_NEG_INF;
     if (m0 == last) r[0] = r[1] = r[2] = SPD_NEG_INF;
+    uint32_t hit = 0;
+#pragma unroll
+    for (int q = 0; q < kGroup; ++q) {
+        const float v = y[q];
+        const float ul = q > 0 ? yn[0][q - 1] : l[0], ur = q + 1 < kGroup ? yn[0][q + 1] : r[0];
+        const float sl = q > 0 ? y[q - 1] : l[1], sr = q + 1 < kGroup ? y[q + 1] : r[1];
+        const float dl = q > 0 ? yn[1][q - 1] : l[2], dr = q + 1 < kGroup ? yn[1][q + 1] : r[2];
+        const bool ok = v > A.threshold && v > ul && v > yn[0][q] && v > ur && v > sl && v >= sr &&
+                        v >= dl && v >= yn[1][q] && v >= dr;
+        if (ok && slot_kept(A, k, d, m0 + q) &&
+            !(m0 + q + 1 == slots && A.edge_on[k] && A.edge[(int64_t)k * A.n_dm + d]))
+            hit |= 1u << q;
+    }
+    const bool at_left = __ballot(lane == 0 && (hit & 1u)) != 0 && mc > 0;
+    const bool at_right = __ballot(m0 == last && (hit >> (kGroup - 1))) != 0 && last + kGroup < slots;
     if (at_left || at_right) {
         // lanes 0 .. 2 look up the left ones in rows d - 1 .. d + 1, lanes 3 .. 5 the right ones
         const int dn = d + (lane < 3 ? lane : lane - 3) - 1;
@@ -1583,25 +1596,10 @@ __device__ __forceinline__ uint32_t chunk_test(CPeakArgs &A, int k, int d, int t
                 wave_lds_order();
             }
         }
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const float left = __shfl(v, a), right = __shfl(v, 3 + a);
-            if (lane == 0) l[a] = left;
-            if (m0 == last) r[a] = right;
-        }
-    }
-    uint32_t hit = 0;
-#pragma unroll
-    for (int q = 0; q < kGroup; ++q) {
-        const float v = y[q];
-        const float ul = q > 0 ? yn[0][q - 1] : l[0], ur = q + 1 < kGroup ? yn[0][q + 1] : r[0];
-        const float sl = q > 0 ? y[q - 1] : l[1], sr = q + 1 < kGroup ? y[q + 1] : r[1];
-        const float dl = q > 0 ? yn[1][q - 1] : l[2], dr = q + 1 < kGroup ? yn[1][q + 1] : r[2];
-        const bool ok = v > A.threshold && v > ul && v > yn[0][q] && v > ur && v > sl && v >= sr &&
-                        v >= dl && v >= yn[1][q] && v >= dr;
-        if (ok && slot_kept(A, k, d, m0 + q) &&
-            !(m0 + q + 1 == slots && A.edge_on[k] && A.edge[(int64_t)k * A.n_dm + d]))
-            hit |= 1u << q;
+        const float ul = __shfl(v, 0), sl = __shfl(v, 1), dl = __shfl(v, 2);
+        const float ur = __shfl(v, 3), sr = __shfl(v, 4), dr = __shfl(v, 5);
+        if (lane == 0 && !(y[0] > ul && y[0] > sl && y[0] >= dl)) hit &= ~1u;
+        if (m0 == last && !(y[kGroup - 1] > ur && y[kGroup - 1] >= sr && y[kGroup - 1] >= dr)) hit &= ~(1u << (kGroup - 1));
     }
     return hit;
 }

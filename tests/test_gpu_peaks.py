@@ -202,3 +202,25 @@ def test_records_of_many_chunks(dev):
             best = min(best, e[0].elapsed_time(e[1]))
         ms.append(best)
     assert ms[1] <= 8.0 * ms[0], ms
+
+
+@pytest.mark.parametrize("slabs", [1, 189, 190, 191, 380, 381, 1023, 1025, 2049, 4099])
+def test_lists_do_not_depend_on_groups(dev, slabs):
+    """One level and tiles of 256 slots, so a row is a slab: at every step of the slabs a group takes (which
+    differ with planes, candidates only and in a batch) the list is the same, and follows the rules."""
+    from paper_1910_08324_amd import spd
+    x, mu, sg = make_input(slabs, 256, 81, pulses=[synth.Pulse(slabs // 2, 120, 3, 20.0)])
+    x[::5, 250:] += 3.0
+    kw = dict(method="ig1", l_end=4, threshold=3.0)
+    (n0, ref), (n1, rec) = lists(dev, x, mu, sg, 256, 1, **kw)
+    assert n0 == n1 == len(ref) > 0 and np.array_equal(ref, rec)
+    t = [torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to(dev) for a in (x, mu, sg)]
+    small = [a[:3] for a in t]
+    for planes in (True, False):
+        b = spd.Batch([small, t, small], spd.Config(segment=256, step_levels=1, planes=planes, **kw), cand_cap=1 << 16)
+        b.search()
+        torch.cuda.synchronize()
+        assert np.array_equal(b.results[1].candidates_host(), ref)
+        assert np.array_equal(b.results[0].candidates_host(), b.results[2].candidates_host())
+    R = oplanes.planes(x, mu, sg, ow.method_levels("ig1", 4))
+    parity.check_candidates(ref, R, 3.0, what="groups")
