@@ -840,6 +840,7 @@ spd::PeakArgs peak_args(const spd_params *params, const Prepared &P, int32_t n_d
     a.above = reinterpret_cast<const uint32_t *>(P.ws + L.off_above);
     a.group_tot = reinterpret_cast<uint32_t *>(P.ws + L.off_tot);
     a.edge = L.off_edge >= 0 ? reinterpret_cast<const uint8_t *>(P.ws + L.off_edge) : nullptr;
+    a.edge_maxima = L.steps.empty() ? spd::kExhEdgeMaxima : spd::kEdgeMaxima;
     a.base_copy = reinterpret_cast<int64_t *>(P.ws + L.off_base);
     a.cand = cand;
     a.cand_cap = cand_cap;

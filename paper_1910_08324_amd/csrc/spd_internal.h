@@ -21,7 +21,7 @@ constexpr int kExhGroup = 64;         // widths bounded together (evaluated in g
 constexpr int kExhBoundFrom = 256;    // widths up to here are always evaluated
 constexpr int kChunk = 256;           // slots the peak finder tests together (64 lanes x kGroup)
 constexpr int kExhItemsPerWave = 4;   // work items per wave when every width fits one block
-constexpr int kEdgeMaxima = 64;       // see StepArgs::edge
+constexpr int kEdgeMaxima = 64;       // see PeakArgs::edge
 constexpr int kExhEdgeMaxima = 16;
 constexpr int kPeakGroups = 16384;    // most work-groups of a peak-finder pass
 constexpr int kPeakGroupsPlanes = 190;    // groups of a small block: single (level, row, tile) slabs up to here
@@ -102,10 +102,8 @@ struct StepArgs {
     uint16_t *W;
     uint32_t *above;          // chunk bits of every (level, row, tile)
     // With look-ahead samples (n_out < n_in, else null) the search evaluates the slots after a
-    // plane's last one that share its group of kGroup slots (its 256, exhaustive search).  The last
-    // slot of a row is a candidate only if it is not below the one after it, except where its tile
-    // has more than kEdgeMaxima (kExhEdgeMaxima) local maxima above the threshold at that level:
-    // edge[level n_dm + d] = 1 bars it.  Those are the lists that the search has always given.
+    // plane's last one that share its group of kGroup slots (its 256, exhaustive search), and says in
+    // edge[level n_dm + d] whether the last slot of row d is below the one after it.
     uint8_t *edge;
     int64_t ld_in, ld_cin, ld_out;
     int32_t n_dm;
@@ -244,7 +242,12 @@ struct PeakArgs {
     int32_t tile_slots[kMaxLevels];
     int32_t cpt[kMaxLevels];
     int32_t bit_shift[kMaxLevels];
-    const uint8_t *edge;      // as StepArgs::edge; read at the levels where it was written:
+    // StepArgs::edge, at the levels where it is written (edge_on).  The last slot of a row is not a
+    // candidate if it is below the slot after it, except where its tile has more than edge_maxima
+    // (kEdgeMaxima; exhaustive search, kExhEdgeMaxima) local maxima in time above the threshold at
+    // that level, counted by chunks: those are the lists that the search has always given.
+    const uint8_t *edge;
+    int32_t edge_maxima;
     int8_t edge_on[kMaxLevels];
     int64_t slab_base[kMaxLevels + 1];
     int64_t level_pitch[kMaxLevels];

@@ -426,12 +426,12 @@ __device__ __forceinline__ void write_rec(const StepArgs &A, const G &V, RecStep
     }
 }
 
-// What the peak finder gets of one chunk (a wave's 64 groups from gw on) of level j: its bit in
-// the tile's word, its record (candidates only) and the comparison at the row's end.  Runs for the
-// few chunks with a slot above the threshold, and evaluates them once more from the windows in LDS,
-// so that the width sets' registers need not live across it.  V hides where its fields come from
-// (see opaque()), so that none of its loads and address arithmetic moves into the tile's main path.
-template <bool W, bool RHO, class G>
+// Candidates only: what the peak finder gets of one chunk (a wave's 64 groups from gw on) of level j:
+// its bit in the tile's word and its record.  Runs for the few chunks with a slot above the threshold,
+// and evaluates them once more from the windows in LDS, so that the width sets' registers need not live
+// across it.  V hides where its fields come from (see opaque()), so that none of its loads and address
+// arithmetic moves into the tile's main path.
+template <bool RHO, class G>
 __device__ __forceinline__ void step_chunk(const G V, int j, int d, int tile, int gw, bool any,
                                            float *lds, uint32_t *st_cnt) {
     const ConstArgsPtr A = V.args();
@@ -444,8 +444,6 @@ __device__ __forceinline__ void step_chunk(const G V, int j, int d, int tile, in
     const int m0 = min(g, ngroups - 1) * kGroup;
     const int slots = V.slots(j);
     const int ma = tile * Sj + m0;
-    const bool edge = V.edge() && (slots % kGroup) && tile == (slots - 1) / Sj;
-    const bool act = any && g < ngroups && ma < slots;
     float best[kGroup];
     int bu[kGroup];
 #pragma unroll
@@ -453,7 +451,7 @@ __device__ __forceinline__ void step_chunk(const G V, int j, int d, int tile, in
         best[q] = SPD_NEG_INF;
         bu[q] = 0;
     }
-    if ((!W || edge) && act) {
+    if (any && g < ngroups && ma < slots) {
         const bool has_carry = A->carry && (j > 0 || V.cin() != nullptr);
         const float *c = lds + A->lv[0].lds_c + m0;
         float X[kGroup];
@@ -466,32 +464,11 @@ __device__ __forceinline__ void step_chunk(const G V, int j, int d, int tile, in
         else
             bank_record(lds + A->lv[0].lds_y + m0, (ConstFloatPtr)A->rtab[j], L->umax, L->evalmask, room, X, best, bu);
     }
-    bool set = any;
-    if constexpr (!W) {
-        const int item = d * V.n_tiles() + tile;
-        const int64_t di = V.dir_off(j) + (int64_t)item * L->cpt + chunk;
-        set = put_record(V.pool(), V.pool_used(), (uint32_t)item & V.pool_mask(), V.pool_units(), V.dir() + di, chunk < L->cpt, lane,
-                         slots - ma, A->threshold, best, bu, L->k, L->base);
-    }
+    const int item = d * V.n_tiles() + tile;
+    const int64_t di = V.dir_off(j) + (int64_t)item * L->cpt + chunk;
+    const bool set = put_record(V.pool(), V.pool_used(), (uint32_t)item & V.pool_mask(), V.pool_units(), V.dir() + di,
+                                chunk < L->cpt, lane, slots - ma, A->threshold, best, bu, L->k, L->base);
     if (set && lane == 0) atomicOr(&st_cnt[j], 1u << (chunk >> L->bit_shift));
-    if (any && edge) {
-        // the row's last slot against the evaluated slot after it (see StepArgs::edge)
-        float left = __shfl_up(best[kGroup - 1], 1);
-        float right = __shfl_down(best[0], 1);
-        if (lane == 0) left = SPD_NEG_INF;
-        if (lane == 63) right = SPD_NEG_INF;
-        uint32_t maxima = 0;
-#pragma unroll
-        for (int q = 0; q < kGroup; ++q) {
-            const float l = q > 0 ? best[q - 1] : left;
-            const float r = q + 1 < kGroup ? best[q + 1] : right;
-            const bool in = act && ma + q < slots;
-            maxima += (uint32_t)__popcll(__ballot(in && best[q] > A->threshold && best[q] > l && best[q] >= r));
-            if (q + 1 < kGroup && in && ma + q + 1 == slots && !(best[q] >= r))
-                st_cnt[2 * kStepMaxLevels + j] = 1;
-        }
-        if (lane == 0) atomicAdd(&st_cnt[kStepMaxLevels + j], maxima);
-    }
 }
 
 // One tile (DM row d, tile `tile`) of a cascade launch.  A holds what every beam of the launch
@@ -520,7 +497,7 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
     constexpr int kCarry = (FAM >= 4 && FAM <= 6) ? 1 : (FAM == 0 ? -1 : 0);
     const bool carry = kCarry < 0 ? (A.carry != 0) : (kCarry == 1);
     const int64_t u0 = (int64_t)tile * T;
-    if (tid < 3 * kStepMaxLevels) st_cnt[tid] = 0;
+    if (tid < kStepMaxLevels) st_cnt[tid] = 0;
     if (d == 0 && tile == 0 && V.rec()) write_rec<NTH>(A, V, V.rec());
 
     // ---- 1. window of the input series (normalised in the first step) and carried prefixes
@@ -724,6 +701,14 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
                                     rowW[m0 + q] = (uint16_t)(bu[q] ? base + (bu[q] << k) : 0);
                                 }
                         }
+                        if (A.want_cand && act && ma + kGroup > slots && V.edge()) {
+                            // the row's last slot against the evaluated slot after it
+                            bool below = false;
+#pragma unroll
+                            for (int q = 0; q + 1 < kGroup; ++q)
+                                if (ma + q + 1 == slots) below = !(best[q] >= best[q + 1]);
+                            V.edge()[(int64_t)k * V.n_dm() + d] = below;
+                        }
                         if (cg) {
                             // the last level's longest boxcar is the next step's carried prefix
                             cg[(m0 >> 1) + 0] = xc0;
@@ -732,8 +717,12 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
                     }
                     any = __ballot(act && fmaxf(fmaxf(best[0], best[1]), fmaxf(best[2], best[3])) > A.threshold) != 0;
                 }
-                if (A.want_cand && (any || (!W && L.bit_shift)))
-                    step_chunk<W, RHO>(V.opaque(), j, d, tile, gw, any, lds, st_cnt);
+                if constexpr (W) {
+                    if (A.want_cand && any && tid == wave0) atomicOr(&st_cnt[j], 1u << ((gw >> 6) >> L.bit_shift));
+                } else {
+                    if (A.want_cand && (any || L.bit_shift))
+                        step_chunk<RHO>(V.opaque(), j, d, tile, gw, any, lds, st_cnt);
+                }
             }
             if (sync_batches) {
                 lds_barrier();                   // the batch's reads of level j are done
@@ -775,9 +764,6 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
         // the tile's chunk bits of all its levels side by side (one short write per work-group)
         if (tid < A.J)
             V.above()[V.cnt_off(tid) + ((int64_t)d * V.n_tiles() + tile) * A.J] = st_cnt[tid];
-        if (tid < A.J && V.edge() && (V.slots(tid) % kGroup) && tile == (V.slots(tid) - 1) / (T >> tid))
-            V.edge()[(int64_t)A.lv[tid].k * V.n_dm() + d] =
-                st_cnt[2 * kStepMaxLevels + tid] && st_cnt[kStepMaxLevels + tid] <= (uint32_t)kEdgeMaxima;
     }
 }
 
@@ -804,7 +790,7 @@ __global__ __launch_bounds__(NTH, (Fam<FAM>::WAVES)) void step_kernel(const Step
     // of 16, every float4 access of a tile was misaligned, and LDS, busy 95% of the cycles, bounded
     // every width set; now 15%: 1024 x 131072 BD-16 1000 -> 909 us, IG(2) with a sigma table 696 -> 553)
     extern __shared__ __attribute__((aligned(16))) float lds[];
-    __shared__ uint32_t st_cnt[3 * kStepMaxLevels];
+    __shared__ uint32_t st_cnt[kStepMaxLevels];
     const int i = (int)xcd_order(blockIdx.x, (int64_t)A.n_dm * A.n_tiles);
     const int d = i / A.n_tiles;
     const int tile = i - d * A.n_tiles;
@@ -818,7 +804,7 @@ __global__ __launch_bounds__(NTH, (Fam<FAM>::WAVES)) void step_kernel(const Step
 template <bool FIRST, int FAM, bool W>
 __global__ __launch_bounds__(kStepThreads, (Fam<FAM>::WAVES)) void step_kernel_batch(const StepBatchArgs B) {
     extern __shared__ __attribute__((aligned(16))) float lds[];
-    __shared__ uint32_t st_cnt[3 * kStepMaxLevels];
+    __shared__ uint32_t st_cnt[kStepMaxLevels];
     const ConstBeamPtr beams = (ConstBeamPtr)B.beams;
     const ConstI64Ptr base = (ConstI64Ptr)B.item_base;
     int b = -1;
@@ -1194,23 +1180,11 @@ __global__ __launch_bounds__(64, 6) void exh_kernel(const ExhArgs A) {
         const bool any = __ballot(on) != 0;
         if (lane == 0) A.above[(int64_t)d * A.n_seg + g] = any ? 1u : 0u;
         if (A.edge && g + 1 == A.n_seg && A.n_out % kExhSlots) {
-            // the row's last slot against the evaluated slot after it (see StepArgs::edge)
-            float left = __shfl_up(best[3], 1);
-            float right = __shfl_down(best[0], 1);
-            if (lane == 0) left = SPD_NEG_INF;
-            if (lane == 63) right = SPD_NEG_INF;
-            int maxima = 0;
-            bool below = false;
+            // the row's last slot against the evaluated slot after it (not in lane 63's last)
+            const float right = __shfl_down(best[0], 1);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float l = v > 0 ? best[v - 1] : left;
-                const float r = v < 3 ? best[v + 1] : right;
-                const bool in = m0 + v < A.n_out;
-                maxima += __popcll(__ballot(in && best[v] > A.threshold && best[v] > l && best[v] >= r));
-                below = below || (m0 + v + 1 == A.n_out && !(best[v] >= r));
-            }
-            const bool blocked = __ballot(below) != 0 && maxima <= kExhEdgeMaxima;
-            if (lane == 0) A.edge[d] = blocked;
+            for (int v = 0; v < 4; ++v)
+                if (m0 + v + 1 == A.n_out) A.edge[d] = !(best[v] >= (v < 3 ? best[v + 1] : right));
         }
     }
     if (fetch) {
@@ -1502,6 +1476,41 @@ __device__ __forceinline__ bool slot_kept(CPeakArgs &A, int k, int d, int m) {
     return A.flag_mode == 2 ? f : !f;
 }
 
+// Local maxima in time above the threshold in tile t of level k in row d, but for the row's last slot: a
+// chunk on its own, with nothing on either side of it (see PeakArgs::edge).
+template <bool REC, bool FORM>
+__device__ __forceinline__ int tile_maxima(CPeakArgs &A, int k, int d, int t, int lane, LdsFloatPtr form,
+                                           bool &missing) {
+    const int slots = A.level_slots[k], ts = A.tile_slots[k], sh = A.bit_shift[k];
+    const int m_end = min((t + 1) * ts, slots);
+    const uint32_t word = slab_word(A, k, d, t);
+    int n = 0;
+    for (int c = 0; c < A.cpt[k] && n <= A.edge_maxima; ++c) {
+        if (!((word >> (c >> sh)) & 1u)) continue;
+        const int mc = t * ts + c * kChunk, m0 = mc + kGroup * lane;
+        float y[kGroup];
+        if (chunk_values<REC>(A, k, d, t, c, lane, m0, m_end, y, nullptr)) {
+            if constexpr (FORM) {
+                form_chunk(A, k, d, mc, min(kChunk, m_end - mc), form);
+#pragma unroll
+                for (int q = 0; q < kGroup; ++q) y[q] = form[kGroup * lane + q];
+                wave_lds_order();
+            } else {
+                missing = true;
+                return 0;
+            }
+        }
+        const float left = __shfl_up(y[kGroup - 1], 1), right = __shfl_down(y[0], 1);
+#pragma unroll
+        for (int q = 0; q < kGroup; ++q) {
+            const float l = q > 0 ? y[q - 1] : lane ? left : SPD_NEG_INF;
+            const float r = q + 1 < kGroup ? y[q + 1] : lane < 63 ? right : SPD_NEG_INF;
+            n += __popcll(__ballot(y[q] > A.threshold && y[q] > l && y[q] >= r && m0 + q + 1 != slots));
+        }
+    }
+    return n;
+}
+
 // The candidates of chunk c of tile t of level k in row d, whose bit is set: bit q of the result
 // for slot m0 + q of this lane.  y receives the slots' SNRs and, from records, w their widths.  Chunks
 // without a record, here or beside, are formed again (FORM) or end the test with `missing` set.
@@ -1568,9 +1577,7 @@ __device__ __forceinline__ uint32_t chunk_test(CPeakArgs &A, int k, int d, int t
         const float dl = q > 0 ? yn[1][q - 1] : l[2], dr = q + 1 < kGroup ? yn[1][q + 1] : r[2];
         const bool ok = v > A.threshold && v > ul && v > yn[0][q] && v > ur && v > sl && v >= sr &&
                         v >= dl && v >= yn[1][q] && v >= dr;
-        if (ok && slot_kept(A, k, d, m0 + q) &&
-            !(m0 + q + 1 == slots && A.edge_on[k] && A.edge[(int64_t)k * A.n_dm + d]))
-            hit |= 1u << q;
+        if (ok && slot_kept(A, k, d, m0 + q)) hit |= 1u << q;
     }
     const bool at_left = __ballot(lane == 0 && (hit & 1u)) != 0 && mc > 0;
     const bool at_right = __ballot(m0 == last && (hit >> (kGroup - 1))) != 0 && last + kGroup < slots;
@@ -1600,6 +1607,14 @@ __device__ __forceinline__ uint32_t chunk_test(CPeakArgs &A, int k, int d, int t
         const float ur = __shfl(v, 3), sr = __shfl(v, 4), dr = __shfl(v, 5);
         if (lane == 0 && !(y[0] > ul && y[0] > sl && y[0] >= dl)) hit &= ~1u;
         if (m0 == last && !(y[kGroup - 1] > ur && y[kGroup - 1] >= sr && y[kGroup - 1] >= dr)) hit &= ~(1u << (kGroup - 1));
+    }
+    if (A.edge_on[k]) {
+        const int q = slots - 1 - m0;                     // the row's last slot in this lane
+        const bool ends = q >= 0 && q < kGroup && ((hit >> q) & 1u) && A.edge[(int64_t)k * A.n_dm + d];
+        if (__ballot(ends)) {
+            const bool many = tile_maxima<REC, FORM>(A, k, d, t, lane, form, missing) > A.edge_maxima;
+            if (ends && !many) hit &= ~(1u << q);
+        }
     }
     return hit;
 }

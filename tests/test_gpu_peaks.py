@@ -224,3 +224,30 @@ def test_lists_do_not_depend_on_groups(dev, slabs):
         assert np.array_equal(b.results[0].candidates_host(), b.results[2].candidates_host())
     R = oplanes.planes(x, mu, sg, ow.method_levels("ig1", 4))
     parity.check_candidates(ref, R, 3.0, what="groups")
+
+
+@pytest.mark.parametrize("method,l_end", [("bd32", 1024), ("ig3", 1024)])
+def test_lookahead_costs_the_filter_nothing(dev, method, l_end):
+    """A small block of a dense set, planes and candidates: with look-ahead samples (and fewer slots) the filter
+    takes no longer than without, give or take a tenth (evaluating the chunks at the rows' ends again, one
+    width after another, made it 1.9 times as long)."""
+    from paper_1910_08324_amd import spd
+    g = torch.Generator(device=dev).manual_seed(7)
+    n_dm, n = 16, 16384
+    x = torch.randn((n_dm, n), generator=g, device=dev)
+    x[:, n - 3 * l_end:] += 0.5                      # chunks above the threshold at every level's end
+    mu, sg = torch.zeros(n_dm, device=dev), torch.ones(n_dm, device=dev)
+    runs = [spd.Runner(x, mu, sg, spd.Config(method, l_end, threshold=4.0), n_out=n_out) for n_out in (n, n - l_end + 1)]
+    best = [np.inf, np.inf]
+    for r in runs:
+        r.filter()
+    for _ in range(20):
+        for i, r in enumerate(runs):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            for _ in range(10):
+                r.filter()
+            e[1].record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], e[0].elapsed_time(e[1]) / 10)
+    assert best[1] <= 1.1 * best[0], best
