@@ -596,6 +596,11 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
     // batches per barrier are slower now (batch 2245 and 2630 us).
     constexpr int kNW = (kGroup + Fam<FAM>::U1 - 1 + 3) / 4;
     constexpr bool kOnePattern = FAM == 0 || (Fam<FAM>::M1 == Fam<FAM>::M2 && Fam<FAM>::U1 == Fam<FAM>::U2);
+    // A wave that reaches past the plane with every width in the data (look-ahead samples) runs the
+    // compiled-in bank too in the densest sets, whose generic bank is what a small launch waits for
+    // (16 x 16384 samples, planes: BD-32 65 -> 55 us, IG(3) 52 -> 47; with BD-16 also 49 -> 46, but 1024 x
+    // 131072 samples then take 676 -> 680, and IG(1)'s beam 3304 -> 3314).
+    constexpr bool kPastEnd = Fam<FAM>::U1 >= 30;
     const int jtop = A.has_out ? A.J : A.J - 1;
     float *ybuf = lds + A.lv[0].lds_y;
     float *cbuf = lds + A.lv[0].lds_c;
@@ -690,7 +695,19 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
                             for (int q = 0; q < kGroup; ++q) X[q] = cbuf[m0 + q];
                         }
                         float Xc[kGroup] = {0.0f, 0.0f, 0.0f, 0.0f};
-                        bank_generic<W>(y, rt, umax, L.evalmask, L.ufull, ends - ma, X, Xc, best, bu);
+                        if (kPastEnd && L.pattern != 0 &&
+                            min(gw + 64, ngroups) <= ((ends - umax + 1 - ms0) >> 2)) {
+                            float w[4 * kNW];
+                            window_load<kNW>(y, w);
+                            if (kOnePattern || (FIRST && j == 0))
+                                bank_fixed<Fam<FAM>::U1, Fam<FAM>::M1, W>(w, rt, X, best, bu);
+                            else
+                                bank_fixed<Fam<FAM>::U2, Fam<FAM>::M2, W>(w, rt, X, best, bu);
+#pragma unroll
+                            for (int q = 0; q < kGroup; ++q) Xc[q] = X[q];
+                        } else {
+                            bank_generic<W>(y, rt, umax, L.evalmask, L.ufull, ends - ma, X, Xc, best, bu);
+                        }
                         xc0 = Xc[0];
                         xc1 = Xc[2];
                         if (W) {
