@@ -23,6 +23,13 @@
  * implemented): on each level plane, slot (d, m) is a candidate iff Y > threshold and, for each
  * in-bounds neighbour (d+a, m+b), a, b in {-1,0,1}, Y > Y_nb if the neighbour precedes (d, m) in
  * row-major order and Y >= Y_nb if it follows.  Candidates are ordered by (level, dm, start).
+ * With look-ahead samples (n_out < n_in) the last slot of a row is also held against the slot after
+ * it, which the search evaluates though it is not in the plane, where plane_slots of the level is no
+ * multiple of 4 (exhaustive search: of 256): it is no candidate if it is below that slot.  This
+ * does not apply where its tile has more than 64 local maxima in time above the threshold at that level
+ * (exhaustive search: its 256 slots more than 16), a maximum being a slot of the plane above the
+ * threshold, above the slot before it and not below the slot after it, each run of 256 slots from the
+ * tile's start taken alone; there, and only there, a row's last candidate depends on the tile length.
  *
  * Conventions
  *   - Every function returns SPD_OK (0) or a negative status; nothing throws across the ABI.
@@ -82,7 +89,7 @@ extern "C" {
  *   threshold       candidates need SNR strictly above it.
  *   flags           SPD_WRITE_PLANES | SPD_WRITE_CANDIDATES.
  *   segment         samples per work item along time (0 = chosen by the library).  Results do not
- *                   depend on it.  BoxDIT / IGRID: a multiple of 256 in 256..32768 that leaves
+ *                   depend on it (but see the candidate rule for a row's last slot).  BoxDIT / IGRID: a multiple of 256 in 256..32768 that leaves
  *                   every launch of the level cascade room for its halo and its on-chip buffers
  *                   (spd_plan returns SPD_EINVAL otherwise); exhaustive: 256, or 512 / 1024 (a wave
  *                   takes 2 / 4 consecutive 256-sample items) when L_end <= 512.

@@ -5,9 +5,9 @@
  * samples) searched with the same BoxDIT or IGRID parameters (Sections 3.1, 3.2 of Adamek &
  * Armour, arXiv:1910.08324).  Every cascade step of the search runs as ONE kernel launch over all
  * beams: a persistent grid walks the (beam, DM row, tile) work items of the whole batch; each
- * pass of the peak finder is likewise one launch over the waves of every beam.  Every beam's
- * planes and candidates are bitwise identical to those of spd_search on that beam alone with the
- * same parameters.
+ * pass of the peak finder is likewise one launch over every beam.  Every beam's planes and candidates
+ * are bitwise identical to those of spd_search on that beam alone with the same parameters (but for a
+ * row's last slot, where the candidate rule of spd.h lets it depend on the tile length).
  *
  * Use:
  *   1. spd_batch_plan: workspace and descriptor-table sizes.

@@ -251,3 +251,31 @@ def test_lookahead_costs_the_filter_nothing(dev, method, l_end):
             torch.cuda.synchronize()
             best[i] = min(best[i], e[0].elapsed_time(e[1]) / 10)
     assert best[1] <= 1.1 * best[0], best
+
+
+@pytest.mark.parametrize("planes", [True, False])
+@pytest.mark.parametrize("method,segment,limit,where", [
+    ("ig1", 0, 64, 4096), ("ig1", 256, 64, 256), ("bd4", 1024, 64, 1024), ("exh", 0, 16, 256)])
+def test_many_maxima_lift_the_bar_on_the_last_slot(dev, planes, method, segment, limit, where):
+    """The last slot of a row, below the evaluated slot after it, is barred up to `limit` local maxima above the
+    threshold in its tile (of `where` slots) and a candidate beyond, whatever lies in the other tiles."""
+    from paper_1910_08324_amd import spd
+    n_out, n = 3 * 1024 + 1021, 4200
+    tile0 = (n_out - 1) // where * where
+    spots = [s for s in range(4, n_out - 12, 4 if method == "exh" else 8)]   # one maximum each, clear of chunk edges
+    inside = [s for s in spots if s >= tile0]
+    for count in (0, limit, limit + 1):
+        if count > len(inside):
+            assert segment == 256                      # (a tile of 256 slots has no room for 65 spikes 8 apart)
+            count = len(inside)
+        x = np.zeros((3, n), np.float32)
+        x[1, n_out] = 30.0                             # slots n_out - 1, n_out: 21 and 30
+        x[1, inside[:count]] = 10.0
+        x[1, [s for s in spots if s < tile0]] = 10.0   # (other tiles: as many as there are)
+        t = [torch.from_numpy(a).to(dev) for a in (x, np.zeros(3, np.float32), np.ones(3, np.float32))]
+        l_end = 2 if method == "exh" else 4
+        r = spd.search(*t, spd.Config(method, l_end, threshold=9.0, planes=planes, segment=segment), n_out=n_out)
+        torch.cuda.synchronize()
+        got = {(int(c["level"]), int(c["dm"]), int(c["start"])) for c in r.candidates_host()}
+        assert ((0, 1, n_out - 1) in got) == (count > limit), count
+        assert {(0, 1, s) for s in inside[:count]} <= got
