@@ -354,3 +354,24 @@ def test_readout_gradient_of_many_tiles(P):
     tol = 113 * 2.0 ** -24 + 3e-6
     assert np.abs(np.asarray(g["wh"], np.float64) / (b3 * sig) - 1.0).max() <= tol
     assert abs(float(g["bh"]) / sig - 1.0) <= tol
+
+
+def test_backward_forms_the_forward_activations(P):
+    """The backward launch forms a row's activations again.  With a read-out so steep that one position holds
+    the whole softmax, d loss / d bh is exp(s - lse) there with s formed again and lse from the forward
+    launch: exactly 1 if both formed the same activations and scores, and e^+-9 or more from it if a single
+    activation differed by one bfloat16 step."""
+    tiles = 16
+    exact = 0
+    for i in range(tiles):
+        _, feat = make_batch(P, 1, seed=300 + i)
+        net = oracle_net(70 + i)
+        net.wh = net.wh * 2e4
+        N = P.Network(packed(P, net), max_tiles=1)
+        lg = torch.empty(1, device="cuda")
+        N.backward(feat, torch.zeros(1, device="cuda"), 1, logits=lg)
+        assert float(lg.item()) > 100.0                # sigmoid 1, so d loss / d logit is 1
+        g = P.unpack(N.grads.cpu().numpy())
+        assert abs(float(g["bh"]) - 1.0) <= 1e-6
+        exact += float(g["bh"]) == 1.0
+    assert exact >= tiles // 2
