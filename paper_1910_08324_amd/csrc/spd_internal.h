@@ -121,7 +121,7 @@ struct StepArgs {
     int64_t ld_rho;
     int32_t n_rho;
     int32_t lds_sc;           // LDS offset (floats) of the per-row width scales (rho != null)
-    int32_t write_planes;     // store the planes (else the peak finder recomputes what it reads)
+    int32_t write_planes;     // store the planes (else the peak finder reads the chunk records)
     int32_t nth;              // threads per work-group (the planner's choice; single-beam launches)
     RecStep *rec;             // where the first work-group records the step, or null
     // candidates only (else null): the record of a chunk with a slot above the threshold is at
@@ -196,7 +196,7 @@ struct ExhArgs {
     int32_t want_cand;
     float threshold;
     // tile-gated search: only work items in tiles whose flag is set are searched (the others
-    // record no pre-candidates and leave the planes untouched); null = every item
+    // leave their chunk bit clear and the planes untouched); null = every item
     const uint8_t *tile_flag;   // [n_row_tiles][n_col_tiles]
     int32_t tile_rows, tile_len, n_col_tiles;
 };

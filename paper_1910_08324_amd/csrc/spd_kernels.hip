@@ -587,11 +587,13 @@ __device__ __forceinline__ void step_tile(const StepArgs &A, const G &V, const i
     // A wave whose groups lie in the plane and, at every width, in the data (one scalar comparison)
     // runs a compiled-in bank with no test per lane; the others the generic one.
     // What is needed only where a chunk has a slot above the threshold stays in step_chunk, out of
-    // this loop's registers: the scalar unit, one for the whole CU, bounds the light width sets (79%
-    // busy, 874 scalar instructions per wave of an IG(1) tile of 4096, when tests per lane and the
-    // candidates' addresses were here; 571-664 now).  Before -> after, at equal tiles: eight uneven
-    // beams candidates only 2741 -> 2135 us, 1024 x 131072 BD-16 909 -> 793, 500 x 100003 IG(1) (rows
-    // of any alignment take float4 loads) 241 -> 200.
+    // this loop's registers: the scalar unit, one for the whole CU, bounds the light width sets (eight
+    // uneven beams, IG(1) candidates only: 919 scalar instructions per wave of a tile of 4096 when
+    // tests per lane and the candidates' addresses were here, 654 now, 0.74 a clock).  Before -> after,
+    // at equal tiles: those beams 2741 -> 2135 us, 1024 x 131072 BD-16 909 -> 793, 500 x 100003 IG(1)
+    // (rows of any alignment take float4 loads) 241 -> 200; and 2000 -> 1925, 683 -> 676 and 197 -> 192
+    // since launches with planes set their chunk bits here and the maxima at a row's end are left to
+    // the peak finder.
     // Reading a window ahead of the barrier, which paid while LDS was the bound, and several
     // batches per barrier are slower now (batch 2245 and 2630 us).
     constexpr int kNW = (kGroup + Fam<FAM>::U1 - 1 + 3) / 4;
@@ -817,7 +819,9 @@ __global__ __launch_bounds__(NTH, (Fam<FAM>::WAVES)) void step_kernel(const Step
 
 // One launch for many beams (same levels and tile length, any sizes): a persistent grid walks
 // the work items (beam, DM row, tile) in order; item i belongs to the beam b with
-// item_base[b] <= i < item_base[b + 1].
+// item_base[b] <= i < item_base[b + 1].  (The beam's fields and the loop cost registers: candidates
+// only, the compiled-in families' first steps keep 2 to 7 VGPRs and 54 to 106 SGPRs a wave in spill
+// slots, a single beam's none and 1 to 36; with planes none but IG(3), 4 VGPRs.)
 template <bool FIRST, int FAM, bool W>
 __global__ __launch_bounds__(kStepThreads, (Fam<FAM>::WAVES)) void step_kernel_batch(const StepBatchArgs B) {
     extern __shared__ __attribute__((aligned(16))) float lds[];
@@ -870,8 +874,11 @@ __global__ __launch_bounds__(kStepThreads, (Fam<FAM>::WAVES)) void step_kernel_b
 // plain evaluation, since such groups come in runs.  On white noise about one group in six is
 // evaluated up to L_end 8192, half of those below 1024, so bounds start at width 257.  Measured:
 // 128 x 131072 at L_end 8192 7.63 -> 5.78 ms (2.0 instead of 2.9 vector instructions per pair, 85% of
-// the issue rate); 64 x 65536 at L_end 256, where the replay's fetches one after another cost as
-// much as the widths, 137 -> 111 us.
+// the issue rate; 6 VGPRs spill at 6 waves per SIMD); 64 x 65536 at L_end 256, where the replay's
+// fetches one after another cost as much as the widths, 137 -> 111 us.  Rows on which bounds are paid
+// and fail are no slower than without them: 32 x 65536 samples, 18 kinds of rows (trends, steps of 64
+// to 4096, offsets, sines, red noise, spikes, constants) take 0.66 to 0.88 of the time at L_end 1000
+// and 4096.
 __device__ __forceinline__ float load_z(const float *xr, int r, int n_in, float mu, float inv) {
     return r < n_in ? (xr[r] - mu) * inv : 0.0f;
 }
@@ -1227,16 +1234,16 @@ __global__ __launch_bounds__(64, 6) void exh_kernel(const ExhArgs A) {
 // groups before its own, tests again (where there is anything to write) and writes the list.
 // What bounds it is the latency of the chain word -> neighbours' words -> values, hence many
 // small groups: a bright pulse sets a run of chunks, and a wave that takes a long range of slabs
-// spends its time on that run alone.  Both passes together, against pre-candidate lists of 64 a slab
+// spends its time on that run alone.  Both passes together, against lists of 64 candidates a slab
 // with dense rescans of the slabs that overflowed them, a scan kernel between: 500 x 95908 slots
 // IG(1) 162 -> 21 us; 1024 x 131072 BD-16 269 -> 30 us; 4096 x 262144 IG(1) 253 -> 95 us;
-// 512 x 131072 BD-32 candidates only (its rescans formed every slot of a tile again) 4290 -> 32 us.
+// 512 x 131072 BD-32 candidates only (its rescans formed every slot of a tile again) 4290 -> 33 us.
 //
 // Values come from the planes or, candidates only, from the records the cascade left of every
-// such chunk.  A chunk that found no room for its record has its slots formed again from the step's record:
-// the units of the level as pairwise sums of the step's input series (level by level, as the
-// cascade forms them), the BoxDIT carried prefix through the levels below, and the level's
-// widths in increasing order with the same FP32 operations as step_tile, so value and width
+// such chunk.  A chunk that found no room for its record has its slots formed again from the step's
+// record (form_slots): the units of the level as pairwise sums of the step's input series, level by
+// level as the cascade forms them, the BoxDIT carried prefix through the levels below, and the
+// level's widths in increasing order with the same FP32 operations as step_tile, so value and width
 // are bitwise those the planes would hold.
 // ----------------------------------------------------------------------------------------
 constexpr int kPeakThreads = 256;

@@ -8,7 +8,9 @@
 // first call on a device, with that device current, resolves the device address of its copy
 // with hipGetSymbolAddress and keeps it; every later call on that device uses the kept address.
 //
-// Nothing in the workspace needs clearing between calls: every chunk bit, record and total is written by the launch that produces it before any kernel reads it.
+// The caller has nothing to clear between calls: every chunk bit, record and total is written by the
+// launch that produces it before any kernel reads it, and the counters of the records' pool are cleared
+// by the call's own first launch.
 // Calls on one GPU share the array, so calls that overlap in time on one GPU (several streams or
 // threads) race on it; such callers serialise their calls.
 #include <hip/hip_runtime.h>
